@@ -72,7 +72,7 @@ typedef struct {
     int want_energy;   /* nonzero: info->energy = Tr[D H] (the observable of Alg. 1) */
     int tile;          /* output tile edge of the squaring kernels: 0 = automatic, or 64/128/256 */
     int kernel;        /* split-mode squaring schedule: 0 = automatic, 1 = one workgroup per
-                          tile (direct-to-LDS pipeline for tiles 128/256), 8 = one workgroup
+                          tile (direct-to-LDS pipeline), 8 = one workgroup
                           per tile with register staging (every tile), 2..7 = persistent schedule (whole rounds of tiles, then the
                           leftover tiles split along K), kernel variant 0..5 for the tile,
                           as (waves, K-slice halves, LDS stages, rolling fragment pipeline:
@@ -81,11 +81,13 @@ typedef struct {
                             128: (4,32,4,0) (4,64,2,0) (4,16,4,0) (4,32,2,0) (4,64,2,1) (4,32,2,1)
                           Only split modes with tiles of 128/256 use these.  FP64 mode:
                           0 = automatic, 1 = register-staged kernel, 2 / 3 / 4 = direct-to-LDS
-                          kernel (128 tiles) with (4 waves, 2 stages) / (4, 4) / (8, 4),
-                          one workgroup per tile, 5 = the (8, 4) kernel on the persistent
-                          schedule (whole rounds + split-K tail; per-tile where there are
-                          fewer tiles than CUs).  The automatic choice (5, else 4) also
-                          serves the FP64 refinement layer of every mode; 6, 7 are invalid. */
+                          kernel on 128 tiles with (4 waves, 2 stages) / (4, 4) / (8, 4),
+                          one workgroup per tile, 5 = direct-to-LDS kernel on 64 x 64 tiles
+                          with the tiles beyond the last whole round of one per CU cut into
+                          32 x 32 ones.  0 is 5 at every size and tile (the tile then only
+                          sets n_padded), and so are 2 / 3 / 4 on 64 tiles; every kernel but
+                          1 gives the same bits.  The automatic choice also serves the FP64
+                          refinement layer of every mode; 6, 7 are invalid. */
     int accelerate;    /* nonzero: accelerated Deep-NN SP2 (Sec. Accelerated Deep-NN SP2).  With
                           the occupied eigenvalues of S_{n-1} known to lie in [h, 1] and the
                           unoccupied ones in [0, l] (from homo, lumo below and the spectral

@@ -19,11 +19,11 @@ hipError_t launch_sk_t(int tile, int variant, const SquareArgs& a, const StreamK
     return hipErrorInvalidValue;
 }
 template <typename T16>
-hipError_t launch_dp_t(int tile, int variant, const SquareArgs& a, const SquareArgs* descs, const int* map, int per,
+hipError_t launch_dp_t(int tile, int variant, const SquareArgs& a, const SquareArgs* descs, const TileRef* map, int per,
                        hipStream_t s);
-extern template hipError_t launch_dp_t<_Float16>(int, int, const SquareArgs&, const SquareArgs*, const int*, int,
+extern template hipError_t launch_dp_t<_Float16>(int, int, const SquareArgs&, const SquareArgs*, const TileRef*, int,
                                                  hipStream_t);
-extern template hipError_t launch_dp_t<__bf16>(int, int, const SquareArgs&, const SquareArgs*, const int*, int,
+extern template hipError_t launch_dp_t<__bf16>(int, int, const SquareArgs&, const SquareArgs*, const TileRef*, int,
                                                hipStream_t);
 
 // Variants of the persistent kernel per tile edge: (waves, slice width in halves, LDS
@@ -107,7 +107,7 @@ hipError_t launch_square_dp(int precision, int tile, int variant, const SquareAr
     if (precision == SP2_BF16X2) return launch_dp_t<__bf16>(tile, variant, a, nullptr, nullptr, 0, s);
     return hipErrorInvalidValue;
 }
-hipError_t launch_square_dp_g(int precision, int tile, int variant, const SquareArgs* descs, const int* map, int per,
+hipError_t launch_square_dp_g(int precision, int tile, int variant, const SquareArgs* descs, const TileRef* map, int per,
                               hipStream_t s) {
     const SquareArgs unused{};
     if (precision == SP2_FP16X2) return launch_dp_t<_Float16>(tile, variant, unused, descs, map, per, s);

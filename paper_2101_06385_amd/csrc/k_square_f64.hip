@@ -1,9 +1,16 @@
 // FP64 squaring layer Y = alpha X^2 + beta X + gamma I on v_mfma_f64_16x16x4f64 (gfx950),
 // for the refinement layer (Eq. Refinement, computed in double precision) and the FP64
-// mode.  Upper-triangle 128 x 128 output tiles, one workgroup per tile of 4 waves (2 x 2
-// waves of 64 x 64, 4 x 4 blocks of 16 x 16 each) or 8 waves (2 x 4 waves of 64 x 32),
-// mirrored on store.
+// mode.  Upper-triangle output tiles, one workgroup per tile, mirrored on store.
 //
+//  * Bound: the matrix pipes (64 cycles per v_mfma_f64_16x16x4f64, 78.6 TFLOP/s).  Several
+//    independent workgroups of 4 waves per CU keep them busy: one's prologue, barriers and
+//    epilogue hide behind the others' products.  64 x 64 tiles with two 16 KB stages fit
+//    five to a CU; the tiles beyond the last whole round of one per CU are cut into 32 x 32
+//    ones so that the end of the launch is spread over the chip (k_square_f64_mix).
+//    One layer, against the 8-wave 128 x 128 workgroups with one per CU (and their
+//    persistent form with a split-K tail) used before: n = 256 17 -> 7.3 us, 832 128 -> 25 us,
+//    2112 290 -> 167 us, 4096 1265 -> 1036 us (66 TFLOP/s), 5120 2233 -> 2015 us, 8192
+//    8.90 -> 8.74 ms (there the panels' L2 misses count too).
 //  * K-stages of 16 doubles: each row of a stage is one 128-byte line.  The two row
 //    panels (I and J: X is symmetric, so both operands are K-contiguous rows) go straight
 //    from global memory into LDS with global_load_lds_dwordx4 (16 bytes per lane, a
@@ -14,7 +21,9 @@
 //    the 16 lanes of each ds_read_b128 pass hit distinct bank groups.
 //  * The K order inside a stage is permuted per lane: MFMA s (0, 1) of unit h (0, 1) takes,
 //    in its K lane j = lane / 16, the K index 8 h + 2 j + s.  A and B use the same map, so
-//    every product term appears once; one 16-byte read then feeds two MFMAs.
+//    every product term appears once; one 16-byte read then feeds two MFMAs.  Every tile
+//    edge runs the same chain of products per element, so the tiling changes no bit.
+#include "sp2_control.h"
 #include "sp2_internal.h"
 
 namespace sp2 {
@@ -23,14 +32,25 @@ namespace {
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kBT = 128;           // output tile edge
 constexpr int kBK = 16;            // doubles per row per stage
 constexpr int kRow = kBK * 8;      // 128 bytes
-constexpr int kArr = kBT * kRow;   // bytes of one panel stage
-constexpr int kStage = 2 * kArr;   // panels I and J
 constexpr int kRPB = 1024 / kRow;  // rows per 1 KB direct-load block (8)
-constexpr int kBPR = kBT / kRPB;   // blocks per panel stage (16)
-constexpr int kMB = 4;                 // 16 x 16 blocks per wave along rows (64 rows)
+
+// BT x BT output tile, WM x WN waves, ST LDS stages of 2 BT rows (panels I and J).
+template <int BT, int WM, int WN, int ST>
+struct F64Cfg {
+    static constexpr int NW = WM * WN, NT = 64 * NW;
+    static constexpr int WTM = BT / WM, WTN = BT / WN;
+    static constexpr int MB = WTM / 16, NB = WTN / 16;   // 16 x 16 blocks per wave
+    static constexpr int ARR = BT * kRow;                // bytes of one panel stage
+    static constexpr int STAGE = 2 * ARR;
+    static constexpr int BPR = BT / kRPB;                // 1 KB blocks per panel stage
+    static constexpr int LPW = 2 * BPR / NW;             // direct loads per wave per stage
+    static constexpr int LDS = ST * STAGE;
+    static constexpr int STRIP = 1024 / BT;              // tile_of strip: 1024 columns
+    static_assert(MB >= 1 && NB >= 1 && (2 * BPR) % NW == 0, "tile / wave mismatch");
+    static_assert(LPW * (ST - 1) <= 24, "vmcnt range of wait_vm");
+};
 
 __device__ inline int swz8(int r) { return (r >> 1) & 7; }
 
@@ -38,13 +58,14 @@ typedef __attribute__((address_space(3))) unsigned char lds_byte;
 __device__ __forceinline__ unsigned lds_addr(const unsigned char* p) {
     return (unsigned)(uintptr_t)(const lds_byte*)p;
 }
-__device__ __forceinline__ void dma16(const void* g, unsigned lds_base) {
+// wave-uniform base in SGPRs and a 32-bit per-lane byte offset
+__device__ __forceinline__ void dma16s(unsigned voff, const void* sbase, unsigned lds_base) {
     asm volatile(
-        "s_mov_b32 m0, %1\n\t"
+        "s_mov_b32 m0, %2\n\t"
         "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %0, off"
+        "global_load_lds_dwordx4 %0, %1"
         :
-        : "v"(g), "s"(lds_base)
+        : "v"(voff), "s"(sbase), "s"(lds_base)
         : "memory", "m0");
 }
 
@@ -54,7 +75,11 @@ __device__ __forceinline__ void dma16(const void* g, unsigned lds_base) {
 __device__ __forceinline__ void wait_vm(int n) {
     if (n >= 24) SP2_VMCNT(24);
     else if (n >= 16) SP2_VMCNT(16);
+    else if (n >= 12) SP2_VMCNT(12);
     else if (n >= 8) SP2_VMCNT(8);
+    else if (n >= 6) SP2_VMCNT(6);
+    else if (n >= 4) SP2_VMCNT(4);
+    else if (n >= 2) SP2_VMCNT(2);
     else SP2_VMCNT(0);
 }
 #undef SP2_VMCNT
@@ -64,162 +89,110 @@ __device__ inline double wsum(double v) {
     return v;
 }
 
-// WN waves across the tile's columns (2: 4 waves of 64 x 64, 4: 8 waves of 64 x 32)
-// One work item: tile t over K-stages [kb, ke).  chunk < 0: the whole tile, epilogue here;
-// otherwise one K-chunk of tail tile `tail_tile`: the FP64 partial goes to slot v of
-// sk.partial and the last arriving chunk sums the chunks in order and runs the epilogue.
-template <int ST, int WN>
-__device__ __forceinline__ void f64_body(const SquareArgs& a, int t, int kb, int ke, int chunk, int tail_tile,
-                                         int v, const StreamK& sk, unsigned char* __restrict__ lds,
-                                         double* __restrict__ red, int* __restrict__ s_flag) {
+// Output tile (I, J) of edge BT over all of K; t is the tile's slot in a.parts.
+template <int BT, int WM, int WN, int ST>
+__device__ __forceinline__ void f64_body(const SquareArgs& a, int I, int J, int t, unsigned char* __restrict__ lds,
+                                         double* __restrict__ red, int* __restrict__ s_done) {
+    typedef F64Cfg<BT, WM, WN, ST> C;
+    constexpr int MB = C::MB, NB = C::NB, LPW = C::LPW;
     static_assert(ST >= 2 && ST <= 4, "stages");
-    constexpr int kNW = 2 * WN;
-    constexpr int kLPW = 2 * kBPR / kNW;   // direct loads per wave per stage
-    constexpr int kNB = kBT / (16 * WN);   // 16 x 16 blocks per wave along columns
-    constexpr int WTN = kBT / WN;
-    int I, J;
-    tile_of(t, a.T, 8, &I, &J);
     const int np = a.np;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
     const double* x = (const double*)a.x0;
-    const double* src[2] = {x + (size_t)I * kBT * np, x + (size_t)J * kBT * np};
-    const int nsl = ke - kb;
+    const unsigned char* src[2] = {(const unsigned char*)(x + (size_t)I * BT * np),
+                                   (const unsigned char*)(x + (size_t)J * BT * np)};
+    const int nsl = (a.n_real + kBK - 1) / kBK;   // X is zero beyond n_real
 
-    // direct load: lane L fills bytes [16 L, 16 L + 16) of block q: panel row q * 8 + L / 8,
-    // physical chunk L % 8 = logical chunk (L % 8) ^ swz8(row)
+    // direct load l of this wave: lane L fills bytes [16 L, 16 L + 16) of a 1 KB block:
+    // panel row q * 8 + L / 8, physical chunk L % 8 = logical chunk (L % 8) ^ swz8(row)
+    unsigned voff[LPW];
+#pragma unroll
+    for (int l = 0; l < LPW; ++l) {
+        const int row = ((wave * LPW + l) % C::BPR) * kRPB + (lane >> 3);
+        voff[l] = (unsigned)row * (unsigned)np * 8u + (unsigned)(((lane & 7) ^ swz8(row)) << 4);
+    }
+    auto load_one = [&](int l, int buf, int ks) {
+        const int j = wave * LPW + l;
+        const int arr = j / C::BPR, qd = j % C::BPR;
+        dma16s(voff[l], src[arr] + (size_t)ks * kRow, lds_addr(lds + buf * C::STAGE + arr * C::ARR + qd * 1024));
+    };
     auto issue = [&](int buf, int ks) {
 #pragma unroll
-        for (int i = 0; i < kLPW; ++i) {
-            const int j = wave * kLPW + i;
-            const int arr = j / kBPR, qd = j % kBPR;
-            const int row = qd * kRPB + (lane >> 3);
-            const double* g = src[arr] + (size_t)row * np + ks * kBK + (((lane & 7) ^ swz8(row)) << 1);
-            dma16(g, __builtin_amdgcn_readfirstlane(lds_addr(lds + buf * kStage + arr * kArr + qd * 1024)));
-        }
+        for (int l = 0; l < LPW; ++l) load_one(l, buf, ks);
     };
     // fragments of unit h (K 8h .. 8h+7) of the stage in buffer buf: lane reads the 16-byte
     // logical chunk 4h + lane / 16 of row (block base + lane % 16)
-    auto frags = [&](int buf, int h, f64x2 (&fa)[kMB], f64x2 (&fb)[kNB]) {
+    auto frags = [&](int buf, int h, f64x2 (&fa)[MB], f64x2 (&fb)[NB]) {
         const int r16 = lane & 15;
-        const unsigned char* base = lds + buf * kStage;
+        const unsigned char* base = lds + buf * C::STAGE;
 #pragma unroll
-        for (int m = 0; m < kMB; ++m) {
-            const int row = wm * 64 + m * 16 + r16;
+        for (int m = 0; m < MB; ++m) {
+            const int row = wm * C::WTM + m * 16 + r16;
             fa[m] = *(const f64x2*)(base + row * kRow + ((((h << 2) + (lane >> 4)) ^ swz8(row)) << 4));
         }
 #pragma unroll
-        for (int n = 0; n < kNB; ++n) {
-            const int row = wn * WTN + n * 16 + r16;
-            fb[n] = *(const f64x2*)(base + kArr + row * kRow + ((((h << 2) + (lane >> 4)) ^ swz8(row)) << 4));
+        for (int n = 0; n < NB; ++n) {
+            const int row = wn * C::WTN + n * 16 + r16;
+            fb[n] = *(const f64x2*)(base + C::ARR + row * kRow + ((((h << 2) + (lane >> 4)) ^ swz8(row)) << 4));
         }
     };
 
-    f64x4 acc[kMB][kNB];
+    f64x4 acc[MB][NB];
 #pragma unroll
-    for (int m = 0; m < kMB; ++m)
+    for (int m = 0; m < MB; ++m)
 #pragma unroll
-        for (int n = 0; n < kNB; ++n) acc[m][n] = f64x4{0.0, 0.0, 0.0, 0.0};
-    auto mma = [&](const f64x2 (&fa)[kMB], const f64x2 (&fb)[kNB]) {
+        for (int n = 0; n < NB; ++n) acc[m][n] = f64x4{0.0, 0.0, 0.0, 0.0};
+    // the MFMAs of one unit; with doit the direct loads of stage ks (into buffer buf) are
+    // spread between them, so that their issue overlaps the matrix cores (scheduling barriers
+    // keep the compiler from regrouping them)
+    auto mma = [&](const f64x2 (&fa)[MB], const f64x2 (&fb)[NB], bool doit, int buf, int ks) {
+        constexpr int NM = 2 * MB * NB;
+        constexpr int EVERY = NM / LPW;
+        static_assert(EVERY >= 1 && NM % LPW == 0, "interleave");
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int m = 0; m < kMB; ++m)
-#pragma unroll
-                for (int n = 0; n < kNB; ++n)
-                    acc[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[m][s], fb[n][s], acc[m][n], 0, 0, 0);
+        for (int i = 0; i < NM; ++i) {
+            const int s = i / (MB * NB), m = (i / NB) % MB, n = i % NB;
+            acc[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[m][s], fb[n][s], acc[m][n], 0, 0, 0);
+            if (i % EVERY == EVERY - 1) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (doit) load_one(i / EVERY, buf, ks);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
     };
 
     // stage q is issued by advance(q - ST + 1); the prologue plays those of 0 .. ST - 1
     const int pro = nsl < ST ? nsl : ST;
-    for (int q = 0; q < pro; ++q) issue(q, kb + q);
-    wait_vm((pro - 1) * kLPW);
+    for (int q = 0; q < pro; ++q) issue(q, q);
+    if (a.skip && *a.skip) {   // read while the first loads are in flight
+        wait_vm(0);
+        return;
+    }
+    wait_vm((pro - 1) * LPW);
     __syncthreads();
-    f64x2 pa[kMB], pb[kNB], qa[kMB], qb[kNB];
+    f64x2 pa[MB], pb[NB], qa[MB], qb[NB];
     frags(0, 0, pa, pb);
     // stage `next` readable: its loads landed (this wave's), every wave past the barrier
     auto arrive = [&](int next) {
         const int last = (next + ST - 2 < nsl - 1) ? next + ST - 2 : nsl - 1;
-        wait_vm((last - next) * kLPW);
+        wait_vm((last - next) * LPW);
         __syncthreads();
-    };
-    // the MFMAs of one unit with the direct loads of stage ks (into buffer buf) spread
-    // between them, so that their address arithmetic and issue overlap the matrix cores;
-    // scheduling barriers keep the compiler from regrouping them
-    auto mma_issue = [&](const f64x2 (&fa)[kMB], const f64x2 (&fb)[kNB], int buf, int ks, bool doit) {
-        constexpr int NM = 2 * kMB * kNB;
-        constexpr int EVERY = NM / kLPW;
-        static_assert(EVERY >= 1 && NM % kLPW == 0, "interleave");
-#pragma unroll
-        for (int i = 0; i < NM; ++i) {
-            const int s = i / (kMB * kNB), m = (i / kNB) % kMB, n = i % kNB;
-            acc[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[m][s], fb[n][s], acc[m][n], 0, 0, 0);
-            if (i % EVERY == EVERY - 1) {
-                __builtin_amdgcn_sched_barrier(0);
-                if (doit) {
-                    const int j = wave * kLPW + i / EVERY;
-                    const int arr = j / kBPR, qd = j % kBPR;
-                    const int row = qd * kRPB + (lane >> 3);
-                    const double* g = src[arr] + (size_t)row * np + ks * kBK + (((lane & 7) ^ swz8(row)) << 1);
-                    dma16(g, __builtin_amdgcn_readfirstlane(lds_addr(lds + buf * kStage + arr * kArr + qd * 1024)));
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
     };
     // units: two per stage (h = 0, 1); P holds h = 0 of a stage, Q h = 1.  Stage st + ST
     // refills the buffer of stage st once every wave has read it (after arrive(st + 1)).
     int st = 0;
     for (; st + 1 < nsl; ++st) {
         frags(st % ST, 1, qa, qb);
-        mma(pa, pb);
+        mma(pa, pb, false, 0, 0);
         arrive(st + 1);
         frags((st + 1) % ST, 0, pa, pb);
-        mma_issue(qa, qb, st % ST, kb + st + ST, st + ST < nsl);
+        mma(qa, qb, st + ST < nsl, st % ST, st + ST);
     }
     frags(st % ST, 1, qa, qb);
-    mma(pa, pb);
-    mma(qa, qb);
-
-    // ------------------------------------------------------------------- split tail
-    if (chunk >= 0) {
-        constexpr size_t TILE_D = (size_t)kBT * kBT;
-        f64x4* wp = (f64x4*)(sk.fpartial + (size_t)v * TILE_D) + (size_t)wave * kMB * kNB * 64 + lane;
-#pragma unroll
-        for (int m = 0; m < kMB; ++m)
-#pragma unroll
-            for (int n = 0; n < kNB; ++n) {
-                typedef double f64x2 __attribute__((ext_vector_type(2)));
-                const f64x2 lo = {acc[m][n][0], acc[m][n][1]}, hi = {acc[m][n][2], acc[m][n][3]};
-                st16_agent(wp, __builtin_bit_cast(u32x4_t, lo));
-                st16_agent((char*)wp + 16, __builtin_bit_cast(u32x4_t, hi));
-                wp += 64;
-            }
-        wait_stores();   // this partial is coherent before the arrival is counted
-        __syncthreads();
-        if (tid == 0) *s_flag = atomicAdd(sk.counter + tail_tile, 1);
-        __syncthreads();
-        // each executed layer adds `chunks` arrivals per tail tile: the last one reduces
-        if (((*s_flag + 1) % sk.chunks) != 0) return;
-        const f64x4* rp = (const f64x4*)(sk.fpartial + (size_t)tail_tile * sk.chunks * TILE_D) +
-                          (size_t)wave * kMB * kNB * 64 + lane;
-        const size_t cstride = TILE_D / 4;
-        auto ld = [](const f64x4* q) -> f64x4 {
-            typedef double f64x2 __attribute__((ext_vector_type(2)));
-            const f64x2 lo = __builtin_bit_cast(f64x2, ld16_agent(q));
-            const f64x2 hi = __builtin_bit_cast(f64x2, ld16_agent((const char*)q + 16));
-            return f64x4{lo[0], lo[1], hi[0], hi[1]};
-        };
-#pragma unroll
-        for (int m = 0; m < kMB; ++m)
-#pragma unroll
-            for (int n = 0; n < kNB; ++n) {
-                f64x4 sum = ld(rp);
-                for (int c = 1; c < sk.chunks; ++c) sum += ld(rp + c * cstride);
-                acc[m][n] = sum;
-                rp += 64;
-            }
-    }
+    mma(pa, pb, false, 0, 0);
+    mma(qa, qb, false, 0, 0);
 
     // ------------------------------------------------------------------- epilogue
     const double alpha = a.coef64 ? a.coef64[0] : (double)a.coef[0];
@@ -231,16 +204,16 @@ __device__ __forceinline__ void f64_body(const SquareArgs& a, int t, int kb, int
     const bool diag = (I == J);
     double tr = 0.0, fr = 0.0;
 #pragma unroll
-    for (int m = 0; m < kMB; ++m) {
+    for (int m = 0; m < MB; ++m) {
 #pragma unroll
-        for (int n = 0; n < kNB; ++n) {
-            const int col = J * kBT + wn * WTN + n * 16 + (lane & 15);
+        for (int n = 0; n < NB; ++n) {
+            const int col = J * BT + wn * C::WTN + n * 16 + (lane & 15);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int row = I * kBT + wm * 64 + m * 16 + 4 * r + (lane >> 4);
+                const int row = I * BT + wm * C::WTM + m * 16 + 4 * r + (lane >> 4);
                 if (diag && row > col) continue;
                 const double xv = acc[m][n][r];
-                double y = (beta != 0.0) ? alpha * xv + beta * si[(size_t)col * np + row] : alpha * xv;
+                double y = (beta != 0.0) ? alpha * xv + beta * si[(size_t)row * np + col] : alpha * xv;
                 if (row == col && col < a.n_real) y += gamma;
                 if (row < nv && col < nv) {
                     so[(size_t)row * ldo + col] = y;
@@ -262,126 +235,116 @@ __device__ __forceinline__ void f64_body(const SquareArgs& a, int t, int kb, int
             red[2 * wave] = tr;
             red[2 * wave + 1] = fr;
         }
-        __syncthreads();
+        __syncthreads();   // also: every wave has left the stages, whose LDS the control reuses
         if (tid == 0) {
             double s0 = 0.0, s1 = 0.0;
-            for (int w = 0; w < kNW; ++w) {
+            for (int w = 0; w < C::NW; ++w) {
                 s0 += red[2 * w];
                 s1 += red[2 * w + 1];
             }
-            a.parts[2 * t] = s0;
-            a.parts[2 * t + 1] = s1;
+            st_agent(a.parts + 2 * t, s0);
+            st_agent(a.parts + 2 * t + 1, s1);
         }
+        tile_done(a, (double*)lds, s_done);
     }
 }
 
-template <int ST, int WN>
-__global__ __launch_bounds__(128 * WN) void k_square_f64(SquareArgs a) {
-    __shared__ __attribute__((aligned(16))) unsigned char lds[ST * kStage];
-    __shared__ double red[4 * WN];
-    __shared__ int s_flag;
-    if (a.skip && *a.skip) return;
+// One workgroup per BT x BT tile of one problem.
+template <int BT, int WM, int WN, int ST>
+__global__ __launch_bounds__(64 * WM * WN) void k_square_f64(SquareArgs a) {
+    typedef F64Cfg<BT, WM, WN, ST> C;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[C::LDS];
+    __shared__ double red[2 * C::NW];
+    __shared__ int s_done;
     const int t = xcd_tile_index(blockIdx.x, a.per, a.ntiles);
     if (t < 0) return;
-    StreamK none;
-    none.grid = 0;
-    none.rounds = 0;
-    none.tail_tiles = 0;
-    none.chunks = 1;
-    none.partial = nullptr;
-    none.counter = nullptr;
-    none.fpartial = nullptr;
-    f64_body<ST, WN>(a, t, 0, a.np / kBK, -1, 0, 0, none, lds, red, &s_flag);
+    int I, J;
+    tile_of(t, a.T, C::STRIP, &I, &J);
+    f64_body<BT, WM, WN, ST>(a, I, J, t, lds, red, &s_done);
 }
 
-// Persistent: sk.grid workgroups run whole rounds of tiles, then the leftover tiles cut into
-// sk.chunks K-chunks each (the same schedule as the persistent split squaring).
-template <int ST, int WN>
-__global__ __launch_bounds__(128 * WN) void k_square_f64_sk(SquareArgs a, StreamK sk) {
-    __shared__ __attribute__((aligned(16))) unsigned char lds[ST * kStage];
-    __shared__ double red[4 * WN];
-    __shared__ int s_flag;
-    if (a.skip && *a.skip) return;
-    const int G = sk.grid;
-    const int v = (blockIdx.x & 7) * (G >> 3) + (blockIdx.x >> 3);   // XCD-aware order
-    const int nsl_all = a.np / kBK;
-    const int items = sk.rounds + ((sk.tail_tiles > 0 && v < sk.tail_tiles * sk.chunks) ? 1 : 0);
-    for (int item = 0; item < items; ++item) {
-        if (item < sk.rounds) {
-            f64_body<ST, WN>(a, item * G + v, 0, nsl_all, -1, 0, v, sk, lds, red, &s_flag);
-        } else {
-            const int tail_tile = v / sk.chunks, chunk = v % sk.chunks;
-            const int kb = (int)(((long long)chunk * nsl_all) / sk.chunks);
-            const int ke = (int)(((long long)(chunk + 1) * nsl_all) / sk.chunks);
-            f64_body<ST, WN>(a, sk.rounds * G + tail_tile, kb, ke, chunk, tail_tile, v, sk, lds, red, &s_flag);
-        }
-        __syncthreads();   // LDS is reused by the next item
+// 64-tiles [0, nmain) whole (nmain a multiple of 8), the others as four 32-tiles each.
+typedef F64Cfg<64, 2, 2, 2> F64Main;
+typedef F64Cfg<32, 2, 2, 2> F64Sub;
+__global__ __launch_bounds__(256) void k_square_f64_mix(SquareArgs a, int nmain) {
+    __shared__ __attribute__((aligned(16))) unsigned char lds[F64Main::LDS];
+    __shared__ double red[2 * F64Main::NW];
+    __shared__ int s_done;
+    int I, J;
+    if ((int)blockIdx.x < nmain) {
+        const int t = (blockIdx.x & 7) * (nmain >> 3) + (blockIdx.x >> 3);
+        tile_of(t, a.T, F64Main::STRIP, &I, &J);
+        f64_body<64, 2, 2, 2>(a, I, J, t, lds, red, &s_done);
+        return;
     }
+    const int nsub = a.ntiles - nmain;
+    const int u = xcd_tile_index(blockIdx.x - nmain, (nsub + 7) >> 3, nsub);
+    if (u < 0) return;
+    tile_of(nmain + (u >> 2), a.T, F64Main::STRIP, &I, &J);
+    const int i = 2 * I + ((u >> 1) & 1), j = 2 * J + (u & 1), slot = nmain + u;
+    if (i > j) {   // below the diagonal: its mirror computes it
+        if (a.skip && *a.skip) return;
+        if (!a.parts) return;
+        if (threadIdx.x == 0) {
+            st_agent(a.parts + 2 * slot, 0.0);
+            st_agent(a.parts + 2 * slot + 1, 0.0);
+        }
+        tile_done(a, (double*)lds, &s_done);
+        return;
+    }
+    f64_body<32, 2, 2, 2>(a, i, j, slot, lds, red, &s_done);
 }
 
-// grouped: block b computes the tile that the tile map names for it (see kTileMapShift)
-template <int ST, int WN>
-__global__ __launch_bounds__(128 * WN) void k_square_f64_g(const SquareArgs* __restrict__ descs,
-                                                          const int* __restrict__ map, int per) {
-    __shared__ __attribute__((aligned(16))) unsigned char lds[ST * kStage];
-    __shared__ double red[4 * WN];
-    const int e = map[(blockIdx.x & 7) * per + (blockIdx.x >> 3)];
-    if (e < 0) return;
-    const SquareArgs a = descs[e >> kTileMapShift];
-    if (a.skip && *a.skip) return;
-    __shared__ int s_flag;
-    StreamK none;
-    none.grid = 0;
-    none.rounds = 0;
-    none.tail_tiles = 0;
-    none.chunks = 1;
-    none.partial = nullptr;
-    none.counter = nullptr;
-    none.fpartial = nullptr;
-    f64_body<ST, WN>(a, e & kTileMapMask, 0, a.np / kBK, -1, 0, 0, none, lds, red, &s_flag);
+// grouped: block b computes the 64-tile that the tile map names for it (see TileRef)
+__global__ __launch_bounds__(256) void k_square_f64_g(const SquareArgs* __restrict__ descs,
+                                                      const TileRef* __restrict__ map, int per) {
+    __shared__ __attribute__((aligned(16))) unsigned char lds[F64Main::LDS];
+    __shared__ double red[2 * F64Main::NW];
+    __shared__ int s_done;
+    const TileRef e = map[(blockIdx.x & 7) * per + (blockIdx.x >> 3)];
+    if (e.problem < 0) return;
+    const SquareArgs a = descs[e.problem];
+    const int t = e.tile;
+    int I, J;
+    tile_of(t, a.T, F64Main::STRIP, &I, &J);
+    f64_body<64, 2, 2, 2>(a, I, J, t, lds, red, &s_done);
 }
 
 }  // namespace
 
-// grouped FP64 layer on 128 tiles (8 waves, 4 stages) over a tile map
-hipError_t launch_square_f64_g(const SquareArgs* descs, const int* map, int per, hipStream_t s) {
-    hipLaunchKernelGGL((k_square_f64_g<4, 4>), dim3(8 * per), dim3(512), 0, s, descs, map, per);
+// Grid of the mixed FP64 launch over `edge` rows: a.T 64-tiles per edge; the largest whole
+// number of 64-tiles per CU stays whole, the rest is cut.  (The CU count only shapes the
+// schedule: every choice gives the same bits.)
+constexpr int kF64Cus = 256;
+void square_f64_mix_grid(int edge, int* T, int* nmain, int* ntiles) {
+    *T = (edge + 63) / 64;
+    const int nt = ntiles_upper(*T);
+    *nmain = nt / kF64Cus * kF64Cus;
+    *ntiles = *nmain + 4 * (nt - *nmain);
+}
+
+hipError_t launch_square_f64_mix(const SquareArgs& a, hipStream_t s) {
+    int T, nmain, ntiles;
+    square_f64_mix_grid(64 * a.T, &T, &nmain, &ntiles);
+    if (ntiles != a.ntiles || a.np % 64 || 64 * T > a.np) return hipErrorInvalidValue;
+    const int nsub = ntiles - nmain;
+    hipLaunchKernelGGL(k_square_f64_mix, dim3(nmain + (nsub + 7) / 8 * 8), dim3(256), 0, s, a, nmain);
     return hipGetLastError();
 }
 
-// Persistent FP64 schedule on 128 tiles: G = CUs (one 8-wave workgroup per CU), whole rounds,
-// then the leftover tiles in G / rem K-chunks (at most one per K-stage).  False when there
-// are fewer tiles than workgroups.
-bool square_f64_sk_plan(int np, int cus, StreamK* sk) {
-    const int nt = ntiles_upper(np / kBT);
-    int g = cus;
-    if (g > kMaxSkGrid) g = kMaxSkGrid;
-    g -= g % 8;
-    if (g < 8 || nt < g) return false;
-    const int nsl = np / kBK;
-    sk->grid = g;
-    sk->rounds = nt / g;
-    sk->tail_tiles = nt % g;
-    sk->chunks = sk->tail_tiles ? g / sk->tail_tiles : 1;
-    if (sk->chunks > nsl) sk->chunks = nsl;
-    return true;
-}
-
-size_t square_f64_sk_partial_bytes() { return (size_t)kMaxSkGrid * kBT * kBT * sizeof(double); }
-
-hipError_t launch_square_f64_sk(const SquareArgs& a, const StreamK& sk, hipStream_t s) {
-    hipLaunchKernelGGL((k_square_f64_sk<4, 4>), dim3(sk.grid), dim3(512), 0, s, a, sk);
+hipError_t launch_square_f64_g(const SquareArgs* descs, const TileRef* map, int per, hipStream_t s) {
+    hipLaunchKernelGGL(k_square_f64_g, dim3(8 * per), dim3(256), 0, s, descs, map, per);
     return hipGetLastError();
 }
 
 // FP64 layer on 128 tiles (n_p a multiple of 128).  variant 0: 4 waves, 2 LDS stages;
 // 1: 4 waves, 4 stages (128 KB); 2: 8 waves, 4 stages.
 hipError_t launch_square_f64(int variant, const SquareArgs& a, hipStream_t s) {
-    if (a.np % kBT) return hipErrorInvalidValue;
+    if (a.np % 128) return hipErrorInvalidValue;
     const int grid = 8 * a.per;
-    if (variant == 0) hipLaunchKernelGGL((k_square_f64<2, 2>), dim3(grid), dim3(256), 0, s, a);
-    else if (variant == 1) hipLaunchKernelGGL((k_square_f64<4, 2>), dim3(grid), dim3(256), 0, s, a);
-    else if (variant == 2) hipLaunchKernelGGL((k_square_f64<4, 4>), dim3(grid), dim3(512), 0, s, a);
+    if (variant == 0) hipLaunchKernelGGL((k_square_f64<128, 2, 2, 2>), dim3(grid), dim3(256), 0, s, a);
+    else if (variant == 1) hipLaunchKernelGGL((k_square_f64<128, 2, 2, 4>), dim3(grid), dim3(256), 0, s, a);
+    else if (variant == 2) hipLaunchKernelGGL((k_square_f64<128, 2, 4, 4>), dim3(grid), dim3(512), 0, s, a);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }

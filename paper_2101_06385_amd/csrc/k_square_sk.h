@@ -23,6 +23,7 @@
 //    16-wide K unit, the LDS reads of the next unit are in flight.
 #pragma once
 
+#include "sp2_control.h"
 #include "sp2_internal.h"
 
 #include <type_traits>
@@ -757,9 +758,10 @@ __device__ __forceinline__ void sk_body(const SquareArgs& a, const StreamK& sk, 
                         s0 += scr[2 * w];
                         s1 += scr[2 * w + 1];
                     }
-                    a.parts[2 * t] = s0;
-                    a.parts[2 * t + 1] = s1;
+                    st_agent(a.parts + 2 * t, s0);
+                    st_agent(a.parts + 2 * t + 1, s1);
                 }
+                tile_done(a, scr + 2 * C::NW, &s_flag);
             }
         }
         __syncthreads();   // LDS is reused by the next item's prologue
@@ -787,18 +789,17 @@ __global__ __launch_bounds__(64 * WM * WN) void k_square_dp(SquareArgs a) {
     none.chunks = 1;
     none.partial = nullptr;
     none.counter = nullptr;
-    none.fpartial = nullptr;
     sk_body<T16, WM, WN, MB, NB, SK, ST, RP, true>(a, none, 0, t);
 }
 
 // One workgroup per upper-triangle tile of many problems: block b computes the tile that
-// the tile map names for it (see kTileMapShift), if any.
+// the tile map names for it (see TileRef), if any.
 template <typename T16, int WM, int WN, int MB, int NB, int SK, int ST, int RP>
 __global__ __launch_bounds__(64 * WM * WN) void k_square_dp_g(const SquareArgs* __restrict__ descs,
-                                                             const int* __restrict__ map, int per) {
-    const int e = map[(blockIdx.x & 7) * per + (blockIdx.x >> 3)];
-    if (e < 0) return;
-    const SquareArgs a = descs[e >> kTileMapShift];
+                                                             const TileRef* __restrict__ map, int per) {
+    const TileRef e = map[(blockIdx.x & 7) * per + (blockIdx.x >> 3)];
+    if (e.problem < 0) return;
+    const SquareArgs a = descs[e.problem];
     if (a.skip && *a.skip) return;
     StreamK none;
     none.grid = 0;
@@ -807,19 +808,19 @@ __global__ __launch_bounds__(64 * WM * WN) void k_square_dp_g(const SquareArgs* 
     none.chunks = 1;
     none.partial = nullptr;
     none.counter = nullptr;
-    none.fpartial = nullptr;
-    sk_body<T16, WM, WN, MB, NB, SK, ST, RP, true>(a, none, 0, e & kTileMapMask);
+    sk_body<T16, WM, WN, MB, NB, SK, ST, RP, true>(a, none, 0, e.tile);
 }
 
 }  // namespace
 
 // Per-tile (one workgroup per tile) forms of the same pipeline.  Variants per tile edge,
 // as (waves, K-slice halves, LDS stages, rolling fragment pipeline): 256: (8, 32, 2, 1),
-// (4, 32, 2, 0); 128: (4, 32, 2, 1), (4, 64, 2, 0), (4, 16, 4, 0).  descs == nullptr: the
+// (4, 32, 2, 0); 128: (4, 32, 2, 1), (4, 64, 2, 0), (4, 16, 4, 0), (4, 64, 2, 1); 64:
+// (4, 32, 4, 0).  descs == nullptr: the
 // single problem `a` (XCD-aware order, grid 8 a.per); otherwise the grouped launch over
 // the tile map (grid 8 per).
 template <typename T16>
-hipError_t launch_dp_t(int tile, int variant, const SquareArgs& a, const SquareArgs* descs, const int* map,
+hipError_t launch_dp_t(int tile, int variant, const SquareArgs& a, const SquareArgs* descs, const TileRef* map,
                        int per, hipStream_t s) {
 #define SP2_L(WM, WN, MB, NB, SK, ST, RP)                                                                   \
     do {                                                                                                   \
@@ -842,6 +843,11 @@ hipError_t launch_dp_t(int tile, int variant, const SquareArgs& a, const SquareA
             case 1: SP2_L(2, 2, 2, 2, 64, 2, 0); break;
             case 2: SP2_L(2, 2, 2, 2, 16, 4, 0); break;
             case 3: SP2_L(2, 2, 2, 2, 64, 2, 1); break;
+            default: return hipErrorInvalidValue;
+        }
+    } else if (tile == 64) {
+        switch (variant) {
+            case 0: SP2_L(2, 2, 1, 1, 32, 4, 0); break;
             default: return hipErrorInvalidValue;
         }
     } else {

@@ -69,8 +69,7 @@ struct Plan {
     int kernel;       // request: 0 = automatic, 1 = one workgroup per tile, 2.. = persistent variant - 2
     bool sk_capable;  // stream-K buffers are part of the workspace
     size_t off_init_parts, off_main_parts, off_gersh, off_dstats, off_s[2], off_p[2][2], off_s64, off_y;
-    size_t off_sk_partial, off_sk_counter, off_f64_partial, off_f64_counter, total;
-    bool f64_sk;      // persistent FP64 layer buffers reserved
+    size_t off_sk_partial, off_sk_counter, total;
 };
 
 // The persistent (whole rounds + split tail) schedule needs a tile of 128 or 256 in a
@@ -104,53 +103,43 @@ bool sk_resolve(const Plan& p, StreamK* sk, int* variant) {
     return square_sk_plan(p.tile_main, *variant, p.np, cus, &per_cu, sk, &T, &nt);
 }
 
-// Split layer with one workgroup per tile: the direct-to-LDS pipeline for 128/256 tiles
-// (kernel option 0/1), the register-staged kernel for 64 tiles or kernel option 8.  On
-// 128 tiles a single problem takes 64-half slices (one workgroup per CU; one layer at
+// Split layer with one workgroup per tile: the direct-to-LDS pipeline (kernel option 0/1),
+// or the register-staged kernel (option 8).  On 128 tiles a single problem takes 64-half slices (one workgroup per CU; one layer at
 // n = 2048: 0.079 against 0.089 ms with 32-half slices and two workgroups per CU, 6144:
 // 0.88 against 0.97 ms); the grouped launches of the batched solve keep the 32-half
 // slices, whose second workgroup per CU hides the prologue and epilogue of the short-K
 // tiles there (114.9 against 116.7 ms per call on the 64-problem batch).
+// On 64 tiles the pipeline has 4 stages of 32 halves (n = 777: 15.4 us per layer with the next
+// layer's control, against 18.2 us + 4.0 us control + 2 us gap register-staged; 2 stages of
+// 64 halves are 4 % slower at n = 777 and 4 % faster at 1500, 4 stages of 64 slower at both).
 constexpr int kKernelLegacyTile = 8;
 constexpr int kDpSingle128 = 3;
 hipError_t launch_split_tile_layer(int precision, int tile, int kernel, const SquareArgs& a, hipStream_t s) {
-    if ((tile == 128 || tile == 256) && kernel != kKernelLegacyTile)
+    if (kernel != kKernelLegacyTile)
         return launch_square_dp(precision, tile, tile == 128 ? kDpSingle128 : 0, a, s);
     return launch_square_split(precision, tile, a, s);
 }
 
-// FP64 layer on 128 tiles: kernel 0 (automatic) = the persistent schedule when `sk` holds a
-// feasible plan, else the per-tile direct-load kernel (8 waves); 2 / 3 / 4 = per-tile
-// variants 0 / 1 / 2; 5 = persistent (per-tile where infeasible); 1 or 64 tiles = the
+// FP64 layer: kernel 0 (automatic) and 5 = 64-tiles with the leftover ones cut into 32-tiles;
+// 2 / 3 / 4 = per-tile variants 0 / 1 / 2 on 128 tiles (on 64 tiles as 0); 1 = the
 // register-staged kernel.
-constexpr int kF64AutoVariant = 2;
-hipError_t launch_f64_layer(int tile, int kernel, const SquareArgs& a, const StreamK* sk, hipStream_t s) {
-    if (tile == 128 && kernel != 1) {
-        if ((kernel == 0 || kernel == 5) && sk && sk->grid > 0) return launch_square_f64_sk(a, *sk, s);
-        return launch_square_f64(kernel >= 2 && kernel <= 4 ? kernel - 2 : kF64AutoVariant, a, s);
-    }
+bool f64_mix_wanted(int tile, int kernel) { return !(kernel == 1 || (tile == 128 && kernel >= 2 && kernel <= 4)); }
+hipError_t launch_f64_layer(int tile, int kernel, const SquareArgs& a, hipStream_t s) {
+    if (f64_mix_wanted(tile, kernel)) return launch_square_f64_mix(a, s);
+    if (kernel >= 2) return launch_square_f64(kernel - 2, a, s);
     return launch_square_plain(SP2_FP64, tile, a, s);
 }
 
-// Persistent FP64 plan for this device, or grid = 0 when infeasible
-StreamK f64_sk_resolve(int np, void* partial, int* counter) {
-    StreamK sk;
-    memset(&sk, 0, sizeof(sk));
-    int dev = 0, cus = 0;
-    if (!partial || !counter) return sk;
-    if (hipGetDevice(&dev) != hipSuccess) return sk;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return sk;
-    if (!square_f64_sk_plan(np, cus, &sk)) {
-        memset(&sk, 0, sizeof(sk));
-        return sk;
+// Tiles of an FP64 layer over `edge` rows in the layout of launch_f64_layer.
+void f64_layer_grid(int tile, int kernel, int np, int edge, int* T, int* ntiles, int* per) {
+    int nmain = 0;
+    if (f64_mix_wanted(tile, kernel)) {
+        square_f64_mix_grid(edge, T, &nmain, ntiles);
+        *per = 0;
+    } else {
+        square_plain_grid(tile, np, T, ntiles, per);
     }
-    sk.fpartial = (double*)partial;
-    sk.counter = counter;
-    return sk;
 }
-
-// workspace for the persistent FP64 layer is reserved once there are enough 128 tiles
-bool f64_sk_space(int np) { return ntiles_upper(np / 128) >= 64; }
 
 int auto_tile_main(int n, bool split) {
     // split modes: 128 tiles from 2048 to 4608 (at 4096 the persistent 128-tile schedule
@@ -182,9 +171,11 @@ void make_plan(int n, const Opts& o, Plan* p) {
     p->init_tiles = init_tiles(p->np);
     if (p->split)
         square_split_grid(p->tile_main, p->np, &p->main_T, &p->main_tiles, &p->main_per);
+    else if (o.precision == SP2_FP64)
+        f64_layer_grid(p->tile_main, kernel, p->np, n, &p->main_T, &p->main_tiles, &p->main_per);
     else
         square_plain_grid(p->tile_main, p->np, &p->main_T, &p->main_tiles, &p->main_per);
-    square_plain_grid(p->tile_ref, p->np, &p->ref_T, &p->ref_tiles, &p->ref_per);
+    f64_layer_grid(p->tile_ref, o.precision == SP2_FP64 ? kernel : 0, p->np, n, &p->ref_T, &p->ref_tiles, &p->ref_per);
     p->gersh_blocks = gershgorin_blocks(n);
     p->dstats_blocks = dstats_blocks(n);
     const size_t np2 = (size_t)p->np * p->np;
@@ -217,13 +208,6 @@ void make_plan(int n, const Opts& o, Plan* p) {
     if (p->sk_capable) off = align_up(off + square_sk_partial_bytes(p->tile_main, p->np));
     p->off_sk_counter = off;
     if (p->sk_capable) off = align_up(off + sizeof(int) * kSkCounterInts);
-    // persistent FP64 layers (refinement on 128 tiles, FP64 mode on 128 tiles)
-    p->f64_sk = ((o.refine && p->tile_ref == 128) || (o.precision == SP2_FP64 && p->tile_main == 128)) &&
-                f64_sk_space(p->np);
-    p->off_f64_partial = off;
-    if (p->f64_sk) off = align_up(off + square_f64_sk_partial_bytes());
-    p->off_f64_counter = off;
-    if (p->f64_sk) off = align_up(off + sizeof(int) * kMaxSkGrid);
     p->total = off;
 }
 
@@ -528,12 +512,6 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
             sk.counter = (int*)(ws + p.off_sk_counter);
             SP2_TRY(launch_zero_ints(sk.counter, kSkCounterInts, s));
         }
-        StreamK f64sk;
-        memset(&f64sk, 0, sizeof(f64sk));
-        if (p.f64_sk) {
-            f64sk = f64_sk_resolve(p.np, ws + p.off_f64_partial, (int*)(ws + p.off_f64_counter));
-            if (f64sk.grid > 0) SP2_TRY(launch_zero_ints(f64sk.counter, kMaxSkGrid, s));
-        }
         SquareArgs a;
         memset(&a, 0, sizeof(a));
         a.parts = main_parts;
@@ -558,6 +536,12 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
         const int chunk = n >= 4096 ? 2 : (n >= 1024 ? 4 : 8);
         ChunkEvents cev(flag.on, (o.max_layers + chunk) / chunk + 1);
         if (!cev.ok) return SP2_EDEVICE;
+        // every split and FP64 kernel but the register-staged ones runs the next layer's control itself
+        const bool fused = (p.split && p.kernel != kKernelLegacyTile) || (o.precision == SP2_FP64 && o.kernel != 1);
+        if (fused) {
+            a.ctl = st;
+            a.host_flag = flag.dev;
+        }
         int waited = 0;   // chunks whose completion the host has observed
         for (int layer = 1; layer <= o.max_layers + 1; ++layer) {
             if (flag.on && layer > 1 && (layer - 1) % chunk == 0) {
@@ -571,7 +555,7 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
             }
             if (layer == 1)
                 SP2_TRY(launch_control_stride(st, init_parts, p.init_tiles, 3, layer, flag.dev, s));
-            else
+            else if (!fused)
                 SP2_TRY(launch_control_stride(st, main_parts, p.main_tiles, 2, layer, flag.dev, s));
             if (layer > o.max_layers) break;
             const int in = (layer - 1) & 1, out = layer & 1;
@@ -588,7 +572,7 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
             else if (p.split)
                 SP2_TRY(launch_split_tile_layer(o.precision, p.tile_main, p.kernel, a, s));
             else if (o.precision == SP2_FP64)
-                SP2_TRY(launch_f64_layer(p.tile_main, o.kernel, a, &f64sk, s));
+                SP2_TRY(launch_f64_layer(p.tile_main, o.kernel, a, s));
             else
                 SP2_TRY(launch_square_plain(o.precision, p.tile_main, a, s));
             SP2_TRY(ev.rec(ev.sq_e[layer], s));
@@ -613,7 +597,7 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
             r.n_valid = p.np;
             r.n_real = n;
             r.coef = st->rcoef[0];
-            SP2_TRY(launch_f64_layer(p.tile_ref, o.precision == SP2_FP64 ? o.kernel : 0, r, &f64sk, s));
+            SP2_TRY(launch_f64_layer(p.tile_ref, o.precision == SP2_FP64 ? o.kernel : 0, r, s));
             SP2_TRY(ev.rec(ev.ref[1], s));
             r.x0 = y;
             r.s_in = y;
@@ -621,7 +605,7 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
             r.ld_out = ldd;
             r.n_valid = n;
             r.coef = st->rcoef[1];
-            SP2_TRY(launch_f64_layer(p.tile_ref, o.precision == SP2_FP64 ? o.kernel : 0, r, &f64sk, s));
+            SP2_TRY(launch_f64_layer(p.tile_ref, o.precision == SP2_FP64 ? o.kernel : 0, r, s));
             SP2_TRY(ev.rec(ev.ref[2], s));
         } else {
             SP2_TRY(launch_select_f64(st, S[0], S[1], o.precision == SP2_FP64, dD, ldd, n, p.np, s));
@@ -796,12 +780,6 @@ int sp2_fermi_apply(const double* dH, int ldh, double* dD, int ldd, int n, int l
         sk.counter = (int*)(ws + p.off_sk_counter);
         SP2_TRY(launch_zero_ints(sk.counter, kSkCounterInts, s));
     }
-    StreamK f64sk;
-    memset(&f64sk, 0, sizeof(f64sk));
-    if (p.f64_sk) {
-        f64sk = f64_sk_resolve(p.np, ws + p.off_f64_partial, (int*)(ws + p.off_f64_counter));
-        if (f64sk.grid > 0) SP2_TRY(launch_zero_ints(f64sk.counter, kMaxSkGrid, s));
-    }
     SquareArgs a;
     memset(&a, 0, sizeof(a));
     a.parts = nullptr;
@@ -830,7 +808,7 @@ int sp2_fermi_apply(const double* dH, int ldh, double* dD, int ldd, int n, int l
         else if (p.split)
             SP2_TRY(launch_split_tile_layer(o.precision, p.tile_main, p.kernel, a, s));
         else if (o.precision == SP2_FP64)
-            SP2_TRY(launch_f64_layer(p.tile_main, o.kernel, a, &f64sk, s));
+            SP2_TRY(launch_f64_layer(p.tile_main, o.kernel, a, s));
         else
             SP2_TRY(launch_square_plain(o.precision, p.tile_main, a, s));
         SP2_TRY(launch_readout(o.precision, acc, S[out], p.np, -c[k + 1], 0.0, 0, s));
@@ -913,6 +891,7 @@ size_t sp2_square_workspace_size(int n, int precision, int tile, int kernel) {
     const int t = tile ? tile : auto_tile_main(n, split);
     int T, nt, per;
     if (split) square_split_grid(t, np, &T, &nt, &per);
+    else if (precision == SP2_FP64) f64_layer_grid(t, kernel, np, np, &T, &nt, &per);
     else square_plain_grid(t, np, &T, &nt, &per);
     size_t off = kAlign;                               // coefficients
     off = align_up(off + sizeof(double) * 2 * nt);     // partials
@@ -921,10 +900,6 @@ size_t sp2_square_workspace_size(int n, int precision, int tile, int kernel) {
     if (sk_wanted(split, t, kernel, np)) {
         off = align_up(off + square_sk_partial_bytes(t, np));
         off = align_up(off + sizeof(int) * kSkCounterInts);
-    }
-    if (precision == SP2_FP64 && t == 128 && (kernel == 0 || kernel == 5) && f64_sk_space(np)) {
-        off = align_up(off + square_f64_sk_partial_bytes());
-        off = align_up(off + sizeof(int) * kMaxSkGrid);
     }
     return off;
 }
@@ -948,6 +923,7 @@ int sp2_square(const void* dX, void* dY, int n, int precision, int tile, int ker
     char* ws = (char*)dWork;
     int T, nt, per;
     if (split) square_split_grid(t, np, &T, &nt, &per);
+    else if (precision == SP2_FP64) f64_layer_grid(t, kernel, np, np, &T, &nt, &per);
     else square_plain_grid(t, np, &T, &nt, &per);
     float* coef = (float*)ws;
     double* parts = (double*)(ws + kAlign);
@@ -997,15 +973,7 @@ int sp2_square(const void* dX, void* dY, int n, int precision, int tile, int ker
         }
     } else if (precision == SP2_FP64) {
         a.x0 = dX;
-        StreamK f64sk;
-        memset(&f64sk, 0, sizeof(f64sk));
-        if (t == 128 && (kernel == 0 || kernel == 5) && f64_sk_space(np)) {
-            void* part = ws + off;
-            off = align_up(off + square_f64_sk_partial_bytes());
-            f64sk = f64_sk_resolve(np, part, (int*)(ws + off));
-            if (f64sk.grid > 0) SP2_TRY(launch_zero_ints(f64sk.counter, kMaxSkGrid, s));
-        }
-        SP2_TRY(launch_f64_layer(t, kernel, a, &f64sk, s));
+        SP2_TRY(launch_f64_layer(t, kernel, a, s));
     } else {
         a.x0 = dX;
         SP2_TRY(launch_square_plain(precision, t, a, s));
@@ -1031,31 +999,32 @@ struct BatchLayout {
     std::vector<int> nontrivial;        // indices of problems that run the recursion
     std::vector<Plan> plans;
     std::vector<size_t> region;         // byte offset of each problem's region
-    size_t off_probs, off_sq, off_offs, off_map, off_stage, total;
+    size_t off_probs, off_sq, off_offs, off_map, off_ref_map, off_stage, total;
     int n_offs;                         // stride of the offset arrays (batch + 1)
-    size_t map_ints;                    // capacity of the tile map of the 128-tile grouped launches
+    size_t map_size, ref_map_size;      // capacity of the tile maps (split squaring, FP64 refinement)
 };
 
-// Tile map of the grouped 128-tile launches (squaring and FP64 refinement): every tile of
-// the problems `order` lists.  Each problem's tiles are cut into kMapParts contiguous runs
-// of the strip order, each run on one XCD (so that the tiles of a run share its L2);
-// problems go largest first, and each run to the XCD with the least work so far (a run's
-// work ~ its tiles x n_p).  Four runs per problem: the 64-problem batch (N = 256..3008)
+// Tile map of the grouped launches (split squaring, FP64 refinement): every tile of the
+// problems listed, tiles_of(problem) of them.  Each problem's tiles are cut into kMapParts
+// contiguous runs of the strip order, each run on one XCD (so that the tiles of a run share
+// its L2); problems go largest first, and each run to the XCD with the least work so far (a
+// run's work ~ its tiles x n_p).  Four runs per problem: the 64-problem batch (N = 256..3008)
 // takes 107.3 ms per call, against 111.7 ms with whole problems per XCD (the last layers,
 // with few problems left, then kept only some XCDs busy), 109.2 ms with 2 runs and
 // 109.0 ms with 8 (each XCD's L2 then holds panels of every problem).
 constexpr int kMapParts = 4;
-int build_tile_map(const std::vector<Plan>& plans, const std::vector<int>& problems, std::vector<int>* map) {
+int build_tile_map(const std::vector<Plan>& plans, const std::vector<int>& problems, int (*tiles_of)(const Plan&),
+                   std::vector<TileRef>* map) {
     std::vector<int> order(problems.size());
     for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
         return plans[problems[x]].np > plans[problems[y]].np;
     });
-    std::vector<int> bins[8];
+    std::vector<TileRef> bins[8];
     double load[8] = {};
     for (int k : order) {
         const Plan& p = plans[problems[k]];
-        const int nt = p.main_tiles;
+        const int nt = tiles_of(p);
         const int parts = nt < kMapParts ? nt : kMapParts;
         bool used[8] = {};
         for (int r = 0; r < parts; ++r) {
@@ -1064,20 +1033,21 @@ int build_tile_map(const std::vector<Plan>& plans, const std::vector<int>& probl
             for (int j = 0; j < 8; ++j)
                 if (!used[j] && (x < 0 || load[j] < load[x])) x = j;
             used[x] = true;
-            for (int t = t0; t < t1; ++t) bins[x].push_back((k << kTileMapShift) | t);
+            for (int t = t0; t < t1; ++t) bins[x].push_back(TileRef{k, t});
             load[x] += (double)(t1 - t0) * p.np;
         }
     }
     size_t per = 0;
     for (auto& b : bins) per = b.size() > per ? b.size() : per;
-    map->assign(8 * per, -1);
-    for (int x = 0; x < 8; ++x)
-        for (size_t j = 0; j < bins[x].size(); ++j) (*map)[x * per + j] = bins[x][j];
+    map->assign(8 * per, TileRef{-1, 0});
+    for (int x = 0; x < 8; ++x) std::copy(bins[x].begin(), bins[x].end(), map->begin() + x * per);
     return (int)per;
 }
+// 64-tiles of a problem's FP64 refinement
+int main_tiles_of(const Plan& p) { return p.main_tiles; }
+int ref_tiles64(const Plan& p) { return ntiles_upper((p.n + 63) / 64); }
 
-// problems of one batched call: the tile map encodes the problem in the bits above kTileMapShift
-constexpr int kMaxBatch = 1 << (31 - kTileMapShift);
+constexpr int kMaxBatch = 8192;   // problems of one batched call
 
 bool batch_layout(int batch, const int* n, const int* n_occ, const Opts& o, BatchLayout* L) {
     L->batch = batch;
@@ -1108,12 +1078,17 @@ bool batch_layout(int batch, const int* n, const int* n_occ, const Opts& o, Batc
     L->off_sq = off;
     off = align_up(off + sizeof(SquareArgs) * 4 * batch);   // even layer, odd layer, refine 1, refine 2
     L->off_offs = off;
-    off = align_up(off + sizeof(int) * 5 * L->n_offs);      // gersh, init, main, ref, dstats
-    L->map_ints = 0;
-    if (L->tile == 128)
-        for (int i = 0; i < batch; ++i) L->map_ints += 8 * (size_t)L->plans[i].main_tiles;
+    off = align_up(off + sizeof(int) * 4 * L->n_offs);      // gersh, init, main, dstats
+    L->map_size = L->ref_map_size = 0;
+    for (int i = 0; i < batch; ++i) {
+        L->map_size += 8 * (size_t)L->plans[i].main_tiles;
+        L->ref_map_size += 8 * (size_t)ref_tiles64(L->plans[i]);
+    }
+    if (!L->plans[0].split) L->map_size = 0;
     L->off_map = off;
-    off = align_up(off + sizeof(int) * L->map_ints);
+    off = align_up(off + sizeof(TileRef) * L->map_size);
+    L->off_ref_map = off;
+    off = align_up(off + sizeof(TileRef) * L->ref_map_size);
     L->off_stage = off;   // the device states of the problems, staged for one transfer
     off = align_up(off + sizeof(DevState) * batch);
     // then one single-problem region per problem; its DevState sits at the region's start
@@ -1234,13 +1209,12 @@ static int run_batched(int batch, const double* const* dH, const int* ldh, doubl
         // ---------------------------------------------------------------- descriptors
         std::vector<BatchProblem> probs(nt);
         std::vector<SquareArgs> sq(4 * nt);
-        std::vector<int> offs(5 * L.n_offs, 0);
+        std::vector<int> offs(4 * L.n_offs, 0);
         std::vector<DevState> states(nt);
         int* o_g = offs.data();
         int* o_i = o_g + L.n_offs;
         int* o_m = o_i + L.n_offs;
-        int* o_r = o_m + L.n_offs;
-        int* o_d = o_r + L.n_offs;
+        int* o_d = o_m + L.n_offs;
         BatchProblem* d_probs = (BatchProblem*)(ws + L.off_probs);
         for (int k = 0; k < nt; ++k) {
             const int i = L.nontrivial[k];
@@ -1275,7 +1249,6 @@ static int run_batched(int batch, const double* const* dH, const int* ldh, doubl
             o_g[k + 1] = o_g[k] + p.gersh_blocks;
             o_i[k + 1] = o_i[k] + p.init_tiles;
             o_m[k + 1] = o_m[k] + p.main_tiles;
-            o_r[k + 1] = o_r[k] + p.ref_tiles;
             o_d[k + 1] = o_d[k] + p.dstats_blocks;
             // squaring layers (even: S[0] -> S[1], odd: S[1] -> S[0]) and the two refinement layers
             for (int par = 0; par < 2; ++par) {
@@ -1289,6 +1262,7 @@ static int run_batched(int batch, const double* const* dH, const int* ldh, doubl
                 a.p0_out = q.pl[out][0];
                 a.p1_out = q.pl[out][1];
                 a.parts = q.main_parts;
+                a.ctl = p.split ? r : nullptr;
                 a.coef = ((DevState*)r)->coef;
                 a.skip = &((DevState*)r)->skip;
                 a.np = p.np;
@@ -1312,9 +1286,8 @@ static int run_batched(int batch, const double* const* dH, const int* ldh, doubl
                 a.n_real = n[i];
                 a.coef = ((DevState*)r)->rcoef[step];
                 a.np = p.np;
-                a.T = p.ref_T;
-                a.ntiles = p.ref_tiles;
-                a.per = p.ref_per;
+                a.T = (n[i] + 63) / 64;
+                a.ntiles = ref_tiles64(p);
             }
             states[k] = initial_state(n[i], n_occ[i], tol, o, p);
             if (homo) {
@@ -1327,14 +1300,16 @@ static int run_batched(int batch, const double* const* dH, const int* ldh, doubl
         SP2_TRY(hipStreamSynchronize(user));
         SP2_TRY(hipMemcpy(d_probs, probs.data(), sizeof(BatchProblem) * nt, hipMemcpyHostToDevice));
         SP2_TRY(hipMemcpy(ws + L.off_sq, sq.data(), sizeof(SquareArgs) * 4 * nt, hipMemcpyHostToDevice));
+        std::vector<TileRef> map, ref_map;
         int map_per = 0;
-        if (L.tile == 128) {
-            std::vector<int> map;
-            map_per = build_tile_map(L.plans, L.nontrivial, &map);
-            if (map.size() > L.map_ints) return SP2_EINVAL;
-            SP2_TRY(hipMemcpy(ws + L.off_map, map.data(), sizeof(int) * map.size(), hipMemcpyHostToDevice));
-        }
-        const int* d_map = (const int*)(ws + L.off_map);
+        if (L.map_size) map_per = build_tile_map(L.plans, L.nontrivial, main_tiles_of, &map);
+        const int ref_per = build_tile_map(L.plans, L.nontrivial, ref_tiles64, &ref_map);
+        if (map.size() > L.map_size || ref_map.size() > L.ref_map_size) return SP2_EINVAL;
+        if (!map.empty())
+            SP2_TRY(hipMemcpy(ws + L.off_map, map.data(), sizeof(TileRef) * map.size(), hipMemcpyHostToDevice));
+        SP2_TRY(hipMemcpy(ws + L.off_ref_map, ref_map.data(), sizeof(TileRef) * ref_map.size(), hipMemcpyHostToDevice));
+        const TileRef* d_map = (const TileRef*)(ws + L.off_map);
+        const TileRef* d_ref_map = (const TileRef*)(ws + L.off_ref_map);
         SP2_TRY(hipMemcpy(ws + L.off_offs, offs.data(), sizeof(int) * offs.size(), hipMemcpyHostToDevice));
         DevState* d_stage = (DevState*)(ws + L.off_stage);
         SP2_TRY(hipMemcpy(d_stage, states.data(), sizeof(DevState) * nt, hipMemcpyHostToDevice));
@@ -1343,8 +1318,7 @@ static int run_batched(int batch, const double* const* dH, const int* ldh, doubl
         const int* d_og = d_offs;
         const int* d_oi = d_og + L.n_offs;
         const int* d_om = d_oi + L.n_offs;
-        const int* d_or = d_om + L.n_offs;
-        const int* d_od = d_or + L.n_offs;
+        const int* d_od = d_om + L.n_offs;
 
         // ---------------------------------------------------------------- the sequence
         hipStream_t cs = batch_stream();
@@ -1357,14 +1331,14 @@ static int run_batched(int batch, const double* const* dH, const int* ldh, doubl
         const int la = o.max_layers < kBatchLayersA ? o.max_layers : kBatchLayersA;
         auto layers = [&](hipStream_t s, int l0, int l1) -> int {
             for (int layer = l0; layer <= l1; ++layer) {
-                SP2_TRY(launch_batch_control(d_probs, nt, layer, s));
+                // the split layers run the next layer's control themselves
+                if (layer == 1 || o.precision == SP2_FP32) SP2_TRY(launch_batch_control(d_probs, nt, layer, s));
                 if (layer > o.max_layers) break;
                 const SquareArgs* a = d_sq + ((layer - 1) & 1) * nt;
                 if (o.precision == SP2_FP32)
                     SP2_TRY(launch_square_plain_g(SP2_FP32, L.tile, a, d_om, nt, o_m[nt], s));
                 else
-                    SP2_TRY(L.tile == 128 ? launch_square_dp_g(o.precision, 128, 0, a, d_map, map_per, s)
-                                          : launch_square_split_g(o.precision, L.tile, a, d_om, nt, o_m[nt], s));
+                    SP2_TRY(launch_square_dp_g(o.precision, L.tile, 0, a, d_map, map_per, s));
             }
             return SP2_OK;
         };
@@ -1381,9 +1355,7 @@ static int run_batched(int batch, const double* const* dH, const int* ldh, doubl
             } else {
                 SP2_TRY(launch_batch_select(d_probs, nt, 64, s));
                 for (int step = 2; step <= 3; ++step)
-                    SP2_TRY(L.tile == 128
-                                ? launch_square_f64_g(d_sq + step * nt, d_map, map_per, s)
-                                : launch_square_plain_g(SP2_FP64, L.tile, d_sq + step * nt, d_or, nt, o_r[nt], s));
+                    SP2_TRY(launch_square_f64_g(d_sq + step * nt, d_ref_map, ref_per, s));
                 SP2_TRY(launch_batch_dstats(d_probs, d_od, nt, o_d[nt], s));
                 SP2_TRY(launch_batch_finalize(d_probs, nt, s));
                 SP2_TRY(launch_batch_states(d_probs, d_stage, nt, 0, s));
@@ -1398,10 +1370,10 @@ static int run_batched(int batch, const double* const* dH, const int* ldh, doubl
         auto run_part = [&](int which) -> int {
             if (!use_graph) return part(cs, which);
             const std::vector<long long> key = {which, dev, (long long)(uintptr_t)ws, (long long)L.total, L.batch,
-                                                nt, L.tile, o.precision, o.max_layers, la, map_per, o_g[nt],
-                                                o_i[nt], o_m[nt], o_r[nt], o_d[nt], (long long)L.off_probs,
+                                                nt, L.tile, o.precision, o.max_layers, la, map_per, ref_per, o_g[nt],
+                                                o_i[nt], o_m[nt], o_d[nt], (long long)L.off_probs,
                                                 (long long)L.off_sq, (long long)L.off_offs, (long long)L.off_map,
-                                                (long long)L.off_stage};
+                                                (long long)L.off_ref_map, (long long)L.off_stage};
             hipGraphExec_t exec = graph_cache_find(key);
             if (!exec) {
                 int prc = SP2_OK;

@@ -29,6 +29,9 @@ struct SquareArgs {
     int per;              // ceil(ntiles / 8)
     float out_scale;      // split modes: 2^-2s applied to the accumulated products
     float in_scale;       // split modes: 2^s applied before splitting Y
+    // control of the next layer by the launch's last finished tile (sp2_control.h)
+    void* ctl;            // DevState of the call, or null: no control in this launch
+    int* host_flag;       // mapped host flag set when Alg. 1 stops, or null
 };
 
 // Schedule of the persistent split-square kernel: G workgroups run `rounds` whole rounds
@@ -46,11 +49,12 @@ constexpr int kSkCounterInts = kMaxSkGrid + 64;
 constexpr int kSkGroupCounter = kMaxSkGrid / 2;
 constexpr int kSkGroupSlot = kMaxSkGrid / 2;
 
-// Tile maps of the grouped (many-problem) launches: entry (problem << kTileMapShift) |
-// tile, or -1 for no work.  Block b reads entry (b mod 8) * per + b / 8, so the blocks that
-// the hardware sends to one XCD (b mod 8 fixed) walk that XCD's part of the map.
-constexpr int kTileMapShift = 18;
-constexpr int kTileMapMask = (1 << kTileMapShift) - 1;
+// Tile maps of the grouped (many-problem) launches: block b computes tile `tile` of problem
+// `problem` in entry (b mod 8) * per + b / 8 (problem -1: no work), so the blocks that the
+// hardware sends to one XCD (b mod 8 fixed) walk that XCD's part of the map.
+struct TileRef {
+    int problem, tile;
+};
 
 // Row stride (elements) of the half-precision planes of an np x np matrix.  With a row
 // pitch of a power of two kilobytes, the rows of one K-slice of a panel fall on the same
@@ -67,7 +71,6 @@ struct StreamK {
     int grid = 0, rounds = 0, tail_tiles = 0, chunks = 0;
     float* partial = nullptr;     // FP32 partial tiles (split squaring, adjoint)
     int* counter = nullptr;       // arrivals per tail tile, counted modulo chunks
-    double* fpartial = nullptr;   // FP64 partial tiles (FP64 layer)
     int stream_k = 0;             // slices per stream-K unit; 0: whole rounds + split tail
     int pad = 0;
 };

@@ -60,7 +60,7 @@ struct DevState {
     int accel;          // 1 when the caller's interval rescaled into 0 <= l < h <= 1
     int acc_layers;     // index of the last accelerated layer (0: none)
     int gap_violation;  // first layer whose interval consistency check failed (0: none)
-    int pad2;
+    int tiles_done;     // squaring tiles finished in this call (tile_done in sp2_control.h)
     double homo, lumo;  // caller's interval inside the gap (energies)
     double acc_l, acc_h;  // unoccupied eigenvalues of S_{n-1} in [0, acc_l], occupied in [acc_h, 1]
     double sigma_c[SP2_MAX_LAYERS + 1];
@@ -185,16 +185,14 @@ hipError_t launch_batch_states(const BatchProblem* pr, DevState* stage, int npro
 // Host-side launchers (defined next to their kernels).
 hipError_t launch_square_split(int precision, int tile, const SquareArgs& a, hipStream_t s);
 hipError_t launch_square_plain(int precision, int tile, const SquareArgs& a, hipStream_t s);
-// FP64 layer with direct-to-LDS staging, 128 tiles (k_square_f64.hip); variant 0 or 1
+// FP64 layer with direct-to-LDS staging, 128 tiles (k_square_f64.hip); variants 0..2
 hipError_t launch_square_f64(int variant, const SquareArgs& a, hipStream_t s);
-// grouped FP64 layer over a tile map (see kTileMapShift), grid 8 per
-hipError_t launch_square_f64_g(const SquareArgs* descs, const int* map, int per, hipStream_t s);
-// persistent FP64 layer (whole rounds + split-K tail), 128 tiles
-bool square_f64_sk_plan(int np, int cus, StreamK* sk);
-size_t square_f64_sk_partial_bytes();
-hipError_t launch_square_f64_sk(const SquareArgs& a, const StreamK& sk, hipStream_t s);
-hipError_t launch_square_split_g(int precision, int tile, const SquareArgs* descs, const int* offs, int nprob,
-                                 int blocks, hipStream_t s);
+// FP64 layer on 64-tiles with the leftover ones cut into 32-tiles: a.T, a.ntiles from
+// square_f64_mix_grid over the rows to compute
+void square_f64_mix_grid(int edge, int* T, int* nmain, int* ntiles);
+hipError_t launch_square_f64_mix(const SquareArgs& a, hipStream_t s);
+// grouped FP64 layer over a map of 64-tiles (see TileRef), grid 8 per
+hipError_t launch_square_f64_g(const SquareArgs* descs, const TileRef* map, int per, hipStream_t s);
 hipError_t launch_square_plain_g(int precision, int tile, const SquareArgs* descs, const int* offs, int nprob,
                                  int blocks, hipStream_t s);
 int square_split_grid(int tile, int np, int* T, int* ntiles, int* per);
@@ -206,7 +204,7 @@ hipError_t launch_square_sk(int precision, int tile, int variant, const SquareAr
                             hipStream_t s);
 // the same pipeline with one workgroup per tile (tiles 128, 256): one problem, or grouped
 hipError_t launch_square_dp(int precision, int tile, int variant, const SquareArgs& a, hipStream_t s);
-hipError_t launch_square_dp_g(int precision, int tile, int variant, const SquareArgs* descs, const int* map, int per,
+hipError_t launch_square_dp_g(int precision, int tile, int variant, const SquareArgs* descs, const TileRef* map, int per,
                               hipStream_t s);
 hipError_t launch_zero_ints(int* p, int count, hipStream_t s);
 

@@ -1,0 +1,63 @@
+"""Squaring kernels at the edges of their tiles: the direct-to-LDS 64-tile split kernel, the
+FP64 kernel on mixed 64 / 32 tiles, and the control of the next layer run by a squaring
+launch's last tile, each against the kernel that computes the same chain of products (bit for
+bit) or exact FP64 arithmetic."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2101_06385_amd import sp2, workloads as wl
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _sym(n, seed, dtype):
+    x = np.random.default_rng(seed).standard_normal((n, n)) / np.sqrt(n)
+    return torch.from_numpy(0.5 * (x + x.T)).to(DEV, dtype)
+
+
+@pytest.mark.parametrize("prec", ["fp16x2", "bf16x2"])
+@pytest.mark.parametrize("n", [1, 31, 64, 65, 127, 200, 833])
+def test_split_64_tile_pipeline_equals_register_staged_kernel(prec, n):
+    x = _sym(n, 500 + n, torch.float32)
+    for coef in ((1.0, 0.0, 0.0), (-1.0, 2.0, 0.25)):
+        y, s = sp2.square(x, *coef, precision=prec, tile=64, kernel=1)
+        y8, s8 = sp2.square(x, *coef, precision=prec, tile=64, kernel=8)
+        assert torch.equal(y, y8) and s == s8
+
+
+# 1472: 276 64-tiles = 256 whole + 20 cut; 1408: 253, all cut
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 33, 63, 65, 129, 700, 1400, 1472])
+def test_fp64_mixed_tiles_equal_128_tiles_and_exact_square(n):
+    x = _sym(n, 600 + n, torch.float64)
+    alpha, beta, gamma = -1.0, 2.0, 0.5
+    y, s = sp2.square(x, alpha, beta, gamma, precision="fp64", tile=128, kernel=0)
+    y4, _ = sp2.square(x, alpha, beta, gamma, precision="fp64", tile=128, kernel=4)
+    assert torch.equal(y, y4) and torch.equal(y, y.T)
+    xc = x.cpu().numpy()
+    ref = alpha * (xc @ xc) + beta * xc + gamma * np.eye(n)
+    # each side: n products and sums, then three more operations
+    bound = 2 * (n + 3) * 2.0**-53 * (np.abs(xc) @ np.abs(xc) + 2 * np.abs(xc) + np.abs(gamma) * np.eye(n))
+    assert np.all(np.abs(y.cpu().numpy() - ref) <= bound + 1e-300)
+    got = y.cpu().numpy()
+    terms = n * n + 1   # additions of the sum of squares in any order
+    assert abs(s[0] - np.trace(got)) <= 2 * n * 2.0**-53 * np.abs(np.diag(got)).sum()
+    assert abs(s[1] - (got**2).sum()) <= 2 * terms * 2.0**-53 * (got**2).sum()
+
+
+@pytest.mark.parametrize("prec", ["fp16x2", "bf16x2"])
+@pytest.mark.parametrize("n,gap", [(10, None), (64, None), (300, None), (777, (-0.9, 0.9))])
+def test_control_in_the_squaring_launch_equals_separate_control(prec, n, gap):
+    """tile 64: kernel 1 runs each next layer's control in its last tile, kernel 8 has the
+    control launches; the histories and D are the same bits."""
+    w = wl.gapped(700 + n, n, n // 2)
+    h = torch.from_numpy(w.h).to(DEV)
+    d, i = sp2.density(h, w.n_occ, precision=prec, tile=64, kernel=1, gap=gap)
+    d8, i8 = sp2.density(h, w.n_occ, precision=prec, tile=64, kernel=8, gap=gap)
+    assert torch.equal(d, d8)
+    for k in ("status", "layers", "sigma", "iderr", "ns", "nx", "sigma_c", "accelerated", "trace"):
+        assert i[k] == i8[k], k
+    d2, i2 = sp2.density(h, w.n_occ, precision=prec, tile=64, kernel=1, gap=gap, max_layers=7)
+    d28, i28 = sp2.density(h, w.n_occ, precision=prec, tile=64, kernel=8, gap=gap, max_layers=7)
+    assert torch.equal(d2, d28) and i2["layers"] == i28["layers"] == 7 and i2["status"] == i28["status"]
