@@ -1,0 +1,6 @@
+// Fragment-major split squaring kernels, BF16 planes.
+#include "k_square_fm.h"
+
+namespace sp2 {
+template hipError_t launch_fm_t<__bf16>(int variant, const FmArgs& a, hipStream_t s);
+}  // namespace sp2

@@ -64,6 +64,7 @@ __global__ void k_state_init(DevState* st, StateParams p) {
         st->nx[i] = 0.0;
         st->sigma_c[i] = 0.0;
     }
+    for (int i = t; i < kDoneInts; i += blockDim.x) done_counters(st)[i] = 0;
     if (t == 0) {
         st->n = p.n;
         st->n_occ = p.n_occ;
@@ -100,7 +101,10 @@ __global__ void k_state_init(DevState* st, StateParams p) {
         st->accel = p.accel;
         st->acc_layers = 0;
         st->gap_violation = 0;
-        st->tiles_done = 0;
+        st->sig1 = st->sig2 = 0;
+        st->ide1 = st->ide2 = 0.0;
+        st->pad0 = 0;
+        st->pad2 = 0.0;
         st->homo = p.homo;
         st->lumo = p.lumo;
         st->acc_l = 0.0;
@@ -190,7 +194,9 @@ __device__ __forceinline__ void bounds_body(DevState* st, const double* __restri
 // ---------------------------------------------------------------------------------
 constexpr int kInitTile = 64;
 
-template <typename St, typename T16, bool kSplit>
+// kFm: the split planes in the fragment-major layout and S as 32 x 32 blocks of the upper
+// triangle in accumulator order (k_square_fm.h).
+template <typename St, typename T16, bool kSplit, bool kFm = false>
 __device__ __forceinline__ void init_body(const double* __restrict__ h, int ldh,
                                                    const DevState* __restrict__ st, St* __restrict__ s_out,
                                                    T16* __restrict__ p0, T16* __restrict__ p1, float in_scale,
@@ -228,8 +234,8 @@ __device__ __forceinline__ void init_body(const double* __restrict__ h, int ldh,
         double v = 0.0;
         if (gi < n && gj < n) v = w0 * hs + (gi == gj ? b0 : 0.0);
         const St vs = (St)v;
-        s_out[(size_t)gi * np + gj] = vs;
-        if (kSplit) {
+        if (!kFm) s_out[(size_t)gi * np + gj] = vs;
+        if (kSplit && !kFm) {
             const float xs = (float)vs * in_scale;
             const T16 h0 = (T16)xs;
             const T16 h1 = (T16)(xs - (float)h0);
@@ -242,8 +248,37 @@ __device__ __forceinline__ void init_body(const double* __restrict__ h, int ldh,
         a[r][c] = vd;
     }
     __syncthreads();
+    if constexpr (kFm) {
+        typedef T16 vec8 __attribute__((ext_vector_type(8)));
+        typedef float f32x4 __attribute__((ext_vector_type(4)));
+        const size_t ps = (size_t)fm_pstride(np) * 512;
+        for (int side = 0; side < (diag ? 1 : 2); ++side) {   // the tile, then its mirror
+            const int br = side ? c0 : r0, bc = side ? r0 : c0;
+            for (int item = t; item < kInitTile * kInitTile / 8; item += kThreads) {
+                const int r = item % kInitTile, ch = item / kInitTile;   // row, chunk of 8 columns
+                vec8 h0, h1;
+                for (int e = 0; e < 8; ++e) {
+                    const float xs = (float)(side ? a[8 * ch + e][r] : a[r][8 * ch + e]) * in_scale;
+                    const T16 hh = (T16)xs;
+                    h0[e] = hh;
+                    h1[e] = (T16)(xs - (float)hh);
+                }
+                const size_t o = (size_t)((br + r) / 32) * ps + (size_t)((bc + 8 * ch) / 16) * 512 +
+                                 ((r & 31) + 32 * (ch & 1)) * 8;
+                *(vec8*)(p0 + o) = h0;
+                *(vec8*)(p1 + o) = h1;
+            }
+        }
+        for (int item = t; item < 4 * 256; item += kThreads) {   // S: 4 blocks of 256 x 4 values
+            const int bi = item >> 9, bj = (item >> 8) & 1, g = (item >> 6) & 3, lane = item & 63;
+            if (diag && bi > bj) continue;
+            f32x4 v;
+            for (int e = 0; e < 4; ++e) v[e] = (float)a[32 * bi + 8 * g + 4 * (lane >> 5) + e][32 * bj + (lane & 31)];
+            *(f32x4*)((float*)s_out + ((size_t)(r0 / 32 + bi) * (np / 32) + c0 / 32 + bj) * 1024 + 256 * g + 4 * lane) = v;
+        }
+    }
     // pass 2: the mirror tile (J, I), row-major over its rows (coalesced)
-    if (!diag) {
+    if (!diag && !kFm) {
         for (int idx = t; idx < kInitTile * kInitTile; idx += kThreads) {
             const int r = idx / kInitTile, c = idx % kInitTile;   // mirror element (c0 + r, r0 + c)
             const St vs = (St)a[c][r];
@@ -489,7 +524,7 @@ __global__ __launch_bounds__(kThreads) void k_bounds(DevState* st, const double*
 __global__ __launch_bounds__(kThreads) void k_control(DevState* st, const double* __restrict__ parts, int nparts,
                                                       int stride, int layer, volatile int* __restrict__ host_flag) {
     __shared__ double sh[kControlLds];
-    control_body(st, parts, nparts, stride, layer, host_flag, sh);
+    control_body<kThreads>(st, parts, nparts, stride, layer, host_flag, sh);
 }
 __global__ __launch_bounds__(kThreads) void k_finalize(DevState* st, const double* __restrict__ dparts, int nd,
                                                        const double* __restrict__ iparts, int ni) {
@@ -501,6 +536,50 @@ __global__ __launch_bounds__(kThreads) void k_init(const double* __restrict__ h,
                                                    T16* __restrict__ p0, T16* __restrict__ p1, float in_scale,
                                                    double* __restrict__ parts) {
     init_body<St, T16, kSplit>(h, ldh, st, s_out, p0, p1, in_scale, parts, blockIdx.x);
+}
+// fragment-major input layer; also clears the partial-sum buffers of the layers
+template <typename T16>
+__global__ __launch_bounds__(kThreads) void k_init_fm(const double* __restrict__ h, int ldh,
+                                                      const DevState* __restrict__ st, float* __restrict__ s_out,
+                                                      T16* __restrict__ p0, T16* __restrict__ p1, float in_scale,
+                                                      double* __restrict__ parts, double* __restrict__ zero, int nzero) {
+    for (int i = blockIdx.x * kThreads + threadIdx.x; i < nzero; i += gridDim.x * kThreads) zero[i] = 0.0;
+    init_body<float, T16, true, true>(h, ldh, st, s_out, p0, p1, in_scale, parts, blockIdx.x);
+}
+// S_{m-1} from its 32 x 32 upper blocks (accumulator order) to FP64 rows, one block and its
+// mirror per workgroup; rows and columns from 32 ceil(n / 32) on are zero, those from n_valid
+// on are not written.
+__global__ __launch_bounds__(kThreads) void k_select_fm(const DevState* __restrict__ st, const float* __restrict__ s0,
+                                                        const float* __restrict__ s1, double* __restrict__ out,
+                                                        int ld_out, int n, int n_valid, int sb) {
+    __shared__ float b[32][33];
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    const int bi = blockIdx.y, bj = blockIdx.x, t = threadIdx.x;
+    if (bi > bj) return;
+    const float* src = (st->refine_src ? s1 : s0) + ((size_t)bi * sb + bj) * 1024;
+    const int g = t >> 6, lane = t & 63, r0 = 8 * g + 4 * (lane >> 5), c = lane & 31;
+    const f32x4 v = 32 * bj < n ? ((const f32x4*)src)[t] : f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int e = 0; e < 4; ++e) {
+        if (bi == bj && r0 + e > c) continue;
+        b[r0 + e][c] = v[e];
+        if (bi == bj) b[c][r0 + e] = v[e];
+    }
+    __syncthreads();
+    for (int i = t; i < 1024; i += kThreads) {
+        const int r = i >> 5, q = i & 31;
+        const int gr = 32 * bi + r, gc = 32 * bj + q;
+        if (gr < n_valid && gc < n_valid) out[(size_t)gr * ld_out + gc] = (double)b[r][q];
+        const int mr = 32 * bj + r, mc = 32 * bi + q;
+        if (bi != bj && mr < n_valid && mc < n_valid) out[(size_t)mr * ld_out + mc] = (double)b[q][r];
+    }
+}
+// the control after the last layer launched: leaves the state in its first hot block
+__global__ __launch_bounds__(64) void k_lead_finish(LeadArgs a) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char lead[];
+    lead_load(a, (unsigned)(uintptr_t)(const __attribute__((address_space(3))) unsigned char*)lead);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    Coefs cf;
+    (void)lead_finish(a, lead, true, &cf);
 }
 template <typename Src>
 __global__ __launch_bounds__(kThreads) void k_select_f64(const DevState* __restrict__ st, const Src* __restrict__ s0,
@@ -539,8 +618,8 @@ __global__ __launch_bounds__(kThreads) void k_init_g(const BatchProblem* __restr
 __global__ __launch_bounds__(kThreads) void k_control_g(const BatchProblem* __restrict__ pr, int layer) {
     __shared__ double sh[kControlLds];
     const BatchProblem& q = pr[blockIdx.x];
-    if (layer == 1) control_body(q.st, q.init_parts, q.init_tiles, 3, layer, nullptr, sh);
-    else control_body(q.st, q.main_parts, q.main_tiles, 2, layer, nullptr, sh);
+    if (layer == 1) control_body<kThreads>(q.st, q.init_parts, q.init_tiles, 3, layer, nullptr, sh);
+    else control_body<kThreads>(q.st, q.main_parts, q.main_tiles, 2, layer, nullptr, sh);
 }
 __global__ __launch_bounds__(kThreads) void k_select_g(const BatchProblem* __restrict__ pr, int per_problem) {
     const int p = blockIdx.x / per_problem;
@@ -571,6 +650,8 @@ __global__ __launch_bounds__(64) void k_state_copy_g(const BatchProblem* __restr
         if (to_regions) r[i] = g[i];
         else g[i] = r[i];
     }
+    if (to_regions)
+        for (int i = threadIdx.x; i < kDoneInts; i += 64) done_counters(pr[blockIdx.x].st)[i] = 0;
 }
 
 inline int grid_for(size_t total) {
@@ -647,6 +728,34 @@ hipError_t launch_init_np(const double* h, int ldh, DevState* st, int np, int pr
         default:
             return hipErrorInvalidValue;
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_init_fm(const double* h, int ldh, DevState* st, int np, int precision, float* s_out, void* p0,
+                          void* p1, int scale_log2, double* parts, double* zero, int nzero, hipStream_t s) {
+    const int nt = init_tiles(np);
+    const float in_scale = ldexpf(1.f, scale_log2);
+    if (precision == SP2_FP16X2)
+        hipLaunchKernelGGL((k_init_fm<_Float16>), dim3(nt), dim3(kThreads), 0, s, h, ldh, st, s_out, (_Float16*)p0,
+                           (_Float16*)p1, in_scale, parts, zero, nzero);
+    else if (precision == SP2_BF16X2)
+        hipLaunchKernelGGL((k_init_fm<__bf16>), dim3(nt), dim3(kThreads), 0, s, h, ldh, st, s_out, (__bf16*)p0,
+                           (__bf16*)p1, in_scale, parts, zero, nzero);
+    else
+        return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t launch_select_fm(const DevState* st, const float* s0, const float* s1, double* out, int ld_out, int n,
+                            int n_valid, int np, hipStream_t s) {
+    const int blocks = (n_valid + 31) / 32;
+    hipLaunchKernelGGL(k_select_fm, dim3(blocks, blocks), dim3(kThreads), 0, s, st, s0, s1, out, ld_out, n, n_valid,
+                       np / 32);
+    return hipGetLastError();
+}
+
+hipError_t launch_lead_finish(const LeadArgs& a, hipStream_t s) {
+    hipLaunchKernelGGL(k_lead_finish, dim3(1), dim3(64), lead_bytes(a), s, a);
     return hipGetLastError();
 }
 

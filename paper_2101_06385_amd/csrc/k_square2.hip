@@ -115,3 +115,15 @@ hipError_t launch_square_dp_g(int precision, int tile, int variant, const Square
     return hipErrorInvalidValue;
 }
 }  // namespace sp2
+
+namespace sp2 {
+template <typename T16>
+hipError_t launch_fm_t(int variant, const FmArgs& a, hipStream_t s);
+extern template hipError_t launch_fm_t<_Float16>(int, const FmArgs&, hipStream_t);
+extern template hipError_t launch_fm_t<__bf16>(int, const FmArgs&, hipStream_t);
+hipError_t launch_fm(int precision, int variant, const FmArgs& a, hipStream_t s) {
+    if (precision == SP2_FP16X2) return launch_fm_t<_Float16>(variant, a, s);
+    if (precision == SP2_BF16X2) return launch_fm_t<__bf16>(variant, a, s);
+    return hipErrorInvalidValue;
+}
+}  // namespace sp2

@@ -245,7 +245,7 @@ __device__ __forceinline__ void f64_body(const SquareArgs& a, int I, int J, int 
             st_agent(a.parts + 2 * t, s0);
             st_agent(a.parts + 2 * t + 1, s1);
         }
-        tile_done(a, (double*)lds, s_done);
+        tile_done<C::NT>(a, t, (double*)lds, s_done);
     }
 }
 
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(256) void k_square_f64_mix(SquareArgs a, int nmain)
             st_agent(a.parts + 2 * slot, 0.0);
             st_agent(a.parts + 2 * slot + 1, 0.0);
         }
-        tile_done(a, (double*)lds, &s_done);
+        tile_done<256>(a, slot, (double*)lds, &s_done);
         return;
     }
     f64_body<32, 2, 2, 2>(a, i, j, slot, lds, red, &s_done);

@@ -761,7 +761,7 @@ __device__ __forceinline__ void sk_body(const SquareArgs& a, const StreamK& sk, 
                     st_agent(a.parts + 2 * t, s0);
                     st_agent(a.parts + 2 * t + 1, s1);
                 }
-                tile_done(a, scr + 2 * C::NW, &s_flag);
+                tile_done<C::NT>(a, t, scr + 2 * C::NW, &s_flag);
             }
         }
         __syncthreads();   // LDS is reused by the next item's prologue

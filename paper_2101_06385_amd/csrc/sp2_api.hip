@@ -25,6 +25,7 @@ struct Opts {
     int precision, max_layers, have_bounds, refine, scale_log2, want_energy, tile, kernel;
     int tile_ref;   // FP64 refinement tile, 0 = by size (set only by the batched path)
     int accelerate;
+    bool fm_ok = false;   // a single density call (the fragment-major path serves only these)
     double eps, emin, emax, homo, lumo;
 };
 
@@ -70,6 +71,8 @@ struct Plan {
     bool sk_capable;  // stream-K buffers are part of the workspace
     size_t off_init_parts, off_main_parts, off_gersh, off_dstats, off_s[2], off_p[2][2], off_s64, off_y;
     size_t off_sk_partial, off_sk_counter, total;
+    bool fm;          // split layers by the fragment-major kernel (k_square_fm.h), variant fm_variant
+    int fm_variant;
 };
 
 // The persistent (whole rounds + split tail) schedule needs a tile of 128 or 256 in a
@@ -150,6 +153,20 @@ int auto_tile_main(int n, bool split) {
     return n <= 512 ? 64 : 128;
 }
 
+// Fragment-major split layers (k_square_fm.h) of a single problem: 64- and 128-tiles, one
+// workgroup per tile asked for or chosen, below the sizes that fill the chip with 128-tiles
+// (one layer with its control, this path against k_square_dp with its control in its last tile
+// or, before that, in a launch: n = 400 8.8 against 16.1 us, 1000 13.4 against 24.8, 2000 38 against 66,
+// 2500 64 against 72, 2900 113 against 130 us; n >= 3072 runs the persistent schedule).
+bool fm_wanted(bool split, int tile, int kernel, int np) {
+    return split && (kernel == 0 || kernel == 1) && (tile == 64 || tile == 128) && np < 3072;
+}
+// Variant: + 1 for the product order of the 128-tile kernels; 4-wave workgroups while a CU's
+// LDS holds all its 64-tiles (two per CU, 512 in all: n = 1000 13.4 us per layer against 22.3
+// us with one wave per tile, 1700 27.9 against 31.6), one wave per tile above (n = 2000 38.4
+// against 43.7 us, 2500 63.6 against 72.2 us).
+int fm_variant(int tile, int ntiles64) { return (tile == 128 ? 1 : 0) + (ntiles64 > 512 ? 2 : 0); }
+
 void make_plan(int n, const Opts& o, Plan* p) {
     p->n = n;
     p->precision = o.precision;
@@ -180,11 +197,15 @@ void make_plan(int n, const Opts& o, Plan* p) {
     p->dstats_blocks = dstats_blocks(n);
     const size_t np2 = (size_t)p->np * p->np;
     const size_t es = o.precision == SP2_FP64 ? 8 : 4;
-    size_t off = align_up(sizeof(DevState));
+    size_t off = align_up(kStateArea);
     p->off_init_parts = off;
     off = align_up(off + sizeof(double) * 3 * p->init_tiles);
     p->off_main_parts = off;
-    off = align_up(off + sizeof(double) * 2 * p->main_tiles);
+    p->sk_capable = sk_wanted(p->split, p->tile_main, kernel, p->np);
+    p->fm = o.fm_ok && fm_wanted(p->split, p->tile_main, kernel, p->np) && !p->sk_capable;
+    if (p->fm) square_split_grid(64, p->np, &p->main_T, &p->main_tiles, &p->main_per);
+    p->fm_variant = p->fm ? fm_variant(p->tile_main, p->main_tiles) : 0;
+    off = align_up(off + sizeof(double) * (p->fm ? 4 * p->main_tiles : 2 * p->main_tiles));   // fm: two buffers
     p->off_gersh = off;
     off = align_up(off + sizeof(double) * 3 * p->gersh_blocks);
     p->off_dstats = off;
@@ -203,7 +224,6 @@ void make_plan(int n, const Opts& o, Plan* p) {
     p->off_y = off;
     off = align_up(off + (o.refine ? 8 * np2 : 0));
     p->kernel = kernel;
-    p->sk_capable = sk_wanted(p->split, p->tile_main, kernel, p->np);
     p->off_sk_partial = off;
     if (p->sk_capable) off = align_up(off + square_sk_partial_bytes(p->tile_main, p->np));
     p->off_sk_counter = off;
@@ -412,6 +432,7 @@ size_t sp2_workspace_size(int n, const sp2_options* opt) {
     if (n <= 0) return 0;
     Opts o;
     if (!read_opts(opt, &o)) return 0;
+    o.fm_ok = true;
     Plan p;
     make_plan(n, o, &p);
     return p.total;
@@ -467,6 +488,7 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
     if (n <= 0 || ldh < n || ldd < n || n_occ < 0 || n_occ > n || !dH || !dD || !dWork) return SP2_EINVAL;
     if (((uintptr_t)dWork) % kAlign) return SP2_EINVAL;
     if (n > 65536) return SP2_EINVAL;
+    o.fm_ok = true;
     Plan p;
     make_plan(n, o, &p);
     if (work_bytes < p.total) return SP2_ENOMEM;
@@ -500,7 +522,11 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
         void* S[2] = {ws + p.off_s[0], ws + p.off_s[1]};
         void* P[2][2] = {{p.split ? ws + p.off_p[0][0] : nullptr, p.split ? ws + p.off_p[0][1] : nullptr},
                          {p.split ? ws + p.off_p[1][0] : nullptr, p.split ? ws + p.off_p[1][1] : nullptr}};
-        SP2_TRY(launch_init_np(dH, ldh, st, p.np, o.precision, S[0], P[0][0], P[0][1], p.scale_log2, init_parts, s));
+        if (p.fm)
+            SP2_TRY(launch_init_fm(dH, ldh, st, p.np, o.precision, (float*)S[0], P[0][0], P[0][1], p.scale_log2,
+                                   init_parts, main_parts, 4 * p.main_tiles, s));
+        else
+            SP2_TRY(launch_init_np(dH, ldh, st, p.np, o.precision, S[0], P[0][0], P[0][1], p.scale_log2, init_parts, s));
         SP2_TRY(ev.rec(ev.prep, s));
 
         StreamK sk;
@@ -540,7 +566,37 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
         const bool fused = (p.split && p.kernel != kKernelLegacyTile) || (o.precision == SP2_FP64 && o.kernel != 1);
         if (fused) {
             a.ctl = st;
+            a.arrivals = p.main_tiles;
             a.host_flag = flag.dev;
+        }
+        // fragment-major layers: layer k reads the sums that layer k - 1 left in buffer k mod 2 and
+        // the hot block (k - 1) mod 2
+        auto lead_of = [&](int layer) {
+            LeadArgs l;
+            memset(&l, 0, sizeof(l));
+            l.st = st;
+            l.hot_in = hot_block(st, layer - 1);
+            l.hot_out = hot_block(st, layer);
+            l.parts = layer == 1 ? init_parts : main_parts + (size_t)(layer & 1) * 2 * p.main_tiles;
+            l.nparts = layer == 1 ? p.init_tiles : p.main_tiles;
+            l.stride = layer == 1 ? 3 : 2;
+            l.host_flag = flag.dev;
+            l.layer = layer;
+            return l;
+        };
+        FmArgs fm;
+        memset(&fm, 0, sizeof(fm));
+        int fm_done = 0;   // fragment-major layers launched
+        if (p.fm) {
+            fm.pstride = fm_pstride(p.np);
+            fm.sb = p.np / 32;
+            fm.ku = (n + 15) / 16;
+            fm.n_real = n;
+            fm.T = p.main_T;
+            fm.ntiles = p.main_tiles;
+            fm.per = (p.main_tiles + 7) / 8;
+            fm.out_scale = a.out_scale;
+            fm.in_scale = a.in_scale;
         }
         int waited = 0;   // chunks whose completion the host has observed
         for (int layer = 1; layer <= o.max_layers + 1; ++layer) {
@@ -552,6 +608,24 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
                     waited = c - 1;
                     if (*flag.host) break;
                 }
+            }
+            if (p.fm) {
+                if (layer > o.max_layers) break;
+                fm.lead = lead_of(layer);
+                fm_done = layer;
+                const int in = (layer - 1) & 1, out = layer & 1;
+                fm.x0 = P[in][0];
+                fm.x1 = P[in][1];
+                fm.p0_out = P[out][0];
+                fm.p1_out = P[out][1];
+                fm.s_in = (const float*)S[in];
+                fm.s_out = (float*)S[out];
+                fm.parts_out = main_parts + (size_t)((layer + 1) & 1) * 2 * p.main_tiles;
+                ev.launched = layer;
+                SP2_TRY(ev.rec(ev.sq_b[layer], s));
+                SP2_TRY(launch_fm(o.precision, p.fm_variant, fm, s));
+                SP2_TRY(ev.rec(ev.sq_e[layer], s));
+                continue;
             }
             if (layer == 1)
                 SP2_TRY(launch_control_stride(st, init_parts, p.init_tiles, 3, layer, flag.dev, s));
@@ -578,11 +652,19 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
             SP2_TRY(ev.rec(ev.sq_e[layer], s));
         }
         (void)waited;
+        if (p.fm) {
+            LeadArgs lead = lead_of(fm_done + 1);
+            lead.hot_out = hot_block(st, 0);
+            SP2_TRY(launch_lead_finish(lead, s));
+        }
         SP2_TRY(ev.rec(ev.loop_end, s));
         if (o.refine) {
             double* s64 = (double*)(ws + p.off_s64);
             double* y = (double*)(ws + p.off_y);
-            SP2_TRY(launch_select_f64(st, S[0], S[1], o.precision == SP2_FP64, s64, p.np, p.np, p.np, s));
+            if (p.fm)
+                SP2_TRY(launch_select_fm(st, (const float*)S[0], (const float*)S[1], s64, p.np, n, round_up(n, 64), p.np, s));
+            else
+                SP2_TRY(launch_select_f64(st, S[0], S[1], o.precision == SP2_FP64, s64, p.np, p.np, p.np, s));
             SP2_TRY(ev.rec(ev.ref[0], s));
             SquareArgs r;
             memset(&r, 0, sizeof(r));
@@ -608,7 +690,10 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
             SP2_TRY(launch_f64_layer(p.tile_ref, o.precision == SP2_FP64 ? o.kernel : 0, r, s));
             SP2_TRY(ev.rec(ev.ref[2], s));
         } else {
-            SP2_TRY(launch_select_f64(st, S[0], S[1], o.precision == SP2_FP64, dD, ldd, n, p.np, s));
+            if (p.fm)
+                SP2_TRY(launch_select_fm(st, (const float*)S[0], (const float*)S[1], dD, ldd, n, n, p.np, s));
+            else
+                SP2_TRY(launch_select_f64(st, S[0], S[1], o.precision == SP2_FP64, dD, ldd, n, p.np, s));
             SP2_TRY(ev.rec(ev.ref[0], s));
             SP2_TRY(ev.rec(ev.ref[1], s));
             SP2_TRY(ev.rec(ev.ref[2], s));
@@ -677,6 +762,7 @@ int sp2_density_static(const double* dH, int ldh, double* dD, int ldd, int n, in
     Opts o;
     if (!read_opts(opt, &o) || n <= 0 || n > 65536) return SP2_EINVAL;
     if (ldh < n || ldd < n || n_occ < 0 || n_occ > n || !dH || !dD) return SP2_EINVAL;
+    o.fm_ok = true;
     Plan p;
     make_plan(n, o, &p);
     if (p.total > (size_t)SP2_STATIC_SCRATCH_BYTES) return SP2_ENOMEM;
@@ -699,6 +785,7 @@ int sp2_density_timed(const double* dH, int ldh, double* dD, int ldd, int n, int
 int sp2_query(const void* dWork, int n, const sp2_options* opt, sp2_info* info, void* stream) {
     Opts o;
     if (!dWork || !info || n <= 0 || !read_opts(opt, &o)) return SP2_EINVAL;
+    o.fm_ok = true;
     Plan p;
     make_plan(n, o, &p);
     DevState host;
@@ -827,7 +914,7 @@ int sp2_fermi_apply(const double* dH, int ldh, double* dD, int ldd, int n, int l
 
 size_t sp2_spectral_bounds_workspace_size(int n) {
     if (n <= 0 || n > 65536) return 0;
-    return align_up(sizeof(DevState)) + align_up(sizeof(double) * 3 * gershgorin_blocks(n));
+    return align_up(kStateArea) + align_up(sizeof(double) * 3 * gershgorin_blocks(n));
 }
 
 int sp2_spectral_bounds(const double* dH, int ldh, int n, double* emin, double* emax, void* dWork,
@@ -838,7 +925,7 @@ int sp2_spectral_bounds(const double* dH, int ldh, int n, double* emin, double* 
     hipStream_t s = (hipStream_t)stream;
     char* ws = (char*)dWork;
     DevState* st = (DevState*)ws;
-    double* gersh = (double*)(ws + align_up(sizeof(DevState)));
+    double* gersh = (double*)(ws + align_up(kStateArea));
     DevState init;
     memset(&init, 0, sizeof(init));
     init.n = n;
@@ -1263,7 +1350,8 @@ static int run_batched(int batch, const double* const* dH, const int* ldh, doubl
                 a.p1_out = q.pl[out][1];
                 a.parts = q.main_parts;
                 a.ctl = p.split ? r : nullptr;
-                a.coef = ((DevState*)r)->coef;
+                a.arrivals = p.main_tiles;
+                    a.coef = ((DevState*)r)->coef;
                 a.skip = &((DevState*)r)->skip;
                 a.np = p.np;
                 a.ld_out = p.np;

@@ -30,9 +30,42 @@ struct SquareArgs {
     float out_scale;      // split modes: 2^-2s applied to the accumulated products
     float in_scale;       // split modes: 2^s applied before splitting Y
     // control of the next layer by the launch's last finished tile (sp2_control.h)
+    int arrivals;         // workgroups that count themselves done (tile_done)
     void* ctl;            // DevState of the call, or null: no control in this launch
     int* host_flag;       // mapped host flag set when Alg. 1 stops, or null
 };
+
+// Leading control of a layer: its sigma_n from the partial sums of the launch before.
+struct LeadArgs {
+    void* st;               // DevState (histories; its hot block is hot[0])
+    const void* hot_in;     // hot block that the layer before left
+    void* hot_out;          // where this layer's goes (another block)
+    const double* parts;    // nparts pairs, `stride` doubles apart
+    int* host_flag;         // mapped host flag set when Alg. 1 stops, or null
+    int nparts, stride;
+    int layer;              // this layer (1 ..)
+};
+
+// Arguments of the fragment-major split kernel (k_square_fm.h).
+struct FmArgs {
+    LeadArgs lead;
+    const void* x0;         // planes of X, fragment-major
+    const void* x1;
+    void* p0_out;           // planes of Y
+    void* p1_out;
+    const float* s_in;      // X, 32 x 32 blocks of the upper triangle in accumulator order
+    float* s_out;           // Y
+    double* parts_out;      // a pair per 64-tile; those of padding tiles stay zero
+    int pstride;            // 1 KB blocks per 32-row panel of a plane
+    int sb;                 // 32-blocks per row of blocks of S
+    int ku;                 // units of 16 K that hold data
+    int n_real;             // logical edge
+    int T, ntiles, per;     // 64-tiles per edge, in all, per XCD
+    float out_scale, in_scale;
+};
+// 1 KB blocks per 32-row panel: one more than the K units, so that panels do not start on
+// the same L2 channel
+__host__ __device__ inline int fm_pstride(int np) { return np / 16 + 1; }
 
 // Schedule of the persistent split-square kernel: G workgroups run `rounds` whole rounds
 // of tiles, then the `tail_tiles` leftover tiles are each cut into `chunks` K-chunks.

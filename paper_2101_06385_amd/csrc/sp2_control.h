@@ -55,61 +55,48 @@ __device__ inline void accelerated_choice(double l, double h, int* sgn, double* 
     }
 }
 
-// Runs on one workgroup of at least kControlThreads threads (every thread of the workgroup
-// calls it); sh: kControlLds doubles of LDS.  The partial sums are read with agent-scope
-// loads, because the workgroups of the same launch may have written them on other XCDs.
-// Fixed order: strided sums per thread, then a tree (across waves through LDS, the last six
-// levels inside wave 0), the same on every path, so the histories are bit-identical.
-constexpr int kControlThreads = 256;
-constexpr int kControlLds = 2 * kControlThreads;
-__device__ __forceinline__ double ld_agent(const double* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// Sum over the wave in the order of a halving tree (x[t] += x[t + w], w = 32 .. 1); lane 0 has
+// it.  The last four levels stay inside rows of 16 lanes (DPP), without LDS round trips.
+template <int N>
+__device__ __forceinline__ double dpp_shl(double v) {
+    typedef int i32x2 __attribute__((ext_vector_type(2)));
+    const i32x2 x = __builtin_bit_cast(i32x2, v);
+    const i32x2 y = {__builtin_amdgcn_update_dpp(0, x[0], 0x100 + N, 0xf, 0xf, true),
+                     __builtin_amdgcn_update_dpp(0, x[1], 0x100 + N, 0xf, 0xf, true)};
+    return __builtin_bit_cast(double, y);
 }
-__device__ __forceinline__ void st_agent(double* p, double v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ double wave_sum0(double v) {
+    v += __shfl_down(v, 32, 64);
+    v += __shfl_down(v, 16, 64);
+    v += dpp_shl<8>(v);
+    v += dpp_shl<4>(v);
+    v += dpp_shl<2>(v);
+    v += dpp_shl<1>(v);
+    return v;
 }
-__device__ __forceinline__ void control_body(DevState* st, const double* parts, int nparts, int stride, int layer,
-                                             volatile int* host_flag, double* sh) {
-    if (st->stopped) {
-        if (threadIdx.x == 0) {
-            st->skip = 1;
-            if (host_flag) *host_flag = 1;
-        }
-        return;
-    }
-    const int t = threadIdx.x;
-    double v[2] = {0.0, 0.0};
-    if (t < kControlThreads) {
-        for (int i = t; i < nparts; i += kControlThreads) {
-            v[0] += ld_agent(parts + (size_t)stride * i);
-            v[1] += ld_agent(parts + (size_t)stride * i + 1);
-        }
-        sh[t] = v[0];
-        sh[kControlThreads + t] = v[1];
-    }
-    __syncthreads();
-    if (t >= 64) return;
-    // wave 0: element t + 64 + (t + 128 + ...) in the order of a halving tree over 256
-    for (int c = 0; c < 2; ++c) {
-        const double* q = sh + c * kControlThreads + t;
-        double x = (q[0] + q[128]) + (q[64] + q[192]);
-        for (int w = 32; w > 0; w >>= 1) x += __shfl_down(x, w, 64);
-        v[c] = x;
-    }
-    if (t != 0) return;
-    const int n = layer;
-    const double n_s = v[0], n_x = v[1];
+__device__ __forceinline__ double first_lane(double v) {
+    typedef int i32x2 __attribute__((ext_vector_type(2)));
+    const i32x2 x = __builtin_bit_cast(i32x2, v);
+    const i32x2 y = {__builtin_amdgcn_readfirstlane(x[0]), __builtin_amdgcn_readfirstlane(x[1])};
+    return __builtin_bit_cast(double, y);
+}
+
+// Scalar logic of Alg. 1's layer n on the state's hot block: N_S and N_X of S_{n-1} in, the
+// layer's sigma and coefficients or the stop out.
+struct StepOut {
+    bool chosen;      // a sigma was chosen (false: non-finite or past max_layers)
+    int sigma;
+    double sigma_c, coef64[3];
+};
+__device__ __forceinline__ void control_step(StateHot* st, int n, double n_s, double n_x, StepOut* o) {
     const double e = n_s - n_x;
-    const int sp = st->sigma[n - 1];
-    st->ns[n] = n_s;
-    st->nx[n] = n_x;
-    st->iderr[n] = e;
-    bool stop = false, conv = false;
+    const int sp = st->sig1;
+    bool conv = false;
+    o->chosen = false;
     if (!isfinite(n_s) || !isfinite(n_x)) {
         st->status = SP2_ENONFINITE;
-        stop = true;
     } else if (n > st->max_layers) {
-        stop = true;   // S_{max_layers} is refined; status set by the final check
+        // S_{max_layers} is refined; status set by the final check
     } else {
         if (n == 1 && st->accel) {
             // rescaled bounds of S_0 = (emax I - H)/(emax - emin): the order is reversed
@@ -153,36 +140,34 @@ __device__ __forceinline__ void control_body(DevState* st, const double* parts, 
                 st->acc_h = s > 0 ? h * h : 2.0 * h - h * h;
             }
         }
-        st->sigma[n] = (signed char)s;
-        st->sigma_c[n] = sc;
+        o->chosen = true;
+        o->sigma = s;
+        o->sigma_c = sc;
         // the alternation test bounds IdErr_n by the two layers before it; it is taken
         // only when both were layers of Alg. 1
         if (e <= 0.0) conv = true;
-        else if (n > 2 && n >= st->acc_layers + 3 && st->sigma[n - 1] != st->sigma[n - 2] &&
-                 e > 4.5 * st->iderr[n - 2] * st->iderr[n - 2])
-            conv = true;
+        else if (n > 2 && n >= st->acc_layers + 3 && sp != st->sig2 && e > 4.5 * st->ide2 * st->ide2) conv = true;
+        st->sig2 = sp;
+        st->sig1 = s;
+        st->ide2 = st->ide1;
+        st->ide1 = e;
         if (!conv) {
-            st->coef[0] = (float)ca;
-            st->coef[1] = (float)cb;
-            st->coef[2] = (float)cc;
-            st->coef64[0] = ca;
-            st->coef64[1] = cb;
-            st->coef64[2] = cc;
+            o->coef64[0] = ca;
+            o->coef64[1] = cb;
+            o->coef64[2] = cc;
+            for (int i = 0; i < 3; ++i) st->coef[i] = (float)o->coef64[i];
             st->skip = 0;
             st->layers = n;
             st->ran = n;
             return;
         }
-        stop = true;
     }
     // stopping: refine S_{n-1}
     st->stopped = 1;
-    if (host_flag) *host_flag = 1;   // lets a host that polls stop enqueueing layers
     st->skip = 1;
     st->converged = conv ? 1 : 0;
     st->layers = (conv || !isfinite(n_s) || !isfinite(n_x)) ? n : n - 1;
-    const int last = st->sigma[n - 1];
-    const int fs = last != 0 ? -last : 1;
+    const int fs = sp != 0 ? -sp : 1;
     st->first_sign = fs;
     st->refine_src = (n - 1) & 1;
     // first composed step, then the opposite one (Eq. Refinement)
@@ -191,25 +176,201 @@ __device__ __forceinline__ void control_body(DevState* st, const double* parts, 
         st->rcoef[0][i] = fs > 0 ? sq[i] : pr[i];
         st->rcoef[1][i] = fs > 0 ? pr[i] : sq[i];
     }
-    (void)stop;
 }
 
-// A tile's partial sums are in parts[2 t], parts[2 t + 1] (written by thread 0 with
-// st_agent): counts the tile as done, and when it is the launch's last one runs the control of
-// the next layer, so that no separate control launch stands between two layers.  The launch
-// adds exactly a.ntiles arrivals; the count starts at 0 with the call's device state.  Every
-// thread of the workgroup calls it; sh: kControlLds doubles of LDS that no wave still reads.
+// Runs on one workgroup of NT threads (64, or at least 256; every thread of the workgroup
+// calls it); sh: kControlLds doubles of LDS.  The partial sums (a pair per tile, `stride`
+// doubles apart) are read with agent-scope loads, because the workgroups of the same
+// launch may have written them on other XCDs; the state's hot block comes in with them, one
+// dword per lane, so the whole control waits for memory once.  Fixed order: 256 strided sums,
+// then a tree over them, the same on every path, so the histories are bit-identical.
+constexpr int kControlThreads = 256;
+constexpr int kControlLds = 2 * kControlThreads + 32;
+__device__ __forceinline__ double ld_agent(const double* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_agent(double* p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <int NT>
+__device__ __forceinline__ void control_body(DevState* st, const double* parts, int nparts, int stride, int layer, volatile int* host_flag, double* sh) {
+    static_assert(NT == 64 || NT >= kControlThreads, "one wave, or all the strided sums at once");
+    const int t = threadIdx.x;
+    unsigned hot = 0;
+    if (t < 64) hot = ((const unsigned*)st)[t];
+    double v[2];
+    auto strided = [&](int k) {   // sum k of 256
+        v[0] = v[1] = 0.0;
+        for (int i = k; i < nparts; i += kControlThreads) {
+            const double* q = parts + (size_t)stride * i;
+            v[0] += ld_agent(q);
+            v[1] += ld_agent(q + 1);
+        }
+    };
+    if constexpr (NT == 64) {
+        double x[4][2];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            strided(t + 64 * k);
+            x[k][0] = v[0];
+            x[k][1] = v[1];
+        }
+        for (int c = 0; c < 2; ++c) v[c] = (x[0][c] + x[2][c]) + (x[1][c] + x[3][c]);
+    } else {
+        if (t < kControlThreads) {
+            strided(t);
+            sh[t] = v[0];
+            sh[kControlThreads + t] = v[1];
+        }
+        __syncthreads();
+        if (t >= 64) return;
+        for (int c = 0; c < 2; ++c) {
+            const double* q = sh + c * kControlThreads + t;
+            v[c] = (q[0] + q[128]) + (q[64] + q[192]);
+        }
+    }
+    unsigned* hs = (unsigned*)(sh + 2 * kControlThreads);
+    hs[t] = hot;
+    for (int c = 0; c < 2; ++c) v[c] = wave_sum0(v[c]);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // wave 0 alone from here: its LDS is in order
+    if (t == 0) {
+        StateHot* h = (StateHot*)hs;
+        if (h->stopped) {
+            h->skip = 1;
+            if (host_flag) *host_flag = 1;
+        } else {
+            const int n = layer ? layer : h->ran + 1;
+            StepOut o;
+            control_step(h, n, v[0], v[1], &o);
+            st->ns[n] = v[0];
+            st->nx[n] = v[1];
+            st->iderr[n] = v[0] - v[1];
+            if (o.chosen) {
+                st->sigma[n] = (signed char)o.sigma;
+                st->sigma_c[n] = o.sigma_c;
+                if (!h->stopped)
+                    for (int i = 0; i < 3; ++i) st->coef64[i] = o.coef64[i];
+            }
+            if (h->stopped && host_flag) *host_flag = 1;   // lets a host that polls stop enqueueing layers
+        }
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    ((unsigned*)st)[t] = hs[t];
+}
+
+// Leading control (see LeadArgs).  lead_load, by one wave, copies the hot block (256 bytes) and
+// the partial sums behind it into lead_bytes of LDS at `lds` (16-byte aligned; the last 256
+// bytes in front of the sums are for the block that is recorded) with
+// global_load_lds; lead_finish, by every wave that needs the result, runs once they have landed
+// (vector-memory loads complete in order, so any wait for a load behind lead_load will do).
+struct Coefs {
+    float f[3];
+    double d[3];
+};
+__host__ __device__ inline size_t lead_bytes(const LeadArgs& a) {
+    return 512 + ((size_t)a.nparts * a.stride * sizeof(double) + 1023) / 1024 * 1024;
+}
+__device__ __forceinline__ void lead_load(const LeadArgs& a, unsigned lds) {
+    const unsigned lane = threadIdx.x & 63;
+    asm volatile(
+        "s_mov_b32 m0, %2\n\t"
+        "s_nop 0\n\t"
+        "global_load_lds_dword %0, %1"
+        :
+        : "v"(4 * lane), "s"(a.hot_in), "s"(lds)
+        : "memory", "m0");
+    // whole 16 bytes (the buffers are padded to 256); past the end: the last ones again
+    const unsigned bytes = ((unsigned)a.nparts * a.stride * 8u + 15u) & ~15u;
+    for (unsigned o = 0; o < bytes; o += 1024) {
+        unsigned off = o + lane * 16;
+        off = off < bytes ? off : bytes - 16;
+        asm volatile(
+            "s_mov_b32 m0, %2\n\t"
+            "s_nop 0\n\t"
+            "global_load_lds_dwordx4 %0, %1"
+            :
+            : "v"(off), "s"(a.parts), "s"(lds + 512 + o)
+            : "memory", "m0");
+    }
+}
+// The layer's coefficients, or false when Alg. 1 has stopped.  record: this workgroup writes
+// the state (exactly one of the launch).  lead: the LDS that lead_load filled.
+__device__ __forceinline__ bool lead_finish(const LeadArgs& a, unsigned char* lead, bool record, Coefs* cf) {
+    const int t = threadIdx.x & 63;
+    const unsigned* hs = (const unsigned*)lead;   // other waves may still read it: never written
+    const double* parts = (const double*)(lead + 512);
+    double x[4][2], v[2];
+    for (int k = 0; k < 4; ++k) {   // strided sums t + 64 k of 256
+        x[k][0] = x[k][1] = 0.0;
+        for (int i = t + 64 * k; i < a.nparts; i += kControlThreads) {
+            const double* q = parts + (size_t)a.stride * i;
+            x[k][0] += q[0];
+            x[k][1] += q[1];
+        }
+    }
+    for (int c = 0; c < 2; ++c) v[c] = (x[0][c] + x[2][c]) + (x[1][c] + x[3][c]);
+    for (int c = 0; c < 2; ++c) v[c] = first_lane(wave_sum0(v[c]));
+    StateHot h = *(const StateHot*)hs;   // every lane takes the same decision
+    const int n = a.layer;
+    StepOut o;
+    o.chosen = false;
+    const bool was = h.stopped != 0;
+    if (!was) control_step(&h, n, v[0], v[1], &o);
+    else h.skip = 1;
+    if (record) {
+        unsigned* out = (unsigned*)(lead + 256);
+        if (t == 0) {
+            *(StateHot*)out = h;
+            if (!was) {
+                DevState* st = (DevState*)a.st;
+                st->ns[n] = v[0];
+                st->nx[n] = v[1];
+                st->iderr[n] = v[0] - v[1];
+                if (o.chosen) {
+                    st->sigma[n] = (signed char)o.sigma;
+                    st->sigma_c[n] = o.sigma_c;
+                }
+            }
+            if (h.stopped && a.host_flag) *(volatile int*)a.host_flag = 1;
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        ((unsigned*)a.hot_out)[t] = out[t];
+    }
+    if (h.stopped) return false;
+    for (int i = 0; i < 3; ++i) {
+        cf->d[i] = o.coef64[i];
+        cf->f[i] = (float)o.coef64[i];
+    }
+    return true;
+}
+
+// A tile's partial sums are in a.parts (written by thread 0 with st_agent); tile slot t of the
+// a.arrivals that the launch counts is done.  When it is the last one, the control of the next
+// layer runs, so that no separate control launch stands between two layers.  Arrivals are
+// counted in kDoneGroups groups and then over the groups (one counter for few tiles); the
+// counters start at 0 with the call's device state and go on by whole launches.  Every thread
+// of the workgroup calls it; sh: kControlLds doubles of LDS that no wave still reads.
 // Measured (n = 777, 40 layers): a control launch took 4.0 us and its gap 2 us per layer.
-__device__ __forceinline__ void tile_done(const SquareArgs& a, double* sh, int* s_done) {
+template <int NT>
+__device__ __forceinline__ void tile_done(const SquareArgs& a, int t, double* sh, int* s_done) {
     if (!a.ctl) return;
     DevState* st = (DevState*)a.ctl;
     if (threadIdx.x == 0) {
         wait_stores();   // the partial sums are coherent before the arrival is counted
-        *s_done = atomicAdd(&st->tiles_done, 1);
+        int* cnt = done_counters(st);
+        const int na = a.arrivals;
+        int last;
+        if (na <= 2 * kDoneGroups) {
+            last = (atomicAdd(cnt, 1) + 1) % na == 0;
+        } else {
+            const int g = t % kDoneGroups, members = (na - g + kDoneGroups - 1) / kDoneGroups;
+            last = (atomicAdd(cnt + (1 + g) * kDoneLineInts, 1) + 1) % members == 0;
+            if (last) last = (atomicAdd(cnt, 1) + 1) % kDoneGroups == 0;
+        }
+        *s_done = last;
     }
     __syncthreads();
-    if ((*s_done + 1) % a.ntiles == 0)
-        control_body(st, a.parts, a.ntiles, 2, st->ran + 1, (volatile int*)a.host_flag, sh);
+    if (*s_done) control_body<NT>(st, a.parts, a.ntiles, 2, 0, (volatile int*)a.host_flag, sh);
 }
 
 }  // namespace

@@ -34,7 +34,8 @@ __device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)
 // Written by the control kernels; read by the layer kernels (skip flag, layer
 // coefficients) and copied back to the host for sp2_info.
 // ---------------------------------------------------------------------------------
-struct DevState {
+// Everything the control of a layer reads, in one 256-byte block (one load by one wave).
+struct StateHot {
     int n, n_occ, n_padded, max_layers;
     int precision, tile, have_bounds, want_energy;
     int stopped;        // 1 once a stopping test held, a non-finite value appeared or the cap hit
@@ -45,28 +46,46 @@ struct DevState {
     int first_sign;     // first composed step of the refinement
     int refine_src;     // ping-pong index of the state matrix that is refined
     int ran;            // squaring layers that ran (the last layer whose control let it run)
+    // accelerated layers (Sec. Accelerated Deep-NN SP2)
+    int accel;          // 1 when the caller's interval rescaled into 0 <= l < h <= 1
+    int acc_layers;     // index of the last accelerated layer (0: none)
+    int gap_violation;  // first layer whose interval consistency check failed (0: none)
+    int sig1, sig2;     // sigma of the last layer and of the one before it
+    int pad0;
     float coef[3];      // (alpha, beta, gamma) of the current layer: Y = alpha X^2 + beta X + gamma I
     float rcoef[2][3];  // the two refinement layers
     float pad1;
     double eps, tol_tr, tol_id;
     double emin, emax;
+    double homo, lumo;    // caller's interval inside the gap (energies)
+    double acc_l, acc_h;  // unoccupied eigenvalues of S_{n-1} in [0, acc_l], occupied in [acc_h, 1]
+    double ide1, ide2;    // IdErr of the last layer and of the one before it
     double asym;
     double trace_d, frob_d, energy;
+    double pad2;
+};
+static_assert(sizeof(StateHot) == 256, "one 64-lane load");
+struct DevState : StateHot {
     signed char sigma[SP2_MAX_LAYERS + 1];  // index n = layer n (sigma[0] = 0)
     double iderr[SP2_MAX_LAYERS + 1];
     double ns[SP2_MAX_LAYERS + 1];
     double nx[SP2_MAX_LAYERS + 1];
-    // accelerated layers (Sec. Accelerated Deep-NN SP2)
-    int accel;          // 1 when the caller's interval rescaled into 0 <= l < h <= 1
-    int acc_layers;     // index of the last accelerated layer (0: none)
-    int gap_violation;  // first layer whose interval consistency check failed (0: none)
-    int tiles_done;     // squaring tiles finished in this call (tile_done in sp2_control.h)
-    double homo, lumo;  // caller's interval inside the gap (energies)
-    double acc_l, acc_h;  // unoccupied eigenvalues of S_{n-1} in [0, acc_l], occupied in [acc_h, 1]
     double sigma_c[SP2_MAX_LAYERS + 1];
     double coef64[3];   // the current layer's (alpha, beta, gamma) unrounded, for the FP64 layer kernels
     double pad3;
 };
+
+// Arrival counters of the call (tile_done in sp2_control.h), right behind the device state:
+// one 128-byte line each, kDoneGroups group counters and one for the groups.  Atomics on one
+// address take 11.5 ns each on MI355X (1400 arrivals: 17.5 us on one counter, 4.5 us on 8).
+constexpr int kDoneGroups = 32;
+constexpr int kDoneLineInts = 32;
+constexpr int kDoneInts = (kDoneGroups + 1) * kDoneLineInts;
+constexpr size_t kStateBytes = (sizeof(DevState) + 255) / 256 * 256;
+constexpr size_t kHot2 = kStateBytes + sizeof(int) * kDoneInts;   // second hot block (leading control)
+constexpr size_t kStateArea = kHot2 + sizeof(StateHot);           // state, counters, second hot block
+__host__ __device__ inline void* hot_block(DevState* st, int i) { return i & 1 ? (char*)st + kHot2 : (char*)st; }
+__host__ __device__ inline int* done_counters(DevState* st) { return (int*)((char*)st + kStateBytes); }
 
 // Upper-triangle tile enumeration shared by every kernel that works on (I <= J) tiles.
 // The T x T tile grid is cut into column strips of width G; strips are enumerated left
@@ -216,6 +235,13 @@ hipError_t launch_bounds(DevState* st, const double* blk, int nblk, hipStream_t 
 hipError_t launch_init_np(const double* h, int ldh, DevState* st, int np, int precision, void* s_out,
                           void* p0, void* p1, int scale_log2, double* parts, hipStream_t s);
 int init_tiles(int np);
+// fragment-major path (k_square_fm.h): input layer, FP64 expansion of S, last control
+hipError_t launch_init_fm(const double* h, int ldh, DevState* st, int np, int precision, float* s_out, void* p0,
+                          void* p1, int scale_log2, double* parts, double* zero, int nzero, hipStream_t s);
+hipError_t launch_select_fm(const DevState* st, const float* s0, const float* s1, double* out, int ld_out, int n,
+                            int n_valid, int np, hipStream_t s);
+hipError_t launch_lead_finish(const LeadArgs& a, hipStream_t s);
+hipError_t launch_fm(int precision, int variant, const FmArgs& a, hipStream_t s);
 hipError_t launch_control_stride(DevState* st, const double* parts, int nparts, int stride, int layer,
                                  int* host_flag, hipStream_t s);
 hipError_t launch_select_f64(const DevState* st, const void* s0, const void* s1, int state_f64,

@@ -1,7 +1,7 @@
 """Squaring kernels at the edges of their tiles: the direct-to-LDS 64-tile split kernel, the
-FP64 kernel on mixed 64 / 32 tiles, and the control of the next layer run by a squaring
-launch's last tile, each against the kernel that computes the same chain of products (bit for
-bit) or exact FP64 arithmetic."""
+FP64 kernel on mixed 64 / 32 tiles, the fragment-major split kernels, and the control of a
+layer run by a squaring launch, each against the kernel that computes the same chain of
+products (bit for bit) or exact FP64 arithmetic."""
 import numpy as np
 import pytest
 import torch
@@ -49,8 +49,8 @@ def test_fp64_mixed_tiles_equal_128_tiles_and_exact_square(n):
 @pytest.mark.parametrize("prec", ["fp16x2", "bf16x2"])
 @pytest.mark.parametrize("n,gap", [(10, None), (64, None), (300, None), (777, (-0.9, 0.9))])
 def test_control_in_the_squaring_launch_equals_separate_control(prec, n, gap):
-    """tile 64: kernel 1 runs each next layer's control in its last tile, kernel 8 has the
-    control launches; the histories and D are the same bits."""
+    """tile 64: kernel 1 runs the control in the squaring launches, kernel 8 has control
+    launches; the histories and D are the same bits."""
     w = wl.gapped(700 + n, n, n // 2)
     h = torch.from_numpy(w.h).to(DEV)
     d, i = sp2.density(h, w.n_occ, precision=prec, tile=64, kernel=1, gap=gap)
@@ -61,3 +61,46 @@ def test_control_in_the_squaring_launch_equals_separate_control(prec, n, gap):
     d2, i2 = sp2.density(h, w.n_occ, precision=prec, tile=64, kernel=1, gap=gap, max_layers=7)
     d28, i28 = sp2.density(h, w.n_occ, precision=prec, tile=64, kernel=8, gap=gap, max_layers=7)
     assert torch.equal(d2, d28) and i2["layers"] == i28["layers"] == 7 and i2["status"] == i28["status"]
+
+
+# fragment-major kernels: 32-blocks and 16-wide units of K that are partly or wholly padding; 4-wave
+# workgroups up to 512 64-tiles (n = 1984), one wave per tile above
+@pytest.mark.parametrize("prec,n", [("fp16x2", 2), ("bf16x2", 15), ("fp16x2", 17), ("fp16x2", 33), ("bf16x2", 48),
+                                    ("fp16x2", 96), ("bf16x2", 97), ("fp16x2", 129), ("fp16x2", 449),
+                                    ("fp16x2", 1984), ("bf16x2", 1985), ("fp16x2", 2040)])
+def test_fragment_major_layers_equal_register_staged_layers(prec, n):
+    w = wl.gapped(800 + n, n, max(1, n // 2), device=DEV if n > 1000 else None)
+    h = torch.from_numpy(w.h).to(DEV)
+    for kw in (dict(), dict(refine=False), dict(max_layers=3, refine=False)):
+        d, i = sp2.density(h, w.n_occ, precision=prec, tile=64, kernel=1, **kw)
+        d8, i8 = sp2.density(h, w.n_occ, precision=prec, tile=64, kernel=8, **kw)
+        assert torch.equal(d, d8) and torch.equal(d, d.T.contiguous())
+        for k in ("status", "layers", "sigma", "iderr", "ns", "nx"):
+            assert i[k] == i8[k], k
+
+
+@pytest.mark.parametrize("n", [130, 2050, 2943])
+def test_fragment_major_128_tile_order_equals_grouped_kernel(n):
+    """tile 128: the grouped kernel keeps row-major planes and 128-tiles."""
+    w = wl.gapped(900 + n, n, n // 3, device=DEV if n > 1000 else None)
+    h = torch.from_numpy(w.h).to(DEV)
+    d, i = sp2.density(h, w.n_occ, tile=128, kernel=1)
+    (dg,), (ig,) = sp2.density_batched([h], [w.n_occ], tile=128)
+    assert torch.equal(d, dg)
+    assert i["sigma"] == ig["sigma"] and i["status"] == ig["status"] == sp2.SP2_OK
+
+
+def test_fragment_major_async_call_and_layer_cap():
+    """Asynchronous calls enqueue every layer: the ones behind the stop return at once, with the
+    state carried through both hot blocks (odd and even caps)."""
+    w = wl.gapped(950, 500, 200)
+    h = torch.from_numpy(w.h).to(DEV)
+    d, i = sp2.density(h, w.n_occ)
+    for cap in (100, 101):
+        ws = sp2.alloc_workspace(sp2.workspace_size(500, sp2.options(max_layers=cap)), DEV)
+        da, _ = sp2.density(h, w.n_occ, sync=False, max_layers=cap, workspace=ws)
+        torch.cuda.synchronize()
+        q = sp2.query(ws, 500, max_layers=cap)
+        assert torch.equal(da, d)
+        for k in ("status", "layers", "sigma", "iderr", "trace", "converged"):
+            assert q[k] == i[k], k
