@@ -50,67 +50,7 @@ __device__ inline void block_sum(double (&v)[C], double* sh /* C * kThreads */) 
     for (int c = 0; c < C; ++c) v[c] = sh[c * kThreads];
 }
 
-struct StateParams {
-    int n, n_occ, np, max_layers, precision, tile, have_bounds, want_energy, accel;
-    double eps, tol_tr, tol_id, emin, emax, homo, lumo;
-};
-
-__global__ void k_state_init(DevState* st, StateParams p) {
-    const int t = threadIdx.x;
-    for (int i = t; i <= SP2_MAX_LAYERS; i += blockDim.x) {
-        st->sigma[i] = 0;
-        st->iderr[i] = 0.0;
-        st->ns[i] = 0.0;
-        st->nx[i] = 0.0;
-        st->sigma_c[i] = 0.0;
-    }
-    for (int i = t; i < kDoneInts; i += blockDim.x) done_counters(st)[i] = 0;
-    if (t == 0) {
-        st->n = p.n;
-        st->n_occ = p.n_occ;
-        st->n_padded = p.np;
-        st->max_layers = p.max_layers;
-        st->precision = p.precision;
-        st->tile = p.tile;
-        st->have_bounds = p.have_bounds;
-        st->want_energy = p.want_energy;
-        st->stopped = 0;
-        st->converged = 0;
-        st->layers = 0;
-        st->status = SP2_OK;
-        st->skip = 0;
-        st->first_sign = 0;
-        st->refine_src = 0;
-        st->ran = 0;
-        for (int i = 0; i < 3; ++i) {
-            st->coef[i] = 0.f;
-            st->coef64[i] = 0.0;
-        }
-        st->pad3 = 0.0;
-        for (int i = 0; i < 6; ++i) st->rcoef[i / 3][i % 3] = 0.f;
-        st->pad1 = 0.f;
-        st->eps = p.eps;
-        st->tol_tr = p.tol_tr;
-        st->tol_id = p.tol_id;
-        st->emin = p.emin;
-        st->emax = p.emax;
-        st->asym = 0.0;
-        st->trace_d = 0.0;
-        st->frob_d = 0.0;
-        st->energy = 0.0;
-        st->accel = p.accel;
-        st->acc_layers = 0;
-        st->gap_violation = 0;
-        st->sig1 = st->sig2 = 0;
-        st->ide1 = st->ide2 = 0.0;
-        st->pad0 = 0;
-        st->pad2 = 0.0;
-        st->homo = p.homo;
-        st->lumo = p.lumo;
-        st->acc_l = 0.0;
-        st->acc_h = 1.0;
-    }
-}
+__global__ void k_state_init(DevState* st, StateParams p) { init_state(st, p); }
 
 // One wavefront per row i: r_i = sum_{j != i} |H_ij| in FP64; the row interval
 // [H_ii - r_i, H_ii + r_i] widened by (2n + 4) ulp-units for the summation error.
@@ -373,21 +313,7 @@ __device__ __forceinline__ void finalize_body(DevState* st, const double* __rest
         __syncthreads();
     }
     if (threadIdx.x != 0) return;
-    st->trace_d = v[0];
-    st->frob_d = v[1];
-    st->energy = st->want_energy ? v[2] : 0.0;
-    st->asym = mx[0];
-    int status = st->status;
-    const double scale = fmax(fmax(fabs(st->emin), fabs(st->emax)), 1.0);
-    if (status == SP2_OK && !(mx[0] <= 1e-12 * scale)) status = SP2_EINVAL;
-    if (status == SP2_OK) {
-        const double idem = v[0] - v[1];
-        if (!isfinite(v[0]) || !isfinite(v[1])) status = SP2_ENONFINITE;
-        else if (st->gap_violation) status = SP2_ENOTIDEMP;   // the interval was not inside the gap
-        else if (!st->converged) status = SP2_ENOCONV;
-        else if (!(fabs(v[0] - st->n_occ) <= st->tol_tr) || !(fabs(idem) <= st->tol_id)) status = SP2_ENOTIDEMP;
-    }
-    st->status = status;
+    finish_state(st, v[0], v[1], v[2], mx[0]);
 }
 
 __global__ __launch_bounds__(kThreads) void k_fill(double* __restrict__ d, int ldd, int n, double diag) {
@@ -526,9 +452,13 @@ __global__ __launch_bounds__(kThreads) void k_control(DevState* st, const double
     __shared__ double sh[kControlLds];
     control_body<kThreads>(st, parts, nparts, stride, layer, host_flag, sh);
 }
+// host_state: null, or the mapped host copy of the state that a waiting host reads
 __global__ __launch_bounds__(kThreads) void k_finalize(DevState* st, const double* __restrict__ dparts, int nd,
-                                                       const double* __restrict__ iparts, int ni) {
+                                                       const double* __restrict__ iparts, int ni,
+                                                       DevState* __restrict__ host_state) {
     finalize_body(st, dparts, nd, iparts, ni);
+    __syncthreads();
+    if (host_state) copy_state(host_state, st);
 }
 template <typename St, typename T16, bool kSplit>
 __global__ __launch_bounds__(kThreads) void k_init(const double* __restrict__ h, int ldh,
@@ -665,24 +595,7 @@ inline int grid_for(size_t total) {
 
 // ------------------------------------------------------------------------------ launchers
 hipError_t launch_state_init(DevState* st, const DevState& in, hipStream_t s) {
-    StateParams p;
-    p.n = in.n;
-    p.n_occ = in.n_occ;
-    p.np = in.n_padded;
-    p.max_layers = in.max_layers;
-    p.precision = in.precision;
-    p.tile = in.tile;
-    p.have_bounds = in.have_bounds;
-    p.want_energy = in.want_energy;
-    p.eps = in.eps;
-    p.tol_tr = in.tol_tr;
-    p.tol_id = in.tol_id;
-    p.emin = in.emin;
-    p.emax = in.emax;
-    p.accel = in.accel;
-    p.homo = in.homo;
-    p.lumo = in.lumo;
-    hipLaunchKernelGGL(k_state_init, dim3(1), dim3(kThreads), 0, s, st, p);
+    hipLaunchKernelGGL(k_state_init, dim3(1), dim3(kThreads), 0, s, st, state_params(in));
     return hipGetLastError();
 }
 
@@ -788,8 +701,8 @@ hipError_t launch_dstats(const double* d, int ldd, const double* h, int ldh, int
 }
 
 hipError_t launch_finalize(DevState* st, const double* dparts, int nd, const double* iparts, int ni,
-                           hipStream_t s) {
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kThreads), 0, s, st, dparts, nd, iparts, ni);
+                           DevState* host_state, hipStream_t s) {
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kThreads), 0, s, st, dparts, nd, iparts, ni, host_state);
     return hipGetLastError();
 }
 

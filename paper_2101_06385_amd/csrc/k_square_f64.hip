@@ -213,7 +213,7 @@ __device__ __forceinline__ void f64_body(const SquareArgs& a, int I, int J, int 
                 const int row = I * BT + wm * C::WTM + m * 16 + 4 * r + (lane >> 4);
                 if (diag && row > col) continue;
                 const double xv = acc[m][n][r];
-                double y = (beta != 0.0) ? alpha * xv + beta * si[(size_t)row * np + col] : alpha * xv;
+                double y = (beta != 0.0) ? fma(alpha, xv, beta * si[(size_t)row * np + col]) : alpha * xv;
                 if (row == col && col < a.n_real) y += gamma;
                 if (row < nv && col < nv) {
                     so[(size_t)row * ldo + col] = y;

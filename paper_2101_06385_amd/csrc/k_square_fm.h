@@ -154,7 +154,8 @@ __device__ __forceinline__ void fm_store_block(const FmArgs& a, const Coefs& cf,
 }
 
 // One wave per workgroup, a 64 x 64 tile of Y (2 x 2 blocks): for problems with more 64-tiles
-// than the 4-wave workgroups' LDS lets a CU hold.  A wave's loads return 16 bytes per clock
+// than the 4-wave workgroups' LDS lets a CU hold.  The last tile runs the next layer's control
+// (the sums of so many tiles would take every wave longer than that).  A wave's loads return 16 bytes per clock
 // into registers and 32 from LDS (measured: a ring of registers alone runs at 512 cycles per
 // unit, whatever its depth, against 384 of the unit's 12 products), so the A fragments come
 // straight into registers, DA units ahead, and the B fragments through a ring of R units in
@@ -165,16 +166,15 @@ __global__ __launch_bounds__(64) void k_square_fm1(FmArgs a) {
     typedef typename Ops::vec8 vec8;
     static_assert((R & (R - 1)) == 0 && R >= 2 && R % 2 == 0 && DA % 2 == 0, "slot index by mask, pairs of units");
     constexpr int SLOT = 4 * 1024;
-    static_assert(R * SLOT >= kFmTranspose, "transpose fits the ring");
-    extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];   // lead_bytes
+    static_assert(R * SLOT >= kFmTranspose && R * SLOT >= kControlLds * 8, "transpose and control fit the ring");
     __shared__ __attribute__((aligned(16))) unsigned char ring[R * SLOT];
+    __shared__ int s_done;
     const int lane = threadIdx.x;
     const int t = xcd_tile_index(blockIdx.x, a.per, a.ntiles);
     if (t < 0) return;
     int I, J;
     tile_of(t, a.T, 8, &I, &J);
-    if (64 * J >= a.n_real) return;   // padding
-    lead_load(a.lead, (unsigned)(uintptr_t)(const fm_lds_byte*)dyn);
+    DevState* st = (DevState*)a.ctl;
     const int KU = a.ku;
     const size_t ps = (size_t)a.pstride * 512;
     const char* abase[4];   // X0 of rows 2 I, 2 I + 1, X1 of the same
@@ -223,19 +223,17 @@ __global__ __launch_bounds__(64) void k_square_fm1(FmArgs a) {
         if constexpr (w < R) fm_for<0, 4>([&](auto k) { load_b(k, w, off(w)); });
         if constexpr (w < DA) fm_for<0, 4>([&](auto k) { load_a(w, k, off(w)); });
     });
+    Coefs cf;   // read while the first loads are in flight
+    for (int i = 0; i < 3; ++i) cf.f[i] = st->coef[i];
+    const bool skip = st->skip;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (skip) return;   // Alg. 1 has stopped
     fm_for<0, 4>([&](auto k) { read_b(std::integral_constant<int, 0>{}, k, 0); });
     int u = 0;
     auto round = [&] {
         fm_for<0, DA>([&](auto d) { step(u + d, d, std::integral_constant<int, d & 1>{}); });
         u += DA;
     };
-    if (u + DA < KU) round();
-    Coefs cf;
-    if (!lead_finish(a.lead, dyn, blockIdx.x == 0, &cf)) {   // Alg. 1 has stopped
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        return;
-    }
     while (u + DA < KU) round();
     fm_for<0, DA>([&](auto d) {   // the last units
         constexpr int s = d & 1;
@@ -264,9 +262,10 @@ __global__ __launch_bounds__(64) void k_square_fm1(FmArgs a) {
         ft += wave_sum0(fr);
     });
     if (lane == 0) {
-        a.parts_out[2 * (size_t)t] = tt;
-        a.parts_out[2 * (size_t)t + 1] = ft;
+        st_agent(a.parts_out + 2 * (size_t)t, tt);
+        st_agent(a.parts_out + 2 * (size_t)t + 1, ft);
     }
+    tile_done<64>(st, a.parts_out, a.ntiles, t, a.host_flag, (double*)ring, &s_done);
 }
 
 // One 64 x 64 tile of Y per workgroup, in 4 waves of one 32 x 32 block each.  R slots of US
@@ -381,6 +380,11 @@ __global__ __launch_bounds__(256) void k_square_fm(FmArgs a) {
         fm_for<0, LPW>([&](auto l) { issue_one(l, w, sl); });
     }
     Frags fp, fq;
+    // a layer behind the stop (workgroup 0 still hands the state on)
+    if (((const StateHot*)a.lead.hot_in)->stopped && blockIdx.x != 0) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        return;
+    }
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"((R - 1) * LPW) : "memory");
     asm volatile("s_barrier" ::: "memory");
     fm_for<0, FPW * US>([&](auto i) { read_one(i, 0, fp); });
@@ -427,12 +431,12 @@ __global__ __launch_bounds__(256) void k_square_fm(FmArgs a) {
 // variant: ORD + 2 x (0: 4-wave workgroups, 1: one wave) (see fm_variant in sp2_api.hip)
 template <typename T16>
 hipError_t launch_fm_t(int variant, const FmArgs& a, hipStream_t s) {
-#define SP2_L(K, NT) hipLaunchKernelGGL((K), dim3(8 * a.per), dim3(NT), lead_bytes(a.lead), s, a)
+#define SP2_L(K, NT, LDS) hipLaunchKernelGGL((K), dim3(8 * a.per), dim3(NT), LDS, s, a)
     switch (variant) {
-        case 0: SP2_L((k_square_fm<T16, 4, 2, 0>), 256); break;
-        case 1: SP2_L((k_square_fm<T16, 4, 2, 1>), 256); break;
-        case 2: SP2_L((k_square_fm1<T16, 4, 4, 0>), 64); break;
-        case 3: SP2_L((k_square_fm1<T16, 4, 4, 1>), 64); break;
+        case 0: SP2_L((k_square_fm<T16, 4, 2, 0>), 256, lead_bytes(a.lead)); break;
+        case 1: SP2_L((k_square_fm<T16, 4, 2, 1>), 256, lead_bytes(a.lead)); break;
+        case 2: SP2_L((k_square_fm1<T16, 4, 4, 0>), 64, 0); break;
+        case 3: SP2_L((k_square_fm1<T16, 4, 4, 1>), 64, 0); break;
         default: return hipErrorInvalidValue;
     }
 #undef SP2_L

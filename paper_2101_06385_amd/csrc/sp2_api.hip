@@ -73,6 +73,7 @@ struct Plan {
     size_t off_sk_partial, off_sk_counter, total;
     bool fm;          // split layers by the fragment-major kernel (k_square_fm.h), variant fm_variant
     int fm_variant;
+    bool fm_lead;     // its control at the head of each launch (else by the last tile)
 };
 
 // The persistent (whole rounds + split tail) schedule needs a tile of 128 or 256 in a
@@ -203,8 +204,15 @@ void make_plan(int n, const Opts& o, Plan* p) {
     p->off_main_parts = off;
     p->sk_capable = sk_wanted(p->split, p->tile_main, kernel, p->np);
     p->fm = o.fm_ok && fm_wanted(p->split, p->tile_main, kernel, p->np) && !p->sk_capable;
-    if (p->fm) square_split_grid(64, p->np, &p->main_T, &p->main_tiles, &p->main_per);
-    p->fm_variant = p->fm ? fm_variant(p->tile_main, p->main_tiles) : 0;
+    p->fm_variant = 0;
+    p->fm_lead = false;
+    if (p->fm) {
+        square_split_grid(64, p->np, &p->main_T, &p->main_tiles, &p->main_per);
+        p->fm_variant = fm_variant(p->tile_main, ntiles_upper((n + 63) / 64));
+        p->fm_lead = p->fm_variant < 2;
+        // without leading control every launched tile is counted: only those that hold data
+        if (!p->fm_lead) square_split_grid(64, round_up(n, 64), &p->main_T, &p->main_tiles, &p->main_per);
+    }
     off = align_up(off + sizeof(double) * (p->fm ? 4 * p->main_tiles : 2 * p->main_tiles));   // fm: two buffers
     p->off_gersh = off;
     off = align_up(off + sizeof(double) * 3 * p->gersh_blocks);
@@ -266,17 +274,24 @@ void fill_info(const DevState& st, const Plan* p, sp2_info* info) {
         if ((expr) != hipSuccess) return SP2_EDEVICE;   \
     } while (0)
 
-// Pinned, device-mapped ints that the control kernel sets when Alg. 1 stops.  They are
-// allocated once per device and process (kFlagSlots slots of one 64-byte line each) and
-// never freed.  A synchronous call owns one slot from before its first launch until its
-// stream has drained, so no kernel of an earlier call can still write a slot that a later
-// call has reset.  With every slot taken the call runs without a flag (all layers enqueued,
-// as an asynchronous call does).
-constexpr int kFlagSlots = 64, kFlagDevices = 64, kFlagStride = 16;   // 16 ints = 64 bytes
+// Pinned, device-mapped slots of synchronous calls: a flag that the control sets when Alg. 1
+// stops, and a copy of the device state that the call's last kernel writes (a host that waits
+// for the stream then has the state without a transfer of its own: 10 us per call).  They are
+// allocated once per device and process (kFlagSlots slots) and never freed.  A synchronous
+// call owns one slot from before its first launch until its stream has drained, so no kernel
+// of an earlier call can still write a slot that a later call has reset.  With every slot
+// taken the call runs without one (all layers enqueued, as an asynchronous call does).
+constexpr int kFlagSlots = 64, kFlagDevices = 64;
+struct HostSlot {
+    int flag;
+    int pad[15];
+    DevState state;
+};
+constexpr size_t kSlotBytes = (sizeof(HostSlot) + 4095) / 4096 * 4096;
 struct FlagPool {
     std::mutex mu;
-    int* host[kFlagDevices] = {};
-    int* dev[kFlagDevices] = {};
+    char* host[kFlagDevices] = {};
+    char* dev[kFlagDevices] = {};
     unsigned long long used[kFlagDevices] = {};
 };
 FlagPool& flag_pool() {
@@ -287,8 +302,10 @@ FlagPool& flag_pool() {
 struct HostFlag {
     bool on = false, ok = true;
     int device = -1, slot = -1;
-    volatile int* host = nullptr;
+    volatile int* host = nullptr;         // the flag
     int* dev = nullptr;
+    const DevState* state = nullptr;      // the state copy
+    DevState* dev_state = nullptr;
     hipStream_t stream = nullptr;
     HostFlag(bool enable, hipStream_t s) : stream(s) {
         if (!enable) return;
@@ -296,9 +313,9 @@ struct HostFlag {
         FlagPool& fp = flag_pool();
         std::lock_guard<std::mutex> lock(fp.mu);
         if (!fp.host[device]) {
-            int* h = nullptr;
-            int* d = nullptr;
-            if (hipHostMalloc((void**)&h, sizeof(int) * kFlagStride * kFlagSlots, hipHostMallocMapped) != hipSuccess) {
+            char* h = nullptr;
+            char* d = nullptr;
+            if (hipHostMalloc((void**)&h, kSlotBytes * kFlagSlots, hipHostMallocMapped) != hipSuccess) {
                 ok = false;
                 return;
             }
@@ -317,32 +334,44 @@ struct HostFlag {
             }
         if (slot < 0) return;
         fp.used[device] |= 1ull << slot;
-        host = fp.host[device] + kFlagStride * slot;
-        dev = fp.dev[device] + kFlagStride * slot;
+        HostSlot* hs = (HostSlot*)(fp.host[device] + kSlotBytes * slot);
+        HostSlot* ds = (HostSlot*)(fp.dev[device] + kSlotBytes * slot);
+        host = &hs->flag;
+        dev = &ds->flag;
+        state = &hs->state;
+        dev_state = &ds->state;
         *host = 0;
         on = true;
+    }
+    // the stream has drained: the slot may be handed out again
+    void release() {
+        if (slot < 0) return;
+        FlagPool& fp = flag_pool();
+        std::lock_guard<std::mutex> lock(fp.mu);
+        fp.used[device] &= ~(1ull << slot);
+        slot = -1;
     }
     ~HostFlag() {
         if (slot < 0) return;
         // a slot whose call's kernels may still be queued is never handed out again
         if (hipStreamSynchronize(stream) != hipSuccess) return;
-        FlagPool& fp = flag_pool();
-        std::lock_guard<std::mutex> lock(fp.mu);
-        fp.used[device] &= ~(1ull << slot);
+        release();
     }
 };
 
+// Events between the chunks of layers that a polling host waits for, created as they are needed.
 struct ChunkEvents {
-    bool ok = true;
-    int count = 0;
     hipEvent_t ev[SP2_MAX_LAYERS + 2] = {};
-    ChunkEvents(bool enable, int n) : count(enable ? n : 0) {
-        for (int i = 0; i < count; ++i)
-            ok = ok && hipEventCreateWithFlags(&ev[i], hipEventDisableTiming) == hipSuccess;
+    hipError_t record(int i, hipStream_t s) {
+        if (!ev[i]) {
+            const hipError_t e = hipEventCreateWithFlags(&ev[i], hipEventDisableTiming);
+            if (e != hipSuccess) return e;
+        }
+        return hipEventRecord(ev[i], s);
     }
     ~ChunkEvents() {
-        for (int i = 0; i < count; ++i)
-            if (ev[i]) (void)hipEventDestroy(ev[i]);
+        for (hipEvent_t e : ev)
+            if (e) (void)hipEventDestroy(e);
     }
 };
 
@@ -464,14 +493,14 @@ static DevState initial_state(int n, int n_occ, double tol, const Opts& o, const
 // Occupation 0 or n: D = 0 or I is fixed by the occupation alone; the state (already
 // initialised at the start of ws) records a converged call of 0 layers.
 static hipError_t run_trivial(const double* dH, int ldh, double* dD, int ldd, int n, int n_occ, const Opts& o,
-                       const Plan& p, char* ws, hipStream_t s) {
+                       const Plan& p, char* ws, DevState* host_state, hipStream_t s) {
     DevState* st = (DevState*)ws;
     double* dstats = (double*)(ws + p.off_dstats);
     hipError_t e = launch_fill(dD, ldd, n, n_occ == n ? 1.0 : 0.0, s);
     int nd = 0;
     if (e == hipSuccess) e = launch_dstats(dD, ldd, o.want_energy ? dH : nullptr, ldh, n, dstats, &nd, s);
     if (e == hipSuccess) e = launch_mark_trivial(st, s);
-    if (e == hipSuccess) e = launch_finalize(st, dstats, nd, (const double*)(ws + p.off_init_parts), 0, s);
+    if (e == hipSuccess) e = launch_finalize(st, dstats, nd, (const double*)(ws + p.off_init_parts), 0, host_state, s);
     return e;
 }
 
@@ -504,13 +533,19 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
     if (!flag.ok) return SP2_EDEVICE;
 
     const DevState init = initial_state(n, n_occ, tol, o, p);
-    SP2_TRY(launch_state_init(st, init, s));
+    // The smallest problems run in one launch (k_tiny.hip) when the schedule is left open; a
+    // timed call keeps the launches that it times.  n = 10: 325 us per call in launches per layer.
+    const bool tiny = n <= kTinyMax && n_occ > 0 && n_occ < n && o.tile == 0 && o.kernel == 0 &&
+                      o.precision != SP2_FP32 && !timing;
+    if (!tiny) SP2_TRY(launch_state_init(st, init, s));
 
     double* init_parts = (double*)(ws + p.off_init_parts);
     double* main_parts = (double*)(ws + p.off_main_parts);
 
-    if (n_occ == 0 || n_occ == n) {
-        SP2_TRY(run_trivial(dH, ldh, dD, ldd, n, n_occ, o, p, ws, s));
+    if (tiny) {
+        SP2_TRY(launch_tiny(dH, ldh, dD, ldd, st, init, p.scale_log2, o.refine, flag.dev_state, s));
+    } else if (n_occ == 0 || n_occ == n) {
+        SP2_TRY(run_trivial(dH, ldh, dD, ldd, n, n_occ, o, p, ws, flag.dev_state, s));
     } else {
         double* dstats = (double*)(ws + p.off_dstats);
         if (!o.have_bounds) {
@@ -559,9 +594,8 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
         // stops, so that no layers are enqueued long after convergence: layers go out in
         // chunks, two chunks ahead of the one the host waits for.  Asynchronous calls
         // enqueue every layer up to max_layers (later ones return at once).
-        const int chunk = n >= 4096 ? 2 : (n >= 1024 ? 4 : 8);
-        ChunkEvents cev(flag.on, (o.max_layers + chunk) / chunk + 1);
-        if (!cev.ok) return SP2_EDEVICE;
+        const int chunk = n >= 1024 ? 2 : 4;
+        ChunkEvents cev;
         // every split and FP64 kernel but the register-staged ones runs the next layer's control itself
         const bool fused = (p.split && p.kernel != kKernelLegacyTile) || (o.precision == SP2_FP64 && o.kernel != 1);
         if (fused) {
@@ -594,7 +628,9 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
             fm.n_real = n;
             fm.T = p.main_T;
             fm.ntiles = p.main_tiles;
-            fm.per = (p.main_tiles + 7) / 8;
+            fm.per = p.main_per;
+            fm.ctl = st;
+            fm.host_flag = flag.dev;
             fm.out_scale = a.out_scale;
             fm.in_scale = a.in_scale;
         }
@@ -602,7 +638,7 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
         for (int layer = 1; layer <= o.max_layers + 1; ++layer) {
             if (flag.on && layer > 1 && (layer - 1) % chunk == 0) {
                 const int c = (layer - 1) / chunk;          // chunk about to start
-                SP2_TRY(hipEventRecord(cev.ev[c - 1], s));  // end of chunk c - 1
+                SP2_TRY(cev.record(c - 1, s));              // end of chunk c - 1
                 if (c >= 2) {
                     SP2_TRY(hipEventSynchronize(cev.ev[c - 2]));
                     waited = c - 1;
@@ -610,8 +646,10 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
                 }
             }
             if (p.fm) {
+                if (!p.fm_lead && layer == 1)
+                    SP2_TRY(launch_control_stride(st, init_parts, p.init_tiles, 3, layer, flag.dev, s));
                 if (layer > o.max_layers) break;
-                fm.lead = lead_of(layer);
+                if (p.fm_lead) fm.lead = lead_of(layer);
                 fm_done = layer;
                 const int in = (layer - 1) & 1, out = layer & 1;
                 fm.x0 = P[in][0];
@@ -620,7 +658,7 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
                 fm.p1_out = P[out][1];
                 fm.s_in = (const float*)S[in];
                 fm.s_out = (float*)S[out];
-                fm.parts_out = main_parts + (size_t)((layer + 1) & 1) * 2 * p.main_tiles;
+                fm.parts_out = main_parts + (p.fm_lead ? (size_t)((layer + 1) & 1) * 2 * p.main_tiles : 0);
                 ev.launched = layer;
                 SP2_TRY(ev.rec(ev.sq_b[layer], s));
                 SP2_TRY(launch_fm(o.precision, p.fm_variant, fm, s));
@@ -652,7 +690,7 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
             SP2_TRY(ev.rec(ev.sq_e[layer], s));
         }
         (void)waited;
-        if (p.fm) {
+        if (p.fm_lead) {
             LeadArgs lead = lead_of(fm_done + 1);
             lead.hot_out = hot_block(st, 0);
             SP2_TRY(launch_lead_finish(lead, s));
@@ -700,19 +738,22 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
         }
         int nd = 0;
         SP2_TRY(launch_dstats(dD, ldd, o.want_energy ? dH : nullptr, ldh, n, dstats, &nd, s));
-        SP2_TRY(launch_finalize(st, dstats, nd, init_parts, p.init_tiles, s));
+        SP2_TRY(launch_finalize(st, dstats, nd, init_parts, p.init_tiles, flag.dev_state, s));
     }
     SP2_TRY(ev.rec(ev.end, s));
     if (!info && !timing) return SP2_OK;
-    DevState host;
+    DevState copy;
     SP2_TRY(hipStreamSynchronize(s));
-    SP2_TRY(hipMemcpy(&host, st, sizeof(DevState), hipMemcpyDeviceToHost));
+    if (!flag.on) SP2_TRY(hipMemcpy(&copy, st, sizeof(DevState), hipMemcpyDeviceToHost));
+    const DevState& host = flag.on ? *flag.state : copy;
     if (info) fill_info(host, &p, info);
     if (timing) {
         const bool trivial = (n_occ == 0 || n_occ == n);
         SP2_TRY(ev.fill(timing, trivial ? 0 : host.ran, trivial));
     }
-    return host.status;
+    const int status = host.status;
+    flag.release();
+    return status;
 }
 
 extern "C" {
@@ -1289,7 +1330,7 @@ static int run_batched(int batch, const double* const* dH, const int* ldh, doubl
         if (n_occ[i] > 0 && n_occ[i] < n[i]) continue;
         char* r = ws + L.region[i];
         SP2_TRY(launch_state_init((DevState*)r, initial_state(n[i], n_occ[i], tol, o, L.plans[i]), user));
-        SP2_TRY(run_trivial(dH[i], ldh[i], dD[i], ldd[i], n[i], n_occ[i], o, L.plans[i], r, user));
+        SP2_TRY(run_trivial(dH[i], ldh[i], dD[i], ldd[i], n[i], n_occ[i], o, L.plans[i], r, nullptr, user));
     }
     const int nt = (int)L.nontrivial.size();
     if (nt > 0) {

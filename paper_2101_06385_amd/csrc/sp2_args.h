@@ -48,7 +48,9 @@ struct LeadArgs {
 
 // Arguments of the fragment-major split kernel (k_square_fm.h).
 struct FmArgs {
-    LeadArgs lead;
+    LeadArgs lead;          // leading control (4-wave workgroups)
+    void* ctl;              // DevState: control of the next layer by the last tile (one wave per tile)
+    int* host_flag;
     const void* x0;         // planes of X, fragment-major
     const void* x1;
     void* p0_out;           // planes of Y

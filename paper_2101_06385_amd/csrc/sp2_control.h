@@ -55,6 +55,88 @@ __device__ inline void accelerated_choice(double l, double h, int* sgn, double* 
     }
 }
 
+// The device state at the start of a call (by one workgroup).
+__device__ __forceinline__ void init_hot(StateHot* st, const StateParams& p) {
+    st->n = p.n;
+    st->n_occ = p.n_occ;
+    st->n_padded = p.np;
+    st->max_layers = p.max_layers;
+    st->precision = p.precision;
+    st->tile = p.tile;
+    st->have_bounds = p.have_bounds;
+    st->want_energy = p.want_energy;
+    st->stopped = 0;
+    st->converged = 0;
+    st->layers = 0;
+    st->status = SP2_OK;
+    st->skip = 0;
+    st->first_sign = 0;
+    st->refine_src = 0;
+    st->ran = 0;
+    st->accel = p.accel;
+    st->acc_layers = 0;
+    st->gap_violation = 0;
+    st->sig1 = st->sig2 = 0;
+    st->pad0 = 0;
+    for (int i = 0; i < 3; ++i) st->coef[i] = 0.f;
+    for (int i = 0; i < 6; ++i) st->rcoef[i / 3][i % 3] = 0.f;
+    st->pad1 = 0.f;
+    st->eps = p.eps;
+    st->tol_tr = p.tol_tr;
+    st->tol_id = p.tol_id;
+    st->emin = p.emin;
+    st->emax = p.emax;
+    st->homo = p.homo;
+    st->lumo = p.lumo;
+    st->acc_l = 0.0;
+    st->acc_h = 1.0;
+    st->ide1 = st->ide2 = 0.0;
+    st->asym = 0.0;
+    st->trace_d = 0.0;
+    st->frob_d = 0.0;
+    st->energy = 0.0;
+    st->pad2 = 0.0;
+}
+__device__ __forceinline__ void init_state(DevState* st, const StateParams& p) {
+    const int t = threadIdx.x;
+    for (int i = t; i <= SP2_MAX_LAYERS; i += blockDim.x) {
+        st->sigma[i] = 0;
+        st->iderr[i] = 0.0;
+        st->ns[i] = 0.0;
+        st->nx[i] = 0.0;
+        st->sigma_c[i] = 0.0;
+    }
+    for (int i = t; i < kDoneInts; i += blockDim.x) done_counters(st)[i] = 0;
+    if (t == 0) {
+        for (int i = 0; i < 3; ++i) st->coef64[i] = 0.0;
+        st->pad3 = 0.0;
+        init_hot(st, p);
+    }
+}
+// Final occupation / idempotency acceptance test.
+__device__ __forceinline__ void finish_state(StateHot* st, double trace, double frob, double energy, double asym) {
+    st->trace_d = trace;
+    st->frob_d = frob;
+    st->energy = st->want_energy ? energy : 0.0;
+    st->asym = asym;
+    int status = st->status;
+    const double scale = fmax(fmax(fabs(st->emin), fabs(st->emax)), 1.0);
+    if (status == SP2_OK && !(asym <= 1e-12 * scale)) status = SP2_EINVAL;
+    if (status == SP2_OK) {
+        const double idem = trace - frob;
+        if (!isfinite(trace) || !isfinite(frob)) status = SP2_ENONFINITE;
+        else if (st->gap_violation) status = SP2_ENOTIDEMP;   // the interval was not inside the gap
+        else if (!st->converged) status = SP2_ENOCONV;
+        else if (!(fabs(trace - st->n_occ) <= st->tol_tr) || !(fabs(idem) <= st->tol_id)) status = SP2_ENOTIDEMP;
+    }
+    st->status = status;
+}
+// by one workgroup
+__device__ __forceinline__ void copy_state(DevState* dst, const DevState* src) {
+    for (int i = threadIdx.x; i < (int)(sizeof(DevState) / 4); i += blockDim.x)
+        ((unsigned*)dst)[i] = ((const unsigned*)src)[i];
+}
+
 // Sum over the wave in the order of a halving tree (x[t] += x[t + w], w = 32 .. 1); lane 0 has
 // it.  The last four levels stay inside rows of 16 lanes (DPP), without LDS round trips.
 template <int N>
@@ -199,26 +281,56 @@ __device__ __forceinline__ void control_body(DevState* st, const double* parts, 
     unsigned hot = 0;
     if (t < 64) hot = ((const unsigned*)st)[t];
     double v[2];
-    auto strided = [&](int k) {   // sum k of 256
-        v[0] = v[1] = 0.0;
-        for (int i = k; i < nparts; i += kControlThreads) {
-            const double* q = parts + (size_t)stride * i;
-            v[0] += ld_agent(q);
-            v[1] += ld_agent(q + 1);
+    // sum k of 256: four loads in flight at a time (an element past the end adds zero)
+    auto strided = [&](int k, double (&x)[2]) {
+        x[0] = x[1] = 0.0;
+        for (int i = k; i < nparts; i += 4 * kControlThreads) {
+            double p[4], r[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int e = i + j * kControlThreads;
+                const double* q = parts + (size_t)stride * (e < nparts ? e : i);
+                p[j] = ld_agent(q);
+                r[j] = ld_agent(q + 1);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (i + j * kControlThreads < nparts) {
+                    x[0] += p[j];
+                    x[1] += r[j];
+                }
         }
     };
     if constexpr (NT == 64) {
         double x[4][2];
+        if (nparts <= 4 * kControlThreads) {   // every load of the wave in flight at once
+            double p[4][4], r[4][4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            strided(t + 64 * k);
-            x[k][0] = v[0];
-            x[k][1] = v[1];
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int e = t + 64 * k + j * kControlThreads;
+                    const double* q = parts + (size_t)stride * (e < nparts ? e : 0);
+                    p[k][j] = ld_agent(q);
+                    r[k][j] = ld_agent(q + 1);
+                }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                x[k][0] = x[k][1] = 0.0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (t + 64 * k + j * kControlThreads < nparts) {
+                        x[k][0] += p[k][j];
+                        x[k][1] += r[k][j];
+                    }
+            }
+        } else {
+            for (int k = 0; k < 4; ++k) strided(t + 64 * k, x[k]);
         }
         for (int c = 0; c < 2; ++c) v[c] = (x[0][c] + x[2][c]) + (x[1][c] + x[3][c]);
     } else {
         if (t < kControlThreads) {
-            strided(t);
+            strided(t, v);
             sh[t] = v[0];
             sh[kControlThreads + t] = v[1];
         }
@@ -344,33 +456,35 @@ __device__ __forceinline__ bool lead_finish(const LeadArgs& a, unsigned char* le
     return true;
 }
 
-// A tile's partial sums are in a.parts (written by thread 0 with st_agent); tile slot t of the
-// a.arrivals that the launch counts is done.  When it is the last one, the control of the next
+// A tile's pair of partial sums is in parts (written by thread 0 with st_agent); slot t of the
+// `arrivals` that the launch counts is done.  When it is the last one, the control of the next
 // layer runs, so that no separate control launch stands between two layers.  Arrivals are
 // counted in kDoneGroups groups and then over the groups (one counter for few tiles); the
 // counters start at 0 with the call's device state and go on by whole launches.  Every thread
 // of the workgroup calls it; sh: kControlLds doubles of LDS that no wave still reads.
 // Measured (n = 777, 40 layers): a control launch took 4.0 us and its gap 2 us per layer.
 template <int NT>
-__device__ __forceinline__ void tile_done(const SquareArgs& a, int t, double* sh, int* s_done) {
-    if (!a.ctl) return;
-    DevState* st = (DevState*)a.ctl;
+__device__ __forceinline__ void tile_done(DevState* st, const double* parts, int arrivals, int t, int* host_flag,
+                                          double* sh, int* s_done) {
     if (threadIdx.x == 0) {
         wait_stores();   // the partial sums are coherent before the arrival is counted
         int* cnt = done_counters(st);
-        const int na = a.arrivals;
         int last;
-        if (na <= 2 * kDoneGroups) {
-            last = (atomicAdd(cnt, 1) + 1) % na == 0;
+        if (arrivals <= 2 * kDoneGroups) {
+            last = (atomicAdd(cnt, 1) + 1) % arrivals == 0;
         } else {
-            const int g = t % kDoneGroups, members = (na - g + kDoneGroups - 1) / kDoneGroups;
+            const int g = t % kDoneGroups, members = (arrivals - g + kDoneGroups - 1) / kDoneGroups;
             last = (atomicAdd(cnt + (1 + g) * kDoneLineInts, 1) + 1) % members == 0;
             if (last) last = (atomicAdd(cnt, 1) + 1) % kDoneGroups == 0;
         }
         *s_done = last;
     }
     __syncthreads();
-    if (*s_done) control_body<NT>(st, a.parts, a.ntiles, 2, 0, (volatile int*)a.host_flag, sh);
+    if (*s_done) control_body<NT>(st, parts, arrivals, 2, 0, (volatile int*)host_flag, sh);
+}
+template <int NT>
+__device__ __forceinline__ void tile_done(const SquareArgs& a, int t, double* sh, int* s_done) {
+    if (a.ctl) tile_done<NT>((DevState*)a.ctl, a.parts, a.arrivals, t, a.host_flag, sh, s_done);
 }
 
 }  // namespace

@@ -87,6 +87,32 @@ constexpr size_t kStateArea = kHot2 + sizeof(StateHot);           // state, coun
 __host__ __device__ inline void* hot_block(DevState* st, int i) { return i & 1 ? (char*)st + kHot2 : (char*)st; }
 __host__ __device__ inline int* done_counters(DevState* st) { return (int*)((char*)st + kStateBytes); }
 
+// What a call's device state starts from.
+struct StateParams {
+    int n, n_occ, np, max_layers, precision, tile, have_bounds, want_energy, accel;
+    double eps, tol_tr, tol_id, emin, emax, homo, lumo;
+};
+inline StateParams state_params(const DevState& in) {
+    StateParams p;
+    p.n = in.n;
+    p.n_occ = in.n_occ;
+    p.np = in.n_padded;
+    p.max_layers = in.max_layers;
+    p.precision = in.precision;
+    p.tile = in.tile;
+    p.have_bounds = in.have_bounds;
+    p.want_energy = in.want_energy;
+    p.eps = in.eps;
+    p.tol_tr = in.tol_tr;
+    p.tol_id = in.tol_id;
+    p.emin = in.emin;
+    p.emax = in.emax;
+    p.accel = in.accel;
+    p.homo = in.homo;
+    p.lumo = in.lumo;
+    return p;
+}
+
 // Upper-triangle tile enumeration shared by every kernel that works on (I <= J) tiles.
 // The T x T tile grid is cut into column strips of width G; strips are enumerated left
 // to right, and inside a strip the tiles go row by row.  Consecutive indices therefore
@@ -250,7 +276,11 @@ hipError_t launch_dstats(const double* d, int ldd, const double* h, int ldh, int
                          double* parts, int* nparts, hipStream_t s);
 int dstats_blocks(int n);
 hipError_t launch_finalize(DevState* st, const double* dparts, int ndparts, const double* init_parts,
-                           int ninit, hipStream_t s);
+                           int ninit, DevState* host_state, hipStream_t s);
+// the whole solve of n <= kTinyMax in one workgroup (k_tiny.hip): split modes and FP64
+constexpr int kTinyMax = 64;
+hipError_t launch_tiny(const double* h, int ldh, double* d, int ldd, DevState* st, const DevState& init, int scale_log2,
+                       int refine, DevState* host_state, hipStream_t s);
 hipError_t launch_fill(double* d, int ldd, int n, double diag, hipStream_t s);
 hipError_t launch_split(const float* x, void* p0, void* p1, int np, int precision, int scale_log2,
                         hipStream_t s);

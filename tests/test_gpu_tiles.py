@@ -104,3 +104,35 @@ def test_fragment_major_async_call_and_layer_cap():
         assert torch.equal(da, d)
         for k in ("status", "layers", "sigma", "iderr", "trace", "converged"):
             assert q[k] == i[k], k
+
+
+# one workgroup per solve up to n = 64: one and two 32-blocks, ragged 16-wide units of K
+@pytest.mark.parametrize("prec", ["fp16x2", "bf16x2", "fp64"])
+@pytest.mark.parametrize("n", [2, 3, 15, 16, 17, 32, 33, 50, 64])
+def test_one_workgroup_solve_equals_layer_launches(prec, n):
+    w = wl.gapped(1000 + n, n, max(1, n // 2))
+    big = torch.zeros((n, n + 7), dtype=torch.float64, device=DEV)
+    big[:, :n] = torch.from_numpy(w.h)
+    h = big[:, :n]
+    for kw in (dict(), dict(refine=False), dict(gap=(-0.9, 0.8), want_energy=True), dict(max_layers=4),
+               dict(bounds=(-21.0, 22.0))):
+        out = torch.full((n, n + 3), 9.0, dtype=torch.float64, device=DEV)
+        d, i = sp2.density(h, w.n_occ, precision=prec, out=out[:, :n], **kw)
+        d1, i1 = sp2.density(h, w.n_occ, precision=prec, tile=64, kernel=5 if prec == "fp64" else 1, **kw)
+        assert torch.equal(d, d1) and torch.all(out[:, n:] == 9.0)
+        for k in ("status", "layers", "converged", "sigma", "accelerated", "gap_violation", "emin", "emax", "asym"):
+            assert i[k] == i1[k], (k, kw)
+        # sums of n^2 terms in another order
+        for k in ("trace", "energy"):
+            scale = float((d.abs() * (h.abs() if k == "energy" else 1.0)).sum())
+            assert abs(i[k] - i1[k]) <= 2 * (n * n + 1) * 2.0**-53 * scale, k
+
+
+def test_one_workgroup_solve_reports_bad_input():
+    w = wl.gapped(1100, 20, 8)
+    for change, name in ((float("nan"), "ENONFINITE"), (w.h[3, 4] + 1e-3, "EINVAL")):
+        x = w.h.copy()
+        x[3, 4] = change
+        _, i = sp2.density(torch.from_numpy(x).to(DEV), w.n_occ)
+        _, i1 = sp2.density(torch.from_numpy(x).to(DEV), w.n_occ, tile=64, kernel=1)
+        assert i["status_name"] == i1["status_name"] == name
