@@ -90,9 +90,12 @@ __device__ inline double wsum(double v) {
 }
 
 // Output tile (I, J) of edge BT over all of K; t is the tile's slot in a.parts.
-template <int BT, int WM, int WN, int ST>
+// LEAD: the layer's control at its head (`lead`, lead_bytes of LDS at `dyn`) instead of the next
+// layer's control by the last tile.
+template <int BT, int WM, int WN, int ST, bool LEAD = false>
 __device__ __forceinline__ void f64_body(const SquareArgs& a, int I, int J, int t, unsigned char* __restrict__ lds,
-                                         double* __restrict__ red, int* __restrict__ s_done) {
+                                         double* __restrict__ red, int* __restrict__ s_done,
+                                         const LeadArgs* lead = nullptr, unsigned char* __restrict__ dyn = nullptr) {
     typedef F64Cfg<BT, WM, WN, ST> C;
     constexpr int MB = C::MB, NB = C::NB, LPW = C::LPW;
     static_assert(ST >= 2 && ST <= 4, "stages");
@@ -165,13 +168,21 @@ __device__ __forceinline__ void f64_body(const SquareArgs& a, int I, int J, int 
 
     // stage q is issued by advance(q - ST + 1); the prologue plays those of 0 .. ST - 1
     const int pro = nsl < ST ? nsl : ST;
+    if (LEAD && wave == 0) lead_load(*lead, lds_addr(dyn));
     for (int q = 0; q < pro; ++q) issue(q, q);
-    if (a.skip && *a.skip) {   // read while the first loads are in flight
+    // read while the first loads are in flight
+    const bool stop = LEAD ? ((const StateHot*)lead->hot_in)->stopped && blockIdx.x != 0 : a.skip && *a.skip;
+    if (stop) {
         wait_vm(0);
         return;
     }
     wait_vm((pro - 1) * LPW);
     __syncthreads();
+    Coefs cf;
+    if (LEAD && !lead_finish(*lead, dyn, blockIdx.x == 0 && wave == 0, &cf)) {   // Alg. 1 has stopped
+        wait_vm(0);
+        return;
+    }
     f64x2 pa[MB], pb[NB], qa[MB], qb[NB];
     frags(0, 0, pa, pb);
     // stage `next` readable: its loads landed (this wave's), every wave past the barrier
@@ -195,9 +206,9 @@ __device__ __forceinline__ void f64_body(const SquareArgs& a, int I, int J, int 
     mma(qa, qb, false, 0, 0);
 
     // ------------------------------------------------------------------- epilogue
-    const double alpha = a.coef64 ? a.coef64[0] : (double)a.coef[0];
-    const double beta = a.coef64 ? a.coef64[1] : (double)a.coef[1];
-    const double gamma = a.coef64 ? a.coef64[2] : (double)a.coef[2];
+    if (!LEAD)
+        for (int i = 0; i < 3; ++i) cf.d[i] = a.coef64 ? a.coef64[i] : (double)a.coef[i];
+    const double alpha = cf.d[0], beta = cf.d[1], gamma = cf.d[2];
     double* so = (double*)a.s_out;
     const double* si = (const double*)a.s_in;
     const int ldo = a.ld_out, nv = a.n_valid;
@@ -245,7 +256,7 @@ __device__ __forceinline__ void f64_body(const SquareArgs& a, int I, int J, int 
             st_agent(a.parts + 2 * t, s0);
             st_agent(a.parts + 2 * t + 1, s1);
         }
-        tile_done<C::NT>(a, t, (double*)lds, s_done);
+        if (!LEAD) tile_done<C::NT>(a, t, (double*)lds, s_done);
     }
 }
 
@@ -295,6 +306,26 @@ __global__ __launch_bounds__(256) void k_square_f64_mix(SquareArgs a, int nmain)
     f64_body<32, 2, 2, 2>(a, i, j, slot, lds, red, &s_done);
 }
 
+// All of a small problem's 64-tiles as four 32-tiles each, with leading control: at these sizes
+// the chain of memory trips at a launch's end (sums stored, counted, read back, state written)
+// costs more (n = 256: 12.1 us per layer with the control in the last tile, 10.9 us
+// here).
+__global__ __launch_bounds__(256) void k_square_f64_lead(SquareArgs a, LeadArgs lead) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];   // lead_bytes
+    __shared__ __attribute__((aligned(16))) unsigned char lds[F64Sub::LDS];
+    __shared__ double red[2 * F64Sub::NW];
+    const int u = xcd_tile_index(blockIdx.x, (a.ntiles + 7) >> 3, a.ntiles);
+    if (u < 0) return;
+    int I, J;
+    tile_of(u >> 2, a.T, F64Main::STRIP, &I, &J);
+    const int i = 2 * I + ((u >> 1) & 1), j = 2 * J + (u & 1);
+    if (i > j) {   // below the diagonal: its mirror computes it
+        if (threadIdx.x < 2) a.parts[2 * u + threadIdx.x] = 0.0;
+        return;
+    }
+    f64_body<32, 2, 2, 2, true>(a, i, j, u, lds, red, nullptr, &lead, dyn);
+}
+
 // grouped: block b computes the 64-tile that the tile map names for it (see TileRef)
 __global__ __launch_bounds__(256) void k_square_f64_g(const SquareArgs* __restrict__ descs,
                                                       const TileRef* __restrict__ map, int per) {
@@ -329,6 +360,17 @@ hipError_t launch_square_f64_mix(const SquareArgs& a, hipStream_t s) {
     if (ntiles != a.ntiles || a.np % 64 || 64 * T > a.np) return hipErrorInvalidValue;
     const int nsub = ntiles - nmain;
     hipLaunchKernelGGL(k_square_f64_mix, dim3(nmain + (nsub + 7) / 8 * 8), dim3(256), 0, s, a, nmain);
+    return hipGetLastError();
+}
+
+bool square_f64_leads(int edge) {
+    int T, nmain, ntiles;
+    square_f64_mix_grid(edge, &T, &nmain, &ntiles);
+    return nmain == 0;
+}
+hipError_t launch_square_f64_lead(const SquareArgs& a, const LeadArgs& lead, hipStream_t s) {
+    if (!square_f64_leads(64 * a.T) || a.ntiles != 4 * ntiles_upper(a.T) || !a.parts) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_square_f64_lead, dim3((a.ntiles + 7) / 8 * 8), dim3(256), lead_bytes(lead), s, a, lead);
     return hipGetLastError();
 }
 

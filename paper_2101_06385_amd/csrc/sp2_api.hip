@@ -73,7 +73,7 @@ struct Plan {
     size_t off_sk_partial, off_sk_counter, total;
     bool fm;          // split layers by the fragment-major kernel (k_square_fm.h), variant fm_variant
     int fm_variant;
-    bool fm_lead;     // its control at the head of each launch (else by the last tile)
+    bool lead;        // control at the head of each layer's launch (else by the last tile, or launches)
 };
 
 // The persistent (whole rounds + split tail) schedule needs a tile of 128 or 256 in a
@@ -205,15 +205,15 @@ void make_plan(int n, const Opts& o, Plan* p) {
     p->sk_capable = sk_wanted(p->split, p->tile_main, kernel, p->np);
     p->fm = o.fm_ok && fm_wanted(p->split, p->tile_main, kernel, p->np) && !p->sk_capable;
     p->fm_variant = 0;
-    p->fm_lead = false;
+    p->lead = o.fm_ok && o.precision == SP2_FP64 && f64_mix_wanted(p->tile_main, kernel) && square_f64_leads(n);
     if (p->fm) {
         square_split_grid(64, p->np, &p->main_T, &p->main_tiles, &p->main_per);
         p->fm_variant = fm_variant(p->tile_main, ntiles_upper((n + 63) / 64));
-        p->fm_lead = p->fm_variant < 2;
+        p->lead = p->fm_variant < 2;
         // without leading control every launched tile is counted: only those that hold data
-        if (!p->fm_lead) square_split_grid(64, round_up(n, 64), &p->main_T, &p->main_tiles, &p->main_per);
+        if (!p->lead) square_split_grid(64, round_up(n, 64), &p->main_T, &p->main_tiles, &p->main_per);
     }
-    off = align_up(off + sizeof(double) * (p->fm ? 4 * p->main_tiles : 2 * p->main_tiles));   // fm: two buffers
+    off = align_up(off + sizeof(double) * (p->fm || p->lead ? 4 : 2) * p->main_tiles);   // fm, lead: two buffers
     p->off_gersh = off;
     off = align_up(off + sizeof(double) * 3 * p->gersh_blocks);
     p->off_dstats = off;
@@ -603,7 +603,7 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
             a.arrivals = p.main_tiles;
             a.host_flag = flag.dev;
         }
-        // fragment-major layers: layer k reads the sums that layer k - 1 left in buffer k mod 2 and
+        // leading control: layer k reads the sums that layer k - 1 left in buffer k mod 2 and
         // the hot block (k - 1) mod 2
         auto lead_of = [&](int layer) {
             LeadArgs l;
@@ -620,7 +620,7 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
         };
         FmArgs fm;
         memset(&fm, 0, sizeof(fm));
-        int fm_done = 0;   // fragment-major layers launched
+        int lead_done = 0;   // layers launched with leading control
         if (p.fm) {
             fm.pstride = fm_pstride(p.np);
             fm.sb = p.np / 32;
@@ -646,11 +646,11 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
                 }
             }
             if (p.fm) {
-                if (!p.fm_lead && layer == 1)
+                if (!p.lead && layer == 1)
                     SP2_TRY(launch_control_stride(st, init_parts, p.init_tiles, 3, layer, flag.dev, s));
                 if (layer > o.max_layers) break;
-                if (p.fm_lead) fm.lead = lead_of(layer);
-                fm_done = layer;
+                if (p.lead) fm.lead = lead_of(layer);
+                lead_done = layer;
                 const int in = (layer - 1) & 1, out = layer & 1;
                 fm.x0 = P[in][0];
                 fm.x1 = P[in][1];
@@ -658,16 +658,16 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
                 fm.p1_out = P[out][1];
                 fm.s_in = (const float*)S[in];
                 fm.s_out = (float*)S[out];
-                fm.parts_out = main_parts + (p.fm_lead ? (size_t)((layer + 1) & 1) * 2 * p.main_tiles : 0);
+                fm.parts_out = main_parts + (p.lead ? (size_t)((layer + 1) & 1) * 2 * p.main_tiles : 0);
                 ev.launched = layer;
                 SP2_TRY(ev.rec(ev.sq_b[layer], s));
                 SP2_TRY(launch_fm(o.precision, p.fm_variant, fm, s));
                 SP2_TRY(ev.rec(ev.sq_e[layer], s));
                 continue;
             }
-            if (layer == 1)
+            if (!p.lead && layer == 1)
                 SP2_TRY(launch_control_stride(st, init_parts, p.init_tiles, 3, layer, flag.dev, s));
-            else if (!fused)
+            else if (!p.lead && !fused)
                 SP2_TRY(launch_control_stride(st, main_parts, p.main_tiles, 2, layer, flag.dev, s));
             if (layer > o.max_layers) break;
             const int in = (layer - 1) & 1, out = layer & 1;
@@ -683,15 +683,19 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
                 SP2_TRY(launch_square_sk(o.precision, p.tile_main, sk_variant, a, sk, s));
             else if (p.split)
                 SP2_TRY(launch_split_tile_layer(o.precision, p.tile_main, p.kernel, a, s));
-            else if (o.precision == SP2_FP64)
+            else if (p.lead) {
+                a.parts = main_parts + (size_t)((layer + 1) & 1) * 2 * p.main_tiles;
+                lead_done = layer;
+                SP2_TRY(launch_square_f64_lead(a, lead_of(layer), s));
+            } else if (o.precision == SP2_FP64)
                 SP2_TRY(launch_f64_layer(p.tile_main, o.kernel, a, s));
             else
                 SP2_TRY(launch_square_plain(o.precision, p.tile_main, a, s));
             SP2_TRY(ev.rec(ev.sq_e[layer], s));
         }
         (void)waited;
-        if (p.fm_lead) {
-            LeadArgs lead = lead_of(fm_done + 1);
+        if (p.lead) {
+            LeadArgs lead = lead_of(lead_done + 1);
             lead.hot_out = hot_block(st, 0);
             SP2_TRY(launch_lead_finish(lead, s));
         }

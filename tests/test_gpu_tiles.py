@@ -136,3 +136,16 @@ def test_one_workgroup_solve_reports_bad_input():
         _, i = sp2.density(torch.from_numpy(x).to(DEV), w.n_occ)
         _, i1 = sp2.density(torch.from_numpy(x).to(DEV), w.n_occ, tile=64, kernel=1)
         assert i["status_name"] == i1["status_name"] == name
+
+
+# FP64 layers with the control at their head (every 64-tile cut: n <= 1408) and in their last tile
+@pytest.mark.parametrize("n", [65, 100, 257, 1408, 1409])
+def test_fp64_layers_equal_128_tile_layers(n):
+    w = wl.gapped(1200 + n, n, n // 2, device=DEV if n > 1000 else None)
+    h = torch.from_numpy(w.h).to(DEV)
+    for kw in (dict(refine=False, max_layers=3), dict(max_layers=6), dict(gap=(-0.9, 0.9), max_layers=5, refine=False)):
+        d, i = sp2.density(h, w.n_occ, precision="fp64", tile=128, **kw)
+        d4, i4 = sp2.density(h, w.n_occ, precision="fp64", tile=128, kernel=4, **kw)   # separate arrivals, 128-tiles
+        assert torch.equal(d, d4) and i["sigma"] == i4["sigma"] and i["layers"] == i4["layers"]
+        for a, b in zip(i["ns"] + i["nx"], i4["ns"] + i4["nx"]):
+            assert abs(a - b) <= 2 * (n * n + 1) * 2.0**-53 * n   # sums of n^2 terms of a matrix with norm <= sqrt(n)
