@@ -87,7 +87,9 @@ typedef struct {
                           32 x 32 ones.  0 is 5 at every size and tile (the tile then only
                           sets n_padded), and so are 2 / 3 / 4 on 64 tiles; every kernel but
                           1 gives the same bits.  The automatic choice also serves the FP64
-                          refinement layer of every mode; 6, 7 are invalid. */
+                          refinement layer of every mode; 6, 7 are invalid.  FP32 mode: 1 =
+                          register-staged kernel, every other value as FP64's 5; the bits
+                          are the same. */
     int accelerate;    /* nonzero: accelerated Deep-NN SP2 (Sec. Accelerated Deep-NN SP2).  With
                           the occupied eigenvalues of S_{n-1} known to lie in [h, 1] and the
                           unoccupied ones in [0, l] (from homo, lumo below and the spectral

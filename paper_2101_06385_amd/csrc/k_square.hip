@@ -476,18 +476,6 @@ __global__ __launch_bounds__(64 * WM * WN) void k_square_plain(SquareArgs a) {
     plain_body<E, BT, WM, WN>(a, t);
 }
 
-// Many problems in one launch: block b belongs to the problem p with offs[p] <= b <
-// offs[p + 1] and handles that problem's tile b - offs[p]; each problem brings its own
-// arguments (buffers, coefficients, skip flag).
-template <typename E, int BT, int WM, int WN>
-__global__ __launch_bounds__(64 * WM * WN) void k_square_plain_g(const SquareArgs* __restrict__ descs,
-                                                                 const int* __restrict__ offs, int nprob) {
-    const int p = find_group(offs, nprob, blockIdx.x);
-    const SquareArgs a = descs[p];
-    if (a.skip && *a.skip) return;
-    plain_body<E, BT, WM, WN>(a, blockIdx.x - offs[p]);
-}
-
 template <int BT>
 int grid_of(int np, int* T, int* ntiles, int* per) {
     *T = np / BT;
@@ -520,23 +508,6 @@ hipError_t launch_square_split(int precision, int tile, const SquareArgs& a, hip
         if (tile == 256) SP2_L(__bf16, 256, 2, 4);
         else if (tile == 128) SP2_L(__bf16, 128, 2, 2);
         else SP2_L(__bf16, 64, 2, 2);
-    } else {
-        return hipErrorInvalidValue;
-    }
-#undef SP2_L
-    return hipGetLastError();
-}
-
-hipError_t launch_square_plain_g(int precision, int tile, const SquareArgs* descs, const int* offs, int nprob,
-                                 int blocks, hipStream_t s) {
-#define SP2_L(E, BT, WM, WN) \
-    hipLaunchKernelGGL((k_square_plain_g<E, BT, WM, WN>), dim3(blocks), dim3(64 * WM * WN), 0, s, descs, offs, nprob)
-    if (precision == SP2_FP64) {
-        if (tile == 128) SP2_L(double, 128, 2, 2);
-        else SP2_L(double, 64, 2, 2);
-    } else if (precision == SP2_FP32) {
-        if (tile == 128) SP2_L(float, 128, 2, 2);
-        else SP2_L(float, 64, 2, 2);
     } else {
         return hipErrorInvalidValue;
     }

@@ -94,7 +94,6 @@ __device__ inline double wsum(double v) {
 // layer's control by the last tile.
 template <int BT, int WM, int WN, int ST, bool LEAD = false>
 __device__ __forceinline__ void f64_body(const SquareArgs& a, int I, int J, int t, unsigned char* __restrict__ lds,
-                                         double* __restrict__ red, int* __restrict__ s_done,
                                          const LeadArgs* lead = nullptr, unsigned char* __restrict__ dyn = nullptr) {
     typedef F64Cfg<BT, WM, WN, ST> C;
     constexpr int MB = C::MB, NB = C::NB, LPW = C::LPW;
@@ -106,7 +105,7 @@ __device__ __forceinline__ void f64_body(const SquareArgs& a, int I, int J, int 
     const double* x = (const double*)a.x0;
     const unsigned char* src[2] = {(const unsigned char*)(x + (size_t)I * BT * np),
                                    (const unsigned char*)(x + (size_t)J * BT * np)};
-    const int nsl = (a.n_real + kBK - 1) / kBK;   // X is zero beyond n_real
+    const int nsl = ((a.k_all ? np : a.n_real) + kBK - 1) / kBK;
 
     // direct load l of this wave: lane L fills bytes [16 L, 16 L + 16) of a 1 KB block:
     // panel row q * 8 + L / 8, physical chunk L % 8 = logical chunk (L % 8) ^ swz8(row)
@@ -240,13 +239,17 @@ __device__ __forceinline__ void f64_body(const SquareArgs& a, int I, int J, int 
         }
     }
     if (a.parts) {
+        // in the stages, which every wave has left: the LDS of a workgroup stays a fifth of a CU's
+        double* red = (double*)(lds + C::LDS - 256);
+        int* s_done = (int*)(lds + C::LDS - 64);
         tr = wsum(tr);
         fr = wsum(fr);
+        __syncthreads();
         if (lane == 0) {
             red[2 * wave] = tr;
             red[2 * wave + 1] = fr;
         }
-        __syncthreads();   // also: every wave has left the stages, whose LDS the control reuses
+        __syncthreads();
         if (tid == 0) {
             double s0 = 0.0, s1 = 0.0;
             for (int w = 0; w < C::NW; ++w) {
@@ -265,13 +268,11 @@ template <int BT, int WM, int WN, int ST>
 __global__ __launch_bounds__(64 * WM * WN) void k_square_f64(SquareArgs a) {
     typedef F64Cfg<BT, WM, WN, ST> C;
     __shared__ __attribute__((aligned(16))) unsigned char lds[C::LDS];
-    __shared__ double red[2 * C::NW];
-    __shared__ int s_done;
     const int t = xcd_tile_index(blockIdx.x, a.per, a.ntiles);
     if (t < 0) return;
     int I, J;
     tile_of(t, a.T, C::STRIP, &I, &J);
-    f64_body<BT, WM, WN, ST>(a, I, J, t, lds, red, &s_done);
+    f64_body<BT, WM, WN, ST>(a, I, J, t, lds);
 }
 
 // 64-tiles [0, nmain) whole (nmain a multiple of 8), the others as four 32-tiles each.
@@ -279,13 +280,11 @@ typedef F64Cfg<64, 2, 2, 2> F64Main;
 typedef F64Cfg<32, 2, 2, 2> F64Sub;
 __global__ __launch_bounds__(256) void k_square_f64_mix(SquareArgs a, int nmain) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[F64Main::LDS];
-    __shared__ double red[2 * F64Main::NW];
-    __shared__ int s_done;
     int I, J;
     if ((int)blockIdx.x < nmain) {
         const int t = (blockIdx.x & 7) * (nmain >> 3) + (blockIdx.x >> 3);
         tile_of(t, a.T, F64Main::STRIP, &I, &J);
-        f64_body<64, 2, 2, 2>(a, I, J, t, lds, red, &s_done);
+        f64_body<64, 2, 2, 2>(a, I, J, t, lds);
         return;
     }
     const int nsub = a.ntiles - nmain;
@@ -300,10 +299,10 @@ __global__ __launch_bounds__(256) void k_square_f64_mix(SquareArgs a, int nmain)
             st_agent(a.parts + 2 * slot, 0.0);
             st_agent(a.parts + 2 * slot + 1, 0.0);
         }
-        tile_done<256>(a, slot, (double*)lds, &s_done);
+        tile_done<256>(a, slot, (double*)lds, (int*)(lds + 4096));
         return;
     }
-    f64_body<32, 2, 2, 2>(a, i, j, slot, lds, red, &s_done);
+    f64_body<32, 2, 2, 2>(a, i, j, slot, lds);
 }
 
 // All of a small problem's 64-tiles as four 32-tiles each, with leading control: at these sizes
@@ -313,7 +312,6 @@ __global__ __launch_bounds__(256) void k_square_f64_mix(SquareArgs a, int nmain)
 __global__ __launch_bounds__(256) void k_square_f64_lead(SquareArgs a, LeadArgs lead) {
     extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];   // lead_bytes
     __shared__ __attribute__((aligned(16))) unsigned char lds[F64Sub::LDS];
-    __shared__ double red[2 * F64Sub::NW];
     const int u = xcd_tile_index(blockIdx.x, (a.ntiles + 7) >> 3, a.ntiles);
     if (u < 0) return;
     int I, J;
@@ -323,53 +321,51 @@ __global__ __launch_bounds__(256) void k_square_f64_lead(SquareArgs a, LeadArgs 
         if (threadIdx.x < 2) a.parts[2 * u + threadIdx.x] = 0.0;
         return;
     }
-    f64_body<32, 2, 2, 2, true>(a, i, j, u, lds, red, nullptr, &lead, dyn);
+    f64_body<32, 2, 2, 2, true>(a, i, j, u, lds, &lead, dyn);
 }
 
 // grouped: block b computes the 64-tile that the tile map names for it (see TileRef)
 __global__ __launch_bounds__(256) void k_square_f64_g(const SquareArgs* __restrict__ descs,
                                                       const TileRef* __restrict__ map, int per) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[F64Main::LDS];
-    __shared__ double red[2 * F64Main::NW];
-    __shared__ int s_done;
     const TileRef e = map[(blockIdx.x & 7) * per + (blockIdx.x >> 3)];
     if (e.problem < 0) return;
     const SquareArgs a = descs[e.problem];
     const int t = e.tile;
     int I, J;
     tile_of(t, a.T, F64Main::STRIP, &I, &J);
-    f64_body<64, 2, 2, 2>(a, I, J, t, lds, red, &s_done);
+    f64_body<64, 2, 2, 2>(a, I, J, t, lds);
 }
 
 }  // namespace
 
-// Grid of the mixed FP64 launch over `edge` rows: a.T 64-tiles per edge; the largest whole
+// Grid of the mixed FP64 and FP32 launches over `edge` rows: a.T 64-tiles per edge; the largest whole
 // number of 64-tiles per CU stays whole, the rest is cut.  (The CU count only shapes the
 // schedule: every choice gives the same bits.)
-constexpr int kF64Cus = 256;
-void square_f64_mix_grid(int edge, int* T, int* nmain, int* ntiles) {
+constexpr int kMixCus = 256;
+void square_mix_grid(int edge, int* T, int* nmain, int* ntiles) {
     *T = (edge + 63) / 64;
     const int nt = ntiles_upper(*T);
-    *nmain = nt / kF64Cus * kF64Cus;
+    *nmain = nt / kMixCus * kMixCus;
     *ntiles = *nmain + 4 * (nt - *nmain);
 }
 
 hipError_t launch_square_f64_mix(const SquareArgs& a, hipStream_t s) {
     int T, nmain, ntiles;
-    square_f64_mix_grid(64 * a.T, &T, &nmain, &ntiles);
+    square_mix_grid(64 * a.T, &T, &nmain, &ntiles);
     if (ntiles != a.ntiles || a.np % 64 || 64 * T > a.np) return hipErrorInvalidValue;
     const int nsub = ntiles - nmain;
     hipLaunchKernelGGL(k_square_f64_mix, dim3(nmain + (nsub + 7) / 8 * 8), dim3(256), 0, s, a, nmain);
     return hipGetLastError();
 }
 
-bool square_f64_leads(int edge) {
+bool square_leads(int edge) {
     int T, nmain, ntiles;
-    square_f64_mix_grid(edge, &T, &nmain, &ntiles);
+    square_mix_grid(edge, &T, &nmain, &ntiles);
     return nmain == 0;
 }
 hipError_t launch_square_f64_lead(const SquareArgs& a, const LeadArgs& lead, hipStream_t s) {
-    if (!square_f64_leads(64 * a.T) || a.ntiles != 4 * ntiles_upper(a.T) || !a.parts) return hipErrorInvalidValue;
+    if (!square_leads(64 * a.T) || a.ntiles != 4 * ntiles_upper(a.T) || !a.parts) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_square_f64_lead, dim3((a.ntiles + 7) / 8 * 8), dim3(256), lead_bytes(lead), s, a, lead);
     return hipGetLastError();
 }

@@ -124,21 +124,25 @@ hipError_t launch_split_tile_layer(int precision, int tile, int kernel, const Sq
     return launch_square_split(precision, tile, a, s);
 }
 
-// FP64 layer: kernel 0 (automatic) and 5 = 64-tiles with the leftover ones cut into 32-tiles;
-// 2 / 3 / 4 = per-tile variants 0 / 1 / 2 on 128 tiles (on 64 tiles as 0); 1 = the
-// register-staged kernel.
-bool f64_mix_wanted(int tile, int kernel) { return !(kernel == 1 || (tile == 128 && kernel >= 2 && kernel <= 4)); }
-hipError_t launch_f64_layer(int tile, int kernel, const SquareArgs& a, hipStream_t s) {
-    if (f64_mix_wanted(tile, kernel)) return launch_square_f64_mix(a, s);
-    if (kernel >= 2) return launch_square_f64(kernel - 2, a, s);
-    return launch_square_plain(SP2_FP64, tile, a, s);
+// FP64 and FP32 layers: kernel 1 = the register-staged kernel; FP64 kernels 2 / 3 / 4 on 128
+// tiles = per-tile variants 0 / 1 / 2; all else = 64-tiles with the leftover ones cut into
+// 32-tiles.
+bool mix_wanted(int precision, int tile, int kernel) {
+    if (precision != SP2_FP64 && precision != SP2_FP32) return false;
+    return !(kernel == 1 || (precision == SP2_FP64 && tile == 128 && kernel >= 2 && kernel <= 4));
+}
+hipError_t launch_plain_layer(int precision, int tile, int kernel, const SquareArgs& a, hipStream_t s) {
+    if (mix_wanted(precision, tile, kernel))
+        return precision == SP2_FP64 ? launch_square_f64_mix(a, s) : launch_square_f32_mix(a, s);
+    if (precision == SP2_FP64 && kernel >= 2) return launch_square_f64(kernel - 2, a, s);
+    return launch_square_plain(precision, tile, a, s);
 }
 
-// Tiles of an FP64 layer over `edge` rows in the layout of launch_f64_layer.
-void f64_layer_grid(int tile, int kernel, int np, int edge, int* T, int* ntiles, int* per) {
+// Tiles of an FP64 or FP32 layer over `edge` rows in the layout of launch_plain_layer.
+void plain_layer_grid(int precision, int tile, int kernel, int np, int edge, int* T, int* ntiles, int* per) {
     int nmain = 0;
-    if (f64_mix_wanted(tile, kernel)) {
-        square_f64_mix_grid(edge, T, &nmain, ntiles);
+    if (mix_wanted(precision, tile, kernel)) {
+        square_mix_grid(edge, T, &nmain, ntiles);
         *per = 0;
     } else {
         square_plain_grid(tile, np, T, ntiles, per);
@@ -189,11 +193,9 @@ void make_plan(int n, const Opts& o, Plan* p) {
     p->init_tiles = init_tiles(p->np);
     if (p->split)
         square_split_grid(p->tile_main, p->np, &p->main_T, &p->main_tiles, &p->main_per);
-    else if (o.precision == SP2_FP64)
-        f64_layer_grid(p->tile_main, kernel, p->np, n, &p->main_T, &p->main_tiles, &p->main_per);
     else
-        square_plain_grid(p->tile_main, p->np, &p->main_T, &p->main_tiles, &p->main_per);
-    f64_layer_grid(p->tile_ref, o.precision == SP2_FP64 ? kernel : 0, p->np, n, &p->ref_T, &p->ref_tiles, &p->ref_per);
+        plain_layer_grid(o.precision, p->tile_main, kernel, p->np, n, &p->main_T, &p->main_tiles, &p->main_per);
+    plain_layer_grid(SP2_FP64, p->tile_ref, o.precision == SP2_FP64 ? kernel : 0, p->np, n, &p->ref_T, &p->ref_tiles, &p->ref_per);
     p->gersh_blocks = gershgorin_blocks(n);
     p->dstats_blocks = dstats_blocks(n);
     const size_t np2 = (size_t)p->np * p->np;
@@ -205,7 +207,7 @@ void make_plan(int n, const Opts& o, Plan* p) {
     p->sk_capable = sk_wanted(p->split, p->tile_main, kernel, p->np);
     p->fm = o.fm_ok && fm_wanted(p->split, p->tile_main, kernel, p->np) && !p->sk_capable;
     p->fm_variant = 0;
-    p->lead = o.fm_ok && o.precision == SP2_FP64 && f64_mix_wanted(p->tile_main, kernel) && square_f64_leads(n);
+    p->lead = o.fm_ok && mix_wanted(o.precision, p->tile_main, kernel) && square_leads(n);
     if (p->fm) {
         square_split_grid(64, p->np, &p->main_T, &p->main_tiles, &p->main_per);
         p->fm_variant = fm_variant(p->tile_main, ntiles_upper((n + 63) / 64));
@@ -596,8 +598,8 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
         // enqueue every layer up to max_layers (later ones return at once).
         const int chunk = n >= 1024 ? 2 : 4;
         ChunkEvents cev;
-        // every split and FP64 kernel but the register-staged ones runs the next layer's control itself
-        const bool fused = (p.split && p.kernel != kKernelLegacyTile) || (o.precision == SP2_FP64 && o.kernel != 1);
+        // every kernel but the register-staged ones runs the next layer's control itself
+        const bool fused = p.split ? p.kernel != kKernelLegacyTile : p.kernel != 1;
         if (fused) {
             a.ctl = st;
             a.arrivals = p.main_tiles;
@@ -686,11 +688,10 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
             else if (p.lead) {
                 a.parts = main_parts + (size_t)((layer + 1) & 1) * 2 * p.main_tiles;
                 lead_done = layer;
-                SP2_TRY(launch_square_f64_lead(a, lead_of(layer), s));
-            } else if (o.precision == SP2_FP64)
-                SP2_TRY(launch_f64_layer(p.tile_main, o.kernel, a, s));
-            else
-                SP2_TRY(launch_square_plain(o.precision, p.tile_main, a, s));
+                if (o.precision == SP2_FP64) SP2_TRY(launch_square_f64_lead(a, lead_of(layer), s));
+                else SP2_TRY(launch_square_f32_lead(a, lead_of(layer), s));
+            } else
+                SP2_TRY(launch_plain_layer(o.precision, p.tile_main, p.kernel, a, s));
             SP2_TRY(ev.rec(ev.sq_e[layer], s));
         }
         (void)waited;
@@ -721,7 +722,7 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
             r.n_valid = p.np;
             r.n_real = n;
             r.coef = st->rcoef[0];
-            SP2_TRY(launch_f64_layer(p.tile_ref, o.precision == SP2_FP64 ? o.kernel : 0, r, s));
+            SP2_TRY(launch_plain_layer(SP2_FP64, p.tile_ref, o.precision == SP2_FP64 ? o.kernel : 0, r, s));
             SP2_TRY(ev.rec(ev.ref[1], s));
             r.x0 = y;
             r.s_in = y;
@@ -729,7 +730,7 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
             r.ld_out = ldd;
             r.n_valid = n;
             r.coef = st->rcoef[1];
-            SP2_TRY(launch_f64_layer(p.tile_ref, o.precision == SP2_FP64 ? o.kernel : 0, r, s));
+            SP2_TRY(launch_plain_layer(SP2_FP64, p.tile_ref, o.precision == SP2_FP64 ? o.kernel : 0, r, s));
             SP2_TRY(ev.rec(ev.ref[2], s));
         } else {
             if (p.fm)
@@ -939,10 +940,8 @@ int sp2_fermi_apply(const double* dH, int ldh, double* dD, int ldd, int n, int l
             SP2_TRY(launch_square_sk(o.precision, p.tile_main, sk_variant, a, sk, s));
         else if (p.split)
             SP2_TRY(launch_split_tile_layer(o.precision, p.tile_main, p.kernel, a, s));
-        else if (o.precision == SP2_FP64)
-            SP2_TRY(launch_f64_layer(p.tile_main, o.kernel, a, s));
         else
-            SP2_TRY(launch_square_plain(o.precision, p.tile_main, a, s));
+            SP2_TRY(launch_plain_layer(o.precision, p.tile_main, p.kernel, a, s));
         SP2_TRY(launch_readout(o.precision, acc, S[out], p.np, -c[k + 1], 0.0, 0, s));
     }
     SP2_TRY(launch_copy_out(acc, p.np, dD, ldd, n, s));
@@ -1023,8 +1022,7 @@ size_t sp2_square_workspace_size(int n, int precision, int tile, int kernel) {
     const int t = tile ? tile : auto_tile_main(n, split);
     int T, nt, per;
     if (split) square_split_grid(t, np, &T, &nt, &per);
-    else if (precision == SP2_FP64) f64_layer_grid(t, kernel, np, np, &T, &nt, &per);
-    else square_plain_grid(t, np, &T, &nt, &per);
+    else plain_layer_grid(precision, t, kernel, np, np, &T, &nt, &per);
     size_t off = kAlign;                               // coefficients
     off = align_up(off + sizeof(double) * 2 * nt);     // partials
     off = align_up(off + sizeof(double) * 2);          // sums
@@ -1053,10 +1051,11 @@ int sp2_square(const void* dX, void* dY, int n, int precision, int tile, int ker
     if (work_bytes < sp2_square_workspace_size(n, precision, tile, kernel)) return SP2_ENOMEM;
     hipStream_t s = (hipStream_t)stream;
     char* ws = (char*)dWork;
+    // the direct loads of the mixed-tile kernels take whole 16-byte chunks
+    if (((uintptr_t)dX) % 16 && mix_wanted(precision, t, kernel)) kernel = 1;
     int T, nt, per;
     if (split) square_split_grid(t, np, &T, &nt, &per);
-    else if (precision == SP2_FP64) f64_layer_grid(t, kernel, np, np, &T, &nt, &per);
-    else square_plain_grid(t, np, &T, &nt, &per);
+    else plain_layer_grid(precision, t, kernel, np, np, &T, &nt, &per);
     float* coef = (float*)ws;
     double* parts = (double*)(ws + kAlign);
     size_t off = align_up(kAlign + sizeof(double) * 2 * nt);
@@ -1103,12 +1102,10 @@ int sp2_square(const void* dX, void* dY, int n, int precision, int tile, int ker
         } else {
             SP2_TRY(launch_split_tile_layer(precision, t, kernel, a, s));
         }
-    } else if (precision == SP2_FP64) {
-        a.x0 = dX;
-        SP2_TRY(launch_f64_layer(t, kernel, a, s));
     } else {
         a.x0 = dX;
-        SP2_TRY(launch_square_plain(precision, t, a, s));
+        a.k_all = 1;   // the caller's padding is not known to be zero
+        SP2_TRY(launch_plain_layer(precision, t, kernel, a, s));
     }
     if (trace_frob) {
         SP2_TRY(launch_sum_parts(parts, nt, sums, s));
@@ -1133,10 +1130,10 @@ struct BatchLayout {
     std::vector<size_t> region;         // byte offset of each problem's region
     size_t off_probs, off_sq, off_offs, off_map, off_ref_map, off_stage, total;
     int n_offs;                         // stride of the offset arrays (batch + 1)
-    size_t map_size, ref_map_size;      // capacity of the tile maps (split squaring, FP64 refinement)
+    size_t map_size, ref_map_size;      // capacity of the tile maps (squaring, FP64 refinement)
 };
 
-// Tile map of the grouped launches (split squaring, FP64 refinement): every tile of the
+// Tile map of the grouped launches (squaring, FP64 refinement): every tile of the
 // problems listed, tiles_of(problem) of them.  Each problem's tiles are cut into kMapParts
 // contiguous runs of the strip order, each run on one XCD (so that the tiles of a run share
 // its L2); problems go largest first, and each run to the XCD with the least work so far (a
@@ -1198,8 +1195,10 @@ bool batch_layout(int batch, const int* n, const int* n_occ, const Opts& o, Batc
         Opts oi = o;
         oi.tile = L->tile;
         oi.tile_ref = L->tile;   // one refinement tile for every problem of the grouped launch
-        oi.kernel = 1;           // one workgroup per tile: grouped launches
+        // one workgroup per tile: grouped launches (FP32: of whole 64-tiles)
+        oi.kernel = o.precision == SP2_FP32 ? 0 : 1;
         make_plan(n[i], oi, &L->plans[i]);
+        if (o.precision == SP2_FP32) L->plans[i].main_tiles = ntiles_upper(L->plans[i].main_T);
         if (n_occ && n_occ[i] > 0 && n_occ[i] < n[i]) L->nontrivial.push_back(i);
     }
     // descriptor areas are sized for every problem, so the size does not depend on n_occ
@@ -1216,7 +1215,6 @@ bool batch_layout(int batch, const int* n, const int* n_occ, const Opts& o, Batc
         L->map_size += 8 * (size_t)L->plans[i].main_tiles;
         L->ref_map_size += 8 * (size_t)ref_tiles64(L->plans[i]);
     }
-    if (!L->plans[0].split) L->map_size = 0;
     L->off_map = off;
     off = align_up(off + sizeof(TileRef) * L->map_size);
     L->off_ref_map = off;
@@ -1394,7 +1392,7 @@ static int run_batched(int batch, const double* const* dH, const int* ldh, doubl
                 a.p0_out = q.pl[out][0];
                 a.p1_out = q.pl[out][1];
                 a.parts = q.main_parts;
-                a.ctl = p.split ? r : nullptr;
+                a.ctl = r;
                 a.arrivals = p.main_tiles;
                     a.coef = ((DevState*)r)->coef;
                 a.skip = &((DevState*)r)->skip;
@@ -1434,12 +1432,10 @@ static int run_batched(int batch, const double* const* dH, const int* ldh, doubl
         SP2_TRY(hipMemcpy(d_probs, probs.data(), sizeof(BatchProblem) * nt, hipMemcpyHostToDevice));
         SP2_TRY(hipMemcpy(ws + L.off_sq, sq.data(), sizeof(SquareArgs) * 4 * nt, hipMemcpyHostToDevice));
         std::vector<TileRef> map, ref_map;
-        int map_per = 0;
-        if (L.map_size) map_per = build_tile_map(L.plans, L.nontrivial, main_tiles_of, &map);
+        const int map_per = build_tile_map(L.plans, L.nontrivial, main_tiles_of, &map);
         const int ref_per = build_tile_map(L.plans, L.nontrivial, ref_tiles64, &ref_map);
         if (map.size() > L.map_size || ref_map.size() > L.ref_map_size) return SP2_EINVAL;
-        if (!map.empty())
-            SP2_TRY(hipMemcpy(ws + L.off_map, map.data(), sizeof(TileRef) * map.size(), hipMemcpyHostToDevice));
+        SP2_TRY(hipMemcpy(ws + L.off_map, map.data(), sizeof(TileRef) * map.size(), hipMemcpyHostToDevice));
         SP2_TRY(hipMemcpy(ws + L.off_ref_map, ref_map.data(), sizeof(TileRef) * ref_map.size(), hipMemcpyHostToDevice));
         const TileRef* d_map = (const TileRef*)(ws + L.off_map);
         const TileRef* d_ref_map = (const TileRef*)(ws + L.off_ref_map);
@@ -1464,12 +1460,11 @@ static int run_batched(int batch, const double* const* dH, const int* ldh, doubl
         const int la = o.max_layers < kBatchLayersA ? o.max_layers : kBatchLayersA;
         auto layers = [&](hipStream_t s, int l0, int l1) -> int {
             for (int layer = l0; layer <= l1; ++layer) {
-                // the split layers run the next layer's control themselves
-                if (layer == 1 || o.precision == SP2_FP32) SP2_TRY(launch_batch_control(d_probs, nt, layer, s));
+                if (layer == 1) SP2_TRY(launch_batch_control(d_probs, nt, layer, s));
                 if (layer > o.max_layers) break;
                 const SquareArgs* a = d_sq + ((layer - 1) & 1) * nt;
                 if (o.precision == SP2_FP32)
-                    SP2_TRY(launch_square_plain_g(SP2_FP32, L.tile, a, d_om, nt, o_m[nt], s));
+                    SP2_TRY(launch_square_f32_g(a, d_map, map_per, s));
                 else
                     SP2_TRY(launch_square_dp_g(o.precision, L.tile, 0, a, d_map, map_per, s));
             }

@@ -24,6 +24,7 @@ struct SquareArgs {
     int ld_out;           // leading dimension of s_out
     int n_valid;          // rows/cols >= n_valid of s_out are not written
     int n_real;           // logical edge: the gamma I term stops here so the padding stays zero
+    int k_all;            // FP64 / FP32: nonzero = products over all np columns, 0 = X is zero beyond n_real
     int T;                // tiles per edge
     int ntiles;           // T (T + 1) / 2
     int per;              // ceil(ntiles / 8)

@@ -233,16 +233,18 @@ hipError_t launch_square_plain(int precision, int tile, const SquareArgs& a, hip
 // FP64 layer with direct-to-LDS staging, 128 tiles (k_square_f64.hip); variants 0..2
 hipError_t launch_square_f64(int variant, const SquareArgs& a, hipStream_t s);
 // FP64 layer on 64-tiles with the leftover ones cut into 32-tiles: a.T, a.ntiles from
-// square_f64_mix_grid over the rows to compute
-void square_f64_mix_grid(int edge, int* T, int* nmain, int* ntiles);
+// square_mix_grid over the rows to compute
+void square_mix_grid(int edge, int* T, int* nmain, int* ntiles);
 hipError_t launch_square_f64_mix(const SquareArgs& a, hipStream_t s);
 // the same with leading control, where every 64-tile is cut (a.parts: not the buffer that `lead` reads)
-bool square_f64_leads(int edge);
+bool square_leads(int edge);
 hipError_t launch_square_f64_lead(const SquareArgs& a, const LeadArgs& lead, hipStream_t s);
 // grouped FP64 layer over a map of 64-tiles (see TileRef), grid 8 per
 hipError_t launch_square_f64_g(const SquareArgs* descs, const TileRef* map, int per, hipStream_t s);
-hipError_t launch_square_plain_g(int precision, int tile, const SquareArgs* descs, const int* offs, int nprob,
-                                 int blocks, hipStream_t s);
+// FP32 layers with direct-to-LDS staging (k_square_f32.hip), tiles as the FP64 ones
+hipError_t launch_square_f32_mix(const SquareArgs& a, hipStream_t s);
+hipError_t launch_square_f32_lead(const SquareArgs& a, const LeadArgs& lead, hipStream_t s);
+hipError_t launch_square_f32_g(const SquareArgs* descs, const TileRef* map, int per, hipStream_t s);
 int square_split_grid(int tile, int np, int* T, int* ntiles, int* per);
 int square_plain_grid(int tile, int np, int* T, int* ntiles, int* per);
 // persistent split square: kSkVariants kernel variants per tile edge (128, 256)

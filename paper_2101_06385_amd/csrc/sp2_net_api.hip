@@ -45,10 +45,11 @@ bool net_plan(int n, int K, int precision, int ckpt_every, NetPlan* p) {
     p->tile_adj = adjoint_tile(p->adj_variant);
     const int m = p->tile_main > p->tile_adj ? p->tile_main : p->tile_adj;
     p->np = round_up(n, m);
+    int nmain = 0;
     if (p->split)
         square_split_grid(p->tile_main, p->np, &p->T_main, &p->nt_main, &p->per_main);
-    else
-        square_plain_grid(p->tile_main, p->np, &p->T_main, &p->nt_main, &p->per_main);
+    else   // over the padding too: the adjoint reads it as zeros
+        square_mix_grid(p->np, &p->T_main, &nmain, &p->nt_main);
     adjoint_grid(p->tile_adj, p->np, &p->T_adj, &p->nt_adj, &p->per_adj);
     const size_t m2 = (size_t)p->np * p->np * sizeof(float);
     if (ckpt_every) p->c = ckpt_every;
@@ -143,8 +144,7 @@ hipError_t layer(const NetPlan& p, const NetBuffers& b, int k, const float* x_in
     a.in_scale = ldexpf(1.f, p.scale_log2);
     // one workgroup per 128 tile with 64-half K-slices (the single-problem choice)
     if (p.split && p.tile_main == 128) return launch_square_dp(p.precision, 128, 3, a, s);
-    return p.split ? launch_square_split(p.precision, p.tile_main, a, s)
-                   : launch_square_plain(p.precision, p.tile_main, a, s);
+    return p.split ? launch_square_split(p.precision, p.tile_main, a, s) : launch_square_f32_mix(a, s);
 }
 
 }  // namespace

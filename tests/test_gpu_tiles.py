@@ -149,3 +149,39 @@ def test_fp64_layers_equal_128_tile_layers(n):
         assert torch.equal(d, d4) and i["sigma"] == i4["sigma"] and i["layers"] == i4["layers"]
         for a, b in zip(i["ns"] + i["nx"], i4["ns"] + i4["nx"]):
             assert abs(a - b) <= 2 * (n * n + 1) * 2.0**-53 * n   # sums of n^2 terms of a matrix with norm <= sqrt(n)
+
+
+# FP32 layers: with the control at their head (n <= 1408) or in their last tile (1409, 1472: whole
+# 64-tiles and cut ones) against the register-staged kernel with control launches
+@pytest.mark.parametrize("n", [65, 100, 257, 1408, 1409, 1472])
+def test_fp32_layers_equal_register_staged_layers(n):
+    w = wl.gapped(1300 + n, n, n // 2, device=DEV if n > 1000 else None)
+    h = torch.from_numpy(w.h).to(DEV)
+    for kw in (dict(max_layers=3), dict(max_layers=6), dict(gap=(-0.9, 0.9), max_layers=5)):
+        d, i = sp2.density(h, w.n_occ, precision="fp32", refine=False, **kw)
+        d1, i1 = sp2.density(h, w.n_occ, precision="fp32", refine=False, kernel=1, **kw)
+        assert torch.equal(d, d1) and i["sigma"] == i1["sigma"] and i["layers"] == i1["layers"]
+        for a, b in zip(i["ns"] + i["nx"], i1["ns"] + i1["nx"]):
+            assert abs(a - b) <= 2 * (n * n + 1) * 2.0**-53 * n   # sums of n^2 terms of a matrix with norm <= sqrt(n)
+
+
+@pytest.mark.parametrize("n", [1, 31, 33, 65, 129, 700, 1472])
+def test_fp32_mixed_tiles_equal_register_staged_kernel(n):
+    x = _sym(n, 1400 + n, torch.float32)
+    y, s = sp2.square(x, -1.0, 2.0, 0.5, precision="fp32")
+    y1, s1 = sp2.square(x, -1.0, 2.0, 0.5, precision="fp32", kernel=1)
+    assert torch.equal(y, y1) and torch.equal(y, y.T)
+    assert abs(s[1] - s1[1]) <= 2 * (n * n + 1) * 2.0**-53 * s1[1]
+    buf = torch.empty(n * n + 1, device=DEV)   # rows that are not 16-byte aligned
+    z = torch.as_strided(buf, (n, n), (n, 1), 1).copy_(x)
+    assert torch.equal(sp2.square(z, -1.0, 2.0, 0.5, precision="fp32")[0], y)
+
+
+def test_fp32_batch_equals_single_calls():
+    ns = (5, 64, 65, 130, 300, 1472)
+    ws = [wl.gapped(1500 + n, n, n // 2, device=DEV if n > 1000 else None) for n in ns]
+    hs = [torch.from_numpy(w.h).to(DEV) for w in ws]
+    ds, infos = sp2.density_batched(hs, [w.n_occ for w in ws], precision="fp32")
+    for h, w, d, i in zip(hs, ws, ds, infos):
+        d1, i1 = sp2.density(h, w.n_occ, precision="fp32", kernel=1)
+        assert torch.equal(d, d1) and i["sigma"] == i1["sigma"]
