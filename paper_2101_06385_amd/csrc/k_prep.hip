@@ -367,37 +367,86 @@ __global__ void k_zero_ints(int* p, int count) {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += gridDim.x * blockDim.x) p[i] = 0;
 }
 
-// Finite-temperature read-out D = (1 - c_0) I + c_0 S_0 - sum_{k>=1} c_k X_k accumulated in
-// FP64 over the padded matrix: first = 1 sets acc = a X + diag I, otherwise acc += a X.
-// Two elements per thread and iteration (n_p is a multiple of 64).
-template <typename St>
-__global__ __launch_bounds__(kThreads) void k_readout(double* __restrict__ acc, const St* __restrict__ x, int np,
-                                                      double a, double diag, int first) {
-    const size_t total = (size_t)np * np / 2;
-    for (size_t q = (size_t)blockIdx.x * kThreads + threadIdx.x; q < total; q += (size_t)gridDim.x * kThreads) {
-        const size_t idx = 2 * q;
-        const int i = (int)(idx / np), j = (int)(idx % np);
-        double v0 = a * (double)x[idx], v1 = a * (double)x[idx + 1];
-        if (first) {
-            if (i == j) v0 += diag;
-            if (i == j + 1) v1 += diag;
-            acc[idx] = v0;
-            acc[idx + 1] = v1;
+// Finite-temperature read-out D = (1 - c_0) I + c_0 S_0 - sum_{k>=1} c_k X_k, R matrices at a
+// time into D in FP64: first = D starts as a_0 X_0 + diag I, otherwise the sum goes on from D;
+// one term after the other for each element, so R changes no bit.  A pass with parts also
+// takes the sums of D that k_dstats takes.  The blocks go through the matrices side by side
+// (rows apart, one wavefront per row, a pass took 776 us at n = 8192).
+//  * Bound: HBM.  n = 8192 with 12 terms: two passes of six (each X read once, D written twice
+//    and read once) and the sums 1.19 ms (4.5 TB/s), against 3.46 ms with one pass per term into a
+//    padded accumulator, a copy of it into D and a separate pass for the sums.
+struct ReadoutArgs {
+    const void* x[kReadoutMax];
+    double a[kReadoutMax];
+    double diag;
+    double* d;
+    const double* h;   // with parts: Tr[D H] too, or null
+    double* parts;     // or null
+    int ldd, ldh, n, np, first;
+    int vec;   // rows of D and H start on 16 bytes
+};
+typedef double f64v2 __attribute__((ext_vector_type(2)));
+template <typename St, int R>
+__global__ __launch_bounds__(kThreads) void k_readout(ReadoutArgs q) {
+    typedef St StV __attribute__((ext_vector_type(16 / sizeof(St))));
+    constexpr int V = 16 / sizeof(St);
+    __shared__ double sh[3 * kThreads];
+    const int per_row = (q.n + V * kThreads - 1) / (V * kThreads);
+    const long long units = (long long)q.n * per_row;
+    double v[3] = {0.0, 0.0, 0.0};
+    for (long long unit = blockIdx.x; unit < units; unit += gridDim.x) {
+        const int i = (int)(unit / per_row), j0 = ((int)(unit % per_row) * kThreads + (int)threadIdx.x) * V;
+        if (j0 >= q.n) continue;
+        double* dr = q.d + (size_t)i * q.ldd + j0;
+        const double* hr = q.parts && q.h ? q.h + (size_t)i * q.ldh + j0 : nullptr;
+        StV x[R];
+        double d[V], e[V];
+#pragma unroll
+        for (int r = 0; r < R; ++r) x[r] = *(const StV*)((const St*)q.x[r] + (size_t)i * q.np + j0);
+        const bool whole = j0 + V <= q.n;
+        if (whole && q.vec) {
+#pragma unroll
+            for (int u = 0; u < V; u += 2) {
+                const f64v2 t = q.first ? f64v2{0.0, 0.0} : *(const f64v2*)(dr + u);
+                const f64v2 w = hr ? *(const f64v2*)(hr + u) : f64v2{0.0, 0.0};
+                d[u] = t[0];
+                d[u + 1] = t[1];
+                e[u] = w[0];
+                e[u + 1] = w[1];
+            }
         } else {
-            acc[idx] += v0;
-            acc[idx + 1] += v1;
+#pragma unroll
+            for (int u = 0; u < V; ++u) {
+                d[u] = j0 + u < q.n && !q.first ? dr[u] : 0.0;
+                e[u] = j0 + u < q.n && hr ? hr[u] : 0.0;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+            const bool diag = i == j0 + u;
+            double y = q.first ? q.a[0] * (double)x[0][u] + (diag ? q.diag : 0.0) : d[u] + q.a[0] * (double)x[0][u];
+#pragma unroll
+            for (int r = 1; r < R; ++r) y += q.a[r] * (double)x[r][u];
+            d[u] = y;
+            if (j0 + u < q.n) {
+                if (diag) v[0] += y;
+                v[1] += y * y;
+                if (hr) v[2] += y * e[u];
+            }
+        }
+        if (whole && q.vec) {
+#pragma unroll
+            for (int u = 0; u < V; u += 2) *(f64v2*)(dr + u) = f64v2{d[u], d[u + 1]};
+        } else {
+#pragma unroll
+            for (int u = 0; u < V; ++u)
+                if (j0 + u < q.n) dr[u] = d[u];
         }
     }
-}
-
-// n x n leading block of the padded accumulator into D (leading dimension ldd)
-__global__ __launch_bounds__(kThreads) void k_copy_out(const double* __restrict__ acc, int np,
-                                                       double* __restrict__ d, int ldd, int n) {
-    const size_t total = (size_t)n * n;
-    for (size_t idx = (size_t)blockIdx.x * kThreads + threadIdx.x; idx < total; idx += (size_t)gridDim.x * kThreads) {
-        const int i = (int)(idx / n), j = (int)(idx % n);
-        d[(size_t)i * ldd + j] = acc[(size_t)i * np + j];
-    }
+    if (!q.parts) return;
+    block_sum<3>(v, sh);
+    if (threadIdx.x == 0)
+        for (int c = 0; c < 3; ++c) q.parts[3 * blockIdx.x + c] = v[c];
 }
 
 // Up to kMaxCoefs floats passed by value into device memory (kernel arguments are part of
@@ -738,23 +787,39 @@ hipError_t launch_set3(float* dst, float a, float b, float c, hipStream_t s) {
     hipLaunchKernelGGL(k_set3, dim3(1), dim3(64), 0, s, dst, a, b, c);
     return hipGetLastError();
 }
-hipError_t launch_readout(int precision, double* acc, const void* x, int np, double a, double diag, int first,
-                          hipStream_t s) {
-    const size_t pairs = (size_t)np * np / 2;
-    size_t g = (pairs + kThreads - 1) / kThreads;
-    if (g > 4096) g = 4096;
-    if (precision == SP2_FP64)
-        hipLaunchKernelGGL(k_readout<double>, dim3((unsigned)g), dim3(kThreads), 0, s, acc, (const double*)x, np, a,
-                           diag, first);
-    else
-        hipLaunchKernelGGL(k_readout<float>, dim3((unsigned)g), dim3(kThreads), 0, s, acc, (const float*)x, np, a,
-                           diag, first);
-    return hipGetLastError();
-}
-hipError_t launch_copy_out(const double* acc, int np, double* d, int ldd, int n, hipStream_t s) {
-    size_t g = ((size_t)n * n + kThreads - 1) / kThreads;
-    if (g > 4096) g = 4096;
-    hipLaunchKernelGGL(k_copy_out, dim3((unsigned)g), dim3(kThreads), 0, s, acc, np, d, ldd, n);
+hipError_t launch_readout(int precision, const void* const* x, const double* a, int count, int first, double diag,
+                          int np, double* d, int ldd, int n, const double* h, int ldh, double* parts, hipStream_t s) {
+    if (count < 1 || count > kReadoutMax) return hipErrorInvalidValue;
+    ReadoutArgs q;
+    for (int r = 0; r < kReadoutMax; ++r) {
+        q.x[r] = r < count ? x[r] : nullptr;
+        q.a[r] = r < count ? a[r] : 0.0;
+    }
+    q.diag = diag;
+    q.d = d;
+    q.h = h;
+    q.parts = parts;
+    q.ldd = ldd;
+    q.ldh = ldh;
+    q.n = n;
+    q.np = np;
+    q.first = first;
+    q.vec = (uintptr_t)d % 16 == 0 && ldd % 2 == 0 && (!parts || !h || ((uintptr_t)h % 16 == 0 && ldh % 2 == 0));
+#define SP2_L(R)                                                                                                \
+    if (precision == SP2_FP64)                                                                                  \
+        hipLaunchKernelGGL((k_readout<double, R>), dim3(dstats_blocks(n)), dim3(kThreads), 0, s, q);            \
+    else                                                                                                        \
+        hipLaunchKernelGGL((k_readout<float, R>), dim3(dstats_blocks(n)), dim3(kThreads), 0, s, q);             \
+    break;
+    switch (count) {
+        case 1: SP2_L(1)
+        case 2: SP2_L(2)
+        case 3: SP2_L(3)
+        case 4: SP2_L(4)
+        case 5: SP2_L(5)
+        default: SP2_L(6)
+    }
+#undef SP2_L
     return hipGetLastError();
 }
 hipError_t launch_store_coefs(float* dst, const double* vals, int count, hipStream_t s) {

@@ -848,7 +848,7 @@ static bool fermi_plan(int n, const sp2_options* opt, Opts* o, Plan* p, size_t* 
                        size_t* total) {
     if (n <= 0 || n > 65536 || !read_opts(opt, o)) return false;
     if (!o->have_bounds || o->accelerate) return false;
-    o->refine = 1;   // the FP64 refinement buffer holds the read-out accumulator
+    o->refine = 1;   // the FP64 refinement buffers hold layer outputs
     make_plan(n, *o, p);
     *off_coef = align_up(p->total);   // FP32 copy, then FP64 copy of the layer coefficients
     *off_sum = align_up(*off_coef + (sizeof(float) + sizeof(double)) * 3 * SP2_MAX_LAYERS);
@@ -893,17 +893,38 @@ int sp2_fermi_apply(const double* dH, int ldh, double* dD, int ldd, int n, int l
     }
     float* dcoef = (float*)(ws + off_coef);
     double* dcoef64 = (double*)(ws + off_coef + align_up(sizeof(float) * 3 * SP2_MAX_LAYERS));
-    double* acc = (double*)(ws + p.off_s64);
     DevState init = initial_state(n, 0, 0.0, o, p);
     SP2_TRY(launch_state_init(st, init, s));
     SP2_TRY(launch_store_coefs(dcoef, coef, 3 * layers, s));
     SP2_TRY(launch_store_coefs64(dcoef64, coef, 3 * layers, s));
-    void* S[2] = {ws + p.off_s[0], ws + p.off_s[1]};
+    // The layers' outputs go round in every buffer of state matrices that the workspace has (the
+    // FP64 refinement buffers hold two FP32 matrices each) and are read out when all are full.
+    const bool wide = o.precision == SP2_FP64;
+    const size_t m = (size_t)p.np * p.np * sizeof(float);
+    void* S[kReadoutMax] = {ws + p.off_s[0],     ws + p.off_s[1],         ws + p.off_s64,
+                            ws + p.off_y,        ws + p.off_s64 + m,      ws + p.off_y + m};
+    const int slots = wide ? 4 : kReadoutMax;
+    const void* pend[kReadoutMax];
+    double pend_a[kReadoutMax];
+    int pending = 0;
+    bool first = true;
+    double* dstats = (double*)(ws + p.off_dstats);
+    // the last pass takes the observables' sums along
+    auto read_out = [&](const void* x, double a, bool last) -> int {
+        pend[pending] = x;
+        pend_a[pending++] = a;
+        if (pending < slots && !last) return SP2_OK;
+        SP2_TRY(launch_readout(o.precision, pend, pend_a, pending, first, 1.0 - c[0], p.np, dD, ldd, n, dH, ldh,
+                               last && obs ? dstats : nullptr, s));
+        first = false;
+        pending = 0;
+        return SP2_OK;
+    };
     void* P[2][2] = {{p.split ? ws + p.off_p[0][0] : nullptr, p.split ? ws + p.off_p[0][1] : nullptr},
                      {p.split ? ws + p.off_p[1][0] : nullptr, p.split ? ws + p.off_p[1][1] : nullptr}};
     double* init_parts = (double*)(ws + p.off_init_parts);
     SP2_TRY(launch_init_np(dH, ldh, st, p.np, o.precision, S[0], P[0][0], P[0][1], p.scale_log2, init_parts, s));
-    SP2_TRY(launch_readout(o.precision, acc, S[0], p.np, c[0], 1.0 - c[0], 1, s));
+    if (const int rc = read_out(S[0], c[0], false)) return rc;
     StreamK sk;
     memset(&sk, 0, sizeof(sk));
     int sk_variant = 0;
@@ -930,10 +951,10 @@ int sp2_fermi_apply(const double* dH, int ldh, double* dD, int ldd, int n, int l
         const int in = k & 1, out = in ^ 1;
         a.coef = dcoef + 3 * k;
         a.coef64 = o.precision == SP2_FP64 ? dcoef64 + 3 * k : nullptr;
-        a.x0 = p.split ? P[in][0] : S[in];
+        a.x0 = p.split ? P[in][0] : S[k % slots];
         a.x1 = p.split ? P[in][1] : nullptr;
-        a.s_in = S[in];
-        a.s_out = S[out];
+        a.s_in = S[k % slots];
+        a.s_out = S[(k + 1) % slots];
         a.p0_out = P[out][0];
         a.p1_out = P[out][1];
         if (use_sk)
@@ -942,15 +963,11 @@ int sp2_fermi_apply(const double* dH, int ldh, double* dD, int ldd, int n, int l
             SP2_TRY(launch_split_tile_layer(o.precision, p.tile_main, p.kernel, a, s));
         else
             SP2_TRY(launch_plain_layer(o.precision, p.tile_main, p.kernel, a, s));
-        SP2_TRY(launch_readout(o.precision, acc, S[out], p.np, -c[k + 1], 0.0, 0, s));
+        if (const int rc = read_out(S[(k + 1) % slots], -c[k + 1], k + 1 == layers)) return rc;
     }
-    SP2_TRY(launch_copy_out(acc, p.np, dD, ldd, n, s));
     if (!obs) return SP2_OK;
-    double* dstats = (double*)(ws + p.off_dstats);
     double* sums = (double*)(ws + off_sum);
-    int nd = 0;
-    SP2_TRY(launch_dstats(dD, ldd, dH, ldh, n, dstats, &nd, s));
-    SP2_TRY(launch_sum3(dstats, nd, sums, s));
+    SP2_TRY(launch_sum3(dstats, dstats_blocks(n), sums, s));
     SP2_TRY(hipMemcpyAsync(obs, sums, sizeof(double) * 3, hipMemcpyDeviceToHost, s));
     SP2_TRY(hipStreamSynchronize(s));
     return (isfinite(obs[0]) && isfinite(obs[1])) ? SP2_OK : SP2_ENONFINITE;

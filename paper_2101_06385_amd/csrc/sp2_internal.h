@@ -291,10 +291,11 @@ hipError_t launch_split(const float* x, void* p0, void* p1, int np, int precisio
                         hipStream_t s);
 hipError_t launch_sum_parts(const double* parts, int nparts, double* out2, hipStream_t s);
 hipError_t launch_set3(float* dst, float a, float b, float c, hipStream_t s);
-// finite-temperature read-out: acc (FP64, n_p x n_p) = a X + diag I (first) or += a X
-hipError_t launch_readout(int precision, double* acc, const void* x, int np, double a, double diag, int first,
-                          hipStream_t s);
-hipError_t launch_copy_out(const double* acc, int np, double* d, int ldd, int n, hipStream_t s);
+// finite-temperature read-out: D (n x n, FP64) = a_0 X_0 + diag I (first) or D + a_0 X_0, then
+// + a_r X_r for r < count <= kReadoutMax; with parts also the sums of launch_dstats
+constexpr int kReadoutMax = 6;
+hipError_t launch_readout(int precision, const void* const* x, const double* a, int count, int first, double diag,
+                          int np, double* d, int ldd, int n, const double* h, int ldh, double* parts, hipStream_t s);
 hipError_t launch_store_coefs(float* dst, const double* vals, int count, hipStream_t s);   // rounded to FP32
 hipError_t launch_store_coefs64(double* dst, const double* vals, int count, hipStream_t s);
 hipError_t launch_sum3(const double* parts, int nparts, double* out3, hipStream_t s);

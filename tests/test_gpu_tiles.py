@@ -185,3 +185,29 @@ def test_fp32_batch_equals_single_calls():
     for h, w, d, i in zip(hs, ws, ds, infos):
         d1, i1 = sp2.density(h, w.n_occ, precision="fp32", kernel=1)
         assert torch.equal(d, d1) and i["sigma"] == i1["sigma"]
+
+
+# the read-out takes up to six (FP64: four) layer outputs per pass
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16x2", "bf16x2"])
+@pytest.mark.parametrize("layers", [1, 3, 4, 5, 6, 7, 11, 12])
+def test_fermi_read_out_over_several_passes(prec, layers):
+    n = 131
+    h = _sym(n, 1600 + layers, torch.float64)
+    rng = np.random.default_rng(layers)
+    theta = np.array([(1.0, 0.0, 0.0) if b else (-1.0, 2.0, 0.0) for b in rng.integers(0, 2, layers)])
+    c = rng.standard_normal(layers + 1)
+    eye = np.eye(n)
+    xs = []   # X_k = I - D for the read-out of X_k alone
+    for k in range(layers + 1):
+        d, _ = sp2.fermi_apply(h, theta, np.eye(layers + 1)[k], (-3.0, 3.0), precision=prec)
+        xs.append(eye - d.cpu().numpy())
+    buf = torch.empty(n, n + 5, dtype=torch.float64, device=DEV)
+    d, obs = sp2.fermi_apply(h, theta, c, (-3.0, 3.0), precision=prec, out=buf[:, 1:n + 1])
+    d = d.cpu().numpy()
+    ref = eye - sum(ck * x for ck, x in zip(c, xs))
+    scale = 1.0 + sum(abs(ck) * (1.0 + np.abs(x).max()) for ck, x in zip(c, xs))
+    assert np.abs(d - ref).max() <= 2 * (layers + 4) * 2.0**-53 * scale
+    hn, slack = h.cpu().numpy(), 2 * (n * n + 1) * 2.0**-53
+    assert abs(obs[0] - np.trace(d)) <= slack * np.abs(np.diag(d)).sum()
+    assert abs(obs[1] - (d * d).sum()) <= slack * (d * d).sum()
+    assert abs(obs[2] - (d * hn).sum()) <= slack * np.abs(d * hn).sum()
