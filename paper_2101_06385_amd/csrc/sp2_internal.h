@@ -183,20 +183,22 @@ struct AdjointArgs {
     float* g_out;         // G_k = W_k (G X_k + X_k G) + B_k G
     double* parts;        // 3 doubles per tile: Tr G, <G, X_k>, <G, X_k^2>
     const float* coef;    // (W_k, B_k, c_k)
-    int np, T, ntiles, per;
+    int np, n;            // G and X are zero beyond n
+    int T, ntiles;        // square_mix_grid over the rows to compute
+};
+// One layer's partials and where their sums go; parts null = none.
+struct AdjointSums {
+    const double* parts;
+    float *dw, *db, *dc;
 };
 
 hipError_t launch_pack_coef(const float* w, const float* b, const float* c, int K, float* out, hipStream_t s);
 hipError_t launch_copy_pad(const float* src, float* dst, int n, int ld, int np, int to_pad, hipStream_t s);
 // dst (np x np, zero padded) <- (src + src^T)/2 of the n x n src (ld); np a multiple of 32
 hipError_t launch_sym_pad(const float* src, float* dst, int n, int ld, int np, hipStream_t s);
-int adjoint_grid(int tile, int np, int* T, int* ntiles, int* per);
-// adjoint variants 0..2 (k_net.hip): tile, schedule, split-K partial buffer, launch
-int adjoint_tile(int variant);
-void adjoint_plan(int variant, int np, int cus, StreamK* sk);
-size_t adjoint_partial_bytes(int variant);
-hipError_t launch_adjoint(int variant, const AdjointArgs& a, const StreamK& sk, hipStream_t s);
-hipError_t launch_reduce3(const double* parts, int nparts, float* dw, float* db, float* dc, int k, hipStream_t s);
+// one adjoint layer (k_adjoint.hip), and the sums of another layer's partials (same tiles) along
+hipError_t launch_adjoint(const AdjointArgs& a, const AdjointSums& prev, hipStream_t s);
+hipError_t launch_reduce3(const AdjointSums& p, int nparts, hipStream_t s);
 
 // One problem of a batched call (device copy; pointers into the batch workspace).  The
 // batched path uses the FP32 state of the split and FP32 modes.

@@ -14,19 +14,16 @@ constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
 
-// adjoint variant for n <= 4096 (64 tiles): 0 = 2 LDS stages, two workgroups per CU;
-// 1 = 4 stages, one per CU
-constexpr int kAdjVariantSmall = 0;
 // ckpt_every = 0 keeps every layer (no recomputation in the backward) while the K + 7
 // padded matrices fit in this many bytes, a small share of the device memory; above it
 // the checkpoints are sqrt(K) apart.
 constexpr size_t kKeepAllBytes = size_t(8) << 30;
 
 struct NetPlan {
-    int n, np, K, c, nck, precision, tile_main, tile_adj, adj_variant, scale_log2;
+    int n, np, K, c, nck, precision, tile_main, scale_log2;
     bool split;
-    int T_main, nt_main, per_main, T_adj, nt_adj, per_adj;
-    size_t off_coef, off_adj_parts, off_adj_partial, off_adj_counter, off_ckpt, off_seg, off_ping, off_planes, off_g,
+    int T_main, nt_main, per_main, T_adj, nt_adj;
+    size_t off_coef, off_adj_parts, off_ckpt, off_seg, off_ping, off_planes, off_g,
         off_xout, total;
 };
 
@@ -39,18 +36,13 @@ bool net_plan(int n, int K, int precision, int ckpt_every, NetPlan* p) {
     p->split = precision != SP2_FP32;
     p->scale_log2 = precision == SP2_FP16X2 ? 12 : 0;
     p->tile_main = n <= 256 ? 64 : 128;
-    // adjoint: 64 tiles until 128 tiles fill the GPU (136 tiles of 128 at n = 2048 left
-    // half the CUs idle)
-    p->adj_variant = n <= 4096 ? kAdjVariantSmall : 2;
-    p->tile_adj = adjoint_tile(p->adj_variant);
-    const int m = p->tile_main > p->tile_adj ? p->tile_main : p->tile_adj;
-    p->np = round_up(n, m);
+    p->np = round_up(n, p->tile_main);
     int nmain = 0;
     if (p->split)
         square_split_grid(p->tile_main, p->np, &p->T_main, &p->nt_main, &p->per_main);
     else   // over the padding too: the adjoint reads it as zeros
         square_mix_grid(p->np, &p->T_main, &nmain, &p->nt_main);
-    adjoint_grid(p->tile_adj, p->np, &p->T_adj, &p->nt_adj, &p->per_adj);
+    square_mix_grid(n, &p->T_adj, &nmain, &p->nt_adj);
     const size_t m2 = (size_t)p->np * p->np * sizeof(float);
     if (ckpt_every) p->c = ckpt_every;
     else p->c = (size_t)(K + 7) * m2 <= kKeepAllBytes ? 1 : (int)ceil(sqrt((double)K));
@@ -60,11 +52,7 @@ bool net_plan(int n, int K, int precision, int ckpt_every, NetPlan* p) {
     p->off_coef = off;
     off = align_up(off + sizeof(float) * 3 * K);
     p->off_adj_parts = off;
-    off = align_up(off + sizeof(double) * 3 * p->nt_adj);
-    p->off_adj_partial = off;   // split-K partials of the adjoint's leftover tiles
-    off = align_up(off + adjoint_partial_bytes(p->adj_variant));
-    p->off_adj_counter = off;
-    off = align_up(off + sizeof(int) * kMaxSkGrid);
+    off = align_up(off + sizeof(double) * 6 * p->nt_adj);   // two layers' partials
     p->off_ckpt = off;
     off = align_up(off + m2 * p->nck);
     p->off_seg = off;
@@ -200,23 +188,13 @@ int sp2_net_backward(const float* dGK, int ldg, int n, int K, const float* dW, c
     int gc = 0;
     // X_K is symmetric, so only the symmetric part of G_K acts on it
     SP2_TRY(launch_sym_pad(dGK, b.g[gc], n, ldg, p.np, s));
-    StreamK sk;
-    memset(&sk, 0, sizeof(sk));
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        return SP2_EDEVICE;
-    adjoint_plan(p.adj_variant, p.np, cus, &sk);
-    sk.partial = (float*)((char*)dWork + p.off_adj_partial);
-    sk.counter = (int*)((char*)dWork + p.off_adj_counter);
-    SP2_TRY(launch_zero_ints(sk.counter, kMaxSkGrid, s));   // arrivals count modulo chunks from here
     AdjointArgs aa;
     memset(&aa, 0, sizeof(aa));
-    aa.parts = b.adj_parts;
     aa.np = p.np;
+    aa.n = n;
     aa.T = p.T_adj;
     aa.ntiles = p.nt_adj;
-    aa.per = p.per_adj;
+    AdjointSums prev = {nullptr, nullptr, nullptr, nullptr};
     for (int seg = p.nck - 1; seg >= 0; --seg) {
         const int s0 = seg * p.c;
         const int e = s0 + p.c < K ? s0 + p.c : K;
@@ -236,11 +214,13 @@ int sp2_net_backward(const float* dGK, int ldg, int n, int K, const float* dW, c
             aa.x = (k == s0) ? xs : b.seg + (size_t)(k - s0) * b.m;
             aa.g_out = b.g[gc ^ 1];
             aa.coef = b.coef + 3 * k;
-            SP2_TRY(launch_adjoint(p.adj_variant, aa, sk, s));
-            SP2_TRY(launch_reduce3(b.adj_parts, p.nt_adj, ddW, ddB, ddC, k, s));
+            aa.parts = b.adj_parts + (size_t)(k & 1) * 3 * p.nt_adj;
+            SP2_TRY(launch_adjoint(aa, prev, s));
+            prev = {aa.parts, ddW + k, ddB + k, ddC + k};
             gc ^= 1;
         }
     }
+    SP2_TRY(launch_reduce3(prev, p.nt_adj, s));
     if (dG0) SP2_TRY(launch_copy_pad(b.g[gc], dG0, n, ldg0, p.np, 0, s));
     return SP2_OK;
 }

@@ -211,3 +211,37 @@ def test_fermi_read_out_over_several_passes(prec, layers):
     assert abs(obs[0] - np.trace(d)) <= slack * np.abs(np.diag(d)).sum()
     assert abs(obs[1] - (d * d).sum()) <= slack * (d * d).sum()
     assert abs(obs[2] - (d * hn).sum()) <= slack * np.abs(d * hn).sum()
+
+
+# adjoint tiles: one ragged tile, several cut ones, and whole 64-tiles with cut ones (1409)
+@pytest.mark.parametrize("n,layers", [(1, 1), (31, 2), (33, 3), (65, 4), (200, 5), (1409, 2)])
+def test_adjoint_tiles_match_fp64(n, layers):
+    x0, gk = _sym(n, 1700 + n, torch.float32), _sym(n, 1800 + n, torch.float32)
+    rng = np.random.default_rng(n)
+    w, b, c = (torch.from_numpy(rng.uniform(0.2, 0.8, layers).astype(np.float32)).to(DEV) for _ in range(3))
+    xk, ws = sp2.net_forward(x0, w, b, c, precision="fp32")
+    dw, db, dc, g0 = sp2.net_backward(gk, w, b, c, ws, precision="fp32")
+    xs = [x0.double().cpu().numpy()]
+    eye = np.eye(n)
+    wd, bd, cd = (v.double().cpu().numpy() for v in (w, b, c))
+    for k in range(layers):
+        xs.append(wd[k] * xs[-1] @ xs[-1] + bd[k] * xs[-1] + cd[k] * eye)
+    g = gk.double().cpu().numpy()
+    u = 2.0**-24
+    # Forward and adjoint layers are each 2 n + 4 roundings of at most |W| |X| |X| + |B| |X| + |c| in
+    # norm; the errors of X_k enter the adjoint once more per layer.  Frobenius norms, layer by layer.
+    nrm = np.linalg.norm
+    ex = [0.0]
+    for k in range(layers):
+        a = nrm(xs[k])
+        ex.append((2 * wd[k] * a + bd[k]) * ex[-1] + (2 * n + 4) * u * (wd[k] * a * a + bd[k] * a + cd[k] * n**0.5))
+    eg = 0.0
+    for k in range(layers - 1, -1, -1):
+        x, a, gn = xs[k], nrm(xs[k]), nrm(g)
+        for got, ref, m in ((dc[k], np.trace(g), n**0.5), (db[k], (g * x).sum(), a), (dw[k], (g * (x @ x)).sum(), a * a)):
+            err = eg * m + gn * (2 * ex[k] * max(a, 1.0) + (2 * n + 8) * u * m)
+            assert abs(float(got) - ref) <= err, (k, float(got), ref, err)
+        eg = (2 * wd[k] * a + bd[k]) * eg + gn * (2 * wd[k] * ex[k] + (2 * n + 8) * u * (2 * wd[k] * a + bd[k]))
+        g = wd[k] * (g @ x + x @ g) + bd[k] * g
+    g0 = g0.double().cpu().numpy()
+    assert np.array_equal(g0, g0.T) and nrm(g0 - g) <= eg
