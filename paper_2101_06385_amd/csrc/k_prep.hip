@@ -340,6 +340,34 @@ __global__ __launch_bounds__(kThreads) void k_split(const float* __restrict__ x,
     }
 }
 
+// planes of x (np x np) in the fragment order of k_square_fm.h, one 32 x 16 block per wave (the
+// stores whole, the loads 256 bytes of a row per four waves), eight columns of a row per lane
+template <typename T16>
+__global__ __launch_bounds__(kThreads) void k_split_fm(const float* __restrict__ x, T16* __restrict__ p0,
+                                                       T16* __restrict__ p1, int np, float in_scale) {
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    typedef T16 vec8 __attribute__((ext_vector_type(8)));
+    const size_t total = (size_t)np * (np / 8), ps = (size_t)fm_pstride(np) * 512;
+    for (size_t idx = (size_t)blockIdx.x * kThreads + threadIdx.x; idx < total; idx += (size_t)gridDim.x * kThreads) {
+        const size_t block = idx / 64;
+        const int lane = (int)(idx % 64), r = 32 * (int)(block / (np / 16)) + (lane & 31);
+        const int c = 2 * (int)(block % (np / 16)) + (lane >> 5);   // chunk of 8 columns
+        const f32x4* src = (const f32x4*)(x + (size_t)r * np + 8 * c);
+        const f32x4 v[2] = {src[0], src[1]};
+        vec8 h0, h1;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float xs = v[e >> 2][e & 3] * in_scale;
+            const T16 a = (T16)xs;
+            h0[e] = a;
+            h1[e] = (T16)(xs - (float)a);
+        }
+        const size_t o = (size_t)(r >> 5) * ps + (size_t)(c >> 1) * 512 + ((r & 31) + 32 * (c & 1)) * 8;
+        *(vec8*)(p0 + o) = h0;
+        *(vec8*)(p1 + o) = h1;
+    }
+}
+
 __global__ __launch_bounds__(kThreads) void k_sum_parts(const double* __restrict__ parts, int nparts,
                                                         double* __restrict__ out2) {
     __shared__ double sh[2 * kThreads];
@@ -770,6 +798,18 @@ hipError_t launch_split(const float* x, void* p0, void* p1, int np, int precisio
     else if (precision == SP2_BF16X2)
         hipLaunchKernelGGL((k_split<__bf16>), dim3(grid_for(total)), dim3(kThreads), 0, s, x, (__bf16*)p0,
                            (__bf16*)p1, np, sc);
+    else
+        return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+hipError_t launch_split_fm(const float* x, void* p0, void* p1, int np, int precision, int scale_log2, hipStream_t s) {
+    const dim3 grid(grid_for((size_t)np * (np / 8)));
+    const float sc = ldexpf(1.f, scale_log2);
+    if (precision == SP2_FP16X2)
+        hipLaunchKernelGGL((k_split_fm<_Float16>), grid, dim3(kThreads), 0, s, x, (_Float16*)p0, (_Float16*)p1, np, sc);
+    else if (precision == SP2_BF16X2)
+        hipLaunchKernelGGL((k_split_fm<__bf16>), grid, dim3(kThreads), 0, s, x, (__bf16*)p0, (__bf16*)p1, np, sc);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();

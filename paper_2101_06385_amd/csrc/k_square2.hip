@@ -121,6 +121,20 @@ template <typename T16>
 hipError_t launch_fm_t(int variant, const FmArgs& a, hipStream_t s);
 extern template hipError_t launch_fm_t<_Float16>(int, const FmArgs&, hipStream_t);
 extern template hipError_t launch_fm_t<__bf16>(int, const FmArgs&, hipStream_t);
+// Fragment-major split layers (k_square_fm.h) of a single problem: 64- and 128-tiles, one
+// workgroup per tile asked for or chosen, below the sizes that fill the chip with 128-tiles
+// (one layer with its control, this path against k_square_dp with its control in its last tile
+// or, before that, in a launch: n = 400 8.8 against 16.1 us, 1000 13.4 against 24.8, 2000 38 against 66,
+// 2500 64 against 72, 2900 113 against 130 us; n >= 3072 runs the persistent schedule).
+bool fm_wanted(bool split, int tile, int kernel, int np) {
+    return split && (kernel == 0 || kernel == 1) && (tile == 64 || tile == 128) && np < 3072;
+}
+// Variant: + 1 for the product order of the 128-tile kernels; 4-wave workgroups while a CU's
+// LDS holds all its 64-tiles (two per CU, 512 in all: n = 1000 13.4 us per layer against 22.3
+// us with one wave per tile, 1700 27.9 against 31.6), one wave per tile above (n = 2000 38.4
+// against 43.7 us, 2500 63.6 against 72.2 us).
+int fm_variant(int tile, int ntiles64) { return (tile == 128 ? 1 : 0) + (ntiles64 > 512 ? 2 : 0); }
+
 hipError_t launch_fm(int precision, int variant, const FmArgs& a, hipStream_t s) {
     if (precision == SP2_FP16X2) return launch_fm_t<_Float16>(variant, a, s);
     if (precision == SP2_BF16X2) return launch_fm_t<__bf16>(variant, a, s);

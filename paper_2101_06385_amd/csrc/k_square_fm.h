@@ -11,6 +11,8 @@
 //    conflicts, or one coalesced load into registers.
 //  * The state S is kept as 32 x 32 blocks of the upper triangle in accumulator order: 1 KB
 //    loads and stores, no mirrored copy (k_select_fm expands it).
+//  * Layers of the network (NET) keep S row-major, which their adjoint reads, and take their
+//    coefficients from memory: no control and no sums.
 //  * Leading control: every workgroup derives its layer's sigma_n from the partial sums of the
 //    previous launch behind its first products (the same fixed-order sums in every workgroup);
 //    workgroup 0 records it.  No control launch, no arrival counter, no wait for stores at the
@@ -20,7 +22,8 @@
 // Measured, one layer of a solve with its control, against the register-staged or 128-tile
 // per-tile kernel with control launches: n = 65 6.9 against 11.2 us, 400 8.8 against 16.1, 777
 // 11.8 against 24, 1000 13.4 against 24.8, 1400 18 against 30, 2000 38 against 66, 2100 41
-// against 55 us.  A 64 x 64 tile takes 192 LDS cycles per 16-wide unit of K (8 KB in, 16 KB
+// against 55 us.  A layer of the network, against k_square_dp on 128-tiles: n = 512 8 against 27,
+// 1400 16 against 39, 2048 38 against 50, 2900 102 against 122 us.  A 64 x 64 tile takes 192 LDS cycles per 16-wide unit of K (8 KB in, 16 KB
 // out) for 96 cycles of products per wave; the clock holds about 1.65 GHz here.  Tried and not
 // kept: one wave per 32 x 32 block (equal up to n = 550, half as fast at 1700), two waves of
 // 64 x 32 (10-20 % slower below n = 2000), the tiles beyond a whole round of one per CU cut into
@@ -82,9 +85,10 @@ __device__ __forceinline__ void fm_for(F&& f) {
 // from the products in `acc` and the block's S, stored as a block of S, split into the planes
 // at (bi, bj) and (bj, bi); adds the block's trace and square sums per lane.  tr: kFmTranspose
 // bytes of LDS of this wave.
+// NET (layers of the network): S is row-major, both triangles, and there are no sums.
 constexpr int kFmTH = 40;                           // transpose pitch in halves (80 bytes: 16-byte aligned rows)
 constexpr int kFmTranspose = 2 * 32 * kFmTH * 2;
-template <typename T16>
+template <typename T16, bool NET>
 __device__ __forceinline__ void fm_store_block(const FmArgs& a, const Coefs& cf, int bi, int bj, const f32x16& acc,
                                                const f32x4 (&s4)[4], size_t ps, T16* __restrict__ tr0, double* tr,
                                                double* fr) {
@@ -97,6 +101,8 @@ __device__ __forceinline__ void fm_store_block(const FmArgs& a, const Coefs& cf,
     T16* p1 = (T16*)a.p1_out;
     const int lane = threadIdx.x & 63, c = lane & 31, hi = lane >> 5;
     f32x4* so = (f32x4*)(a.s_out + ((size_t)bi * a.sb + bj) * 1024) + lane;
+    float* row0 = a.s_out + (size_t)(32 * bi) * a.ld + 32 * bj + c;            // NET: this lane's column
+    float* col0 = a.s_out + (size_t)(32 * bj + c) * a.ld + 32 * bi + 4 * hi;   // and its mirror
     auto block = [&](auto diag_) {
         constexpr bool diag = decltype(diag_)::value;
         fm_for<0, 4>([&](auto g) {
@@ -112,14 +118,18 @@ __device__ __forceinline__ void fm_store_block(const FmArgs& a, const Coefs& cf,
                 const T16 a0 = (T16)ys;
                 h0[(int)e] = a0;
                 h1[(int)e] = (T16)(ys - (float)a0);
-                if (!diag || r < c) {
+                if (NET) {
+                    if (!diag || r <= c) row0[(size_t)r * a.ld] = y;
+                    if (diag && r < c) col0[8 * g + e] = y;
+                } else if (!diag || r < c) {
                     *fr += 2.0 * (double)y * (double)y;
                 } else if (r == c) {
                     *tr += (double)y;
                     *fr += (double)y * (double)y;
                 }
             });
-            so[64 * g] = y4;
+            if (!NET) so[64 * g] = y4;
+            else if (!diag) *(f32x4*)(col0 + 8 * g) = y4;
             // block (bj, bi) of the planes: rows are this block's columns
             if (!diag) {
                 const size_t o = (size_t)bj * ps + (size_t)(2 * bi + (g >> 1)) * 512 + (c + 32 * (g & 1)) * 8 + 4 * hi;
@@ -153,6 +163,24 @@ __device__ __forceinline__ void fm_store_block(const FmArgs& a, const Coefs& cf,
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 }
 
+// This wave's S of block (bi, bj) for the beta term.
+template <bool NET>
+__device__ __forceinline__ void fm_load_block(const FmArgs& a, int bi, int bj, f32x4 (&s4)[4]) {
+    const int lane = threadIdx.x & 63;
+    fm_for<0, 4>([&](auto g) {
+        if (NET) s4[g] = *(const f32x4*)(a.s_in + (size_t)(32 * bj + (lane & 31)) * a.ld + 32 * bi + 8 * g + 4 * (lane >> 5));
+        else s4[g] = ((const f32x4*)(a.s_in + ((size_t)bi * a.sb + bj) * 1024))[64 * g + lane];
+    });
+}
+// NET: a block of a 64-tile beyond the data holds zeros (the adjoint layers read it)
+__device__ __forceinline__ void fm_zero_block(const FmArgs& a, int bi, int bj) {
+    const int lane = threadIdx.x & 63, c = lane & 31, hi = lane >> 5;
+    for (int r = 0; r < 16; ++r) {
+        a.s_out[(size_t)(32 * bi + 2 * r + hi) * a.ld + 32 * bj + c] = 0.f;
+        if (bi != bj) a.s_out[(size_t)(32 * bj + 2 * r + hi) * a.ld + 32 * bi + c] = 0.f;
+    }
+}
+
 // One wave per workgroup, a 64 x 64 tile of Y (2 x 2 blocks): for problems with more 64-tiles
 // than the 4-wave workgroups' LDS lets a CU hold.  The last tile runs the next layer's control
 // (the sums of so many tiles would take every wave longer than that).  A wave's loads return 16 bytes per clock
@@ -160,7 +188,7 @@ __device__ __forceinline__ void fm_store_block(const FmArgs& a, const Coefs& cf,
 // unit, whatever its depth, against 384 of the unit's 12 products), so the A fragments come
 // straight into registers, DA units ahead, and the B fragments through a ring of R units in
 // LDS; reads and loads go between the products.
-template <typename T16, int R, int DA, int ORD>
+template <typename T16, int R, int DA, int ORD, bool NET = false>
 __global__ __launch_bounds__(64) void k_square_fm1(FmArgs a) {
     typedef FmOps<T16> Ops;
     typedef typename Ops::vec8 vec8;
@@ -224,8 +252,8 @@ __global__ __launch_bounds__(64) void k_square_fm1(FmArgs a) {
         if constexpr (w < DA) fm_for<0, 4>([&](auto k) { load_a(w, k, off(w)); });
     });
     Coefs cf;   // read while the first loads are in flight
-    for (int i = 0; i < 3; ++i) cf.f[i] = st->coef[i];
-    const bool skip = st->skip;
+    for (int i = 0; i < 3; ++i) cf.f[i] = NET ? a.coef[i] : st->coef[i];
+    const bool skip = !NET && st->skip;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if (skip) return;   // Alg. 1 has stopped
     fm_for<0, 4>([&](auto k) { read_b(std::integral_constant<int, 0>{}, k, 0); });
@@ -248,19 +276,23 @@ __global__ __launch_bounds__(64) void k_square_fm1(FmArgs a) {
     f32x4 s4[4][4];
     fm_for<0, 4>([&](auto q) {
         const int bi = 2 * I + (q >> 1), bj = 2 * J + (q & 1);
-        fm_for<0, 4>([&](auto g) {
-            s4[q][g] = ((const f32x4*)(a.s_in + ((size_t)bi * a.sb + bj) * 1024))[64 * g + lane];
-        });
+        fm_load_block<NET>(a, bi, bj, s4[q]);
     });
     double tt = 0.0, ft = 0.0;
     fm_for<0, 4>([&](auto q) {
         const int bi = 2 * I + (q >> 1), bj = 2 * J + (q & 1);
-        if (bi > bj || 32 * bj >= a.n_real) return;
+        if (bi > bj) return;
+        if (32 * bj >= a.n_real) {
+            if (NET) fm_zero_block(a, bi, bj);
+            return;
+        }
         double tr = 0.0, fr = 0.0;
-        fm_store_block<T16>(a, cf, bi, bj, acc[q >> 1][q & 1], s4[q], ps, (T16*)ring, &tr, &fr);
+        fm_store_block<T16, NET>(a, cf, bi, bj, acc[q >> 1][q & 1], s4[q], ps, (T16*)ring, &tr, &fr);
+        if (NET) return;
         tt += wave_sum0(tr);
         ft += wave_sum0(fr);
     });
+    if (NET) return;
     if (lane == 0) {
         st_agent(a.parts_out + 2 * (size_t)t, tt);
         st_agent(a.parts_out + 2 * (size_t)t + 1, ft);
@@ -271,7 +303,7 @@ __global__ __launch_bounds__(64) void k_square_fm1(FmArgs a) {
 // One 64 x 64 tile of Y per workgroup, in 4 waves of one 32 x 32 block each.  R slots of US
 // units of 16 K in the LDS ring.  ORD 0: products X0 X0, X0 X1, X1 X0 per unit (the order of
 // the 64-tile kernels), 1: X0 X1, X0 X0, X1 X0 (128-tile kernels).
-template <typename T16, int R, int US, int ORD>
+template <typename T16, int R, int US, int ORD, bool NET = false>
 __global__ __launch_bounds__(256) void k_square_fm(FmArgs a) {
     typedef FmOps<T16> Ops;
     typedef typename Ops::vec8 vec8;
@@ -296,11 +328,9 @@ __global__ __launch_bounds__(256) void k_square_fm(FmArgs a) {
     const int ra = 2 * I, rb = 2 * J;   // first staged panels
     const int bi0 = ra + wi, bj0 = rb + wj;
 
-    f32x4 s4[4];   // this wave's S for the beta term
-    fm_for<0, 4>([&](auto g) {
-        s4[g] = ((const f32x4*)(a.s_in + ((size_t)bi0 * a.sb + bj0) * 1024))[64 * g + lane];
-    });
-    if (wave == 0) lead_load(a.lead, (unsigned)(uintptr_t)(const fm_lds_byte*)dyn);
+    f32x4 s4[4];
+    fm_load_block<NET>(a, bi0, bj0, s4);
+    if (!NET && wave == 0) lead_load(a.lead, (unsigned)(uintptr_t)(const fm_lds_byte*)dyn);
 
     const int KU = a.ku;
     const size_t ps = (size_t)a.pstride * 512;   // halves per 32-row panel
@@ -381,7 +411,7 @@ __global__ __launch_bounds__(256) void k_square_fm(FmArgs a) {
     }
     Frags fp, fq;
     // a layer behind the stop (workgroup 0 still hands the state on)
-    if (((const StateHot*)a.lead.hot_in)->stopped && blockIdx.x != 0) {
+    if (!NET && ((const StateHot*)a.lead.hot_in)->stopped && blockIdx.x != 0) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         return;
     }
@@ -397,7 +427,9 @@ __global__ __launch_bounds__(256) void k_square_fm(FmArgs a) {
     // the control runs behind the first units' products, with the next loads in flight
     if (u + 2 < KS) pair();
     Coefs cf;
-    if (!lead_finish(a.lead, dyn, blockIdx.x == 0 && wave == 0, &cf)) {   // Alg. 1 has stopped
+    if (NET) {
+        for (int i = 0; i < 3; ++i) cf.f[i] = a.coef[i];
+    } else if (!lead_finish(a.lead, dyn, blockIdx.x == 0 && wave == 0, &cf)) {   // Alg. 1 has stopped
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         return;
     }
@@ -409,11 +441,17 @@ __global__ __launch_bounds__(256) void k_square_fm(FmArgs a) {
         mma_last(fp);
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // the ring is free
+    if (NET) {
+        if (bi0 > bj0) return;
+        if (32 * bj0 >= a.n_real) return fm_zero_block(a, bi0, bj0);
+        double tr = 0.0, fr = 0.0;
+        return fm_store_block<T16, true>(a, cf, bi0, bj0, acc[0][0], s4, ps, (T16*)(ring + wave * kFmTranspose), &tr, &fr);
+    }
     if (threadIdx.x < 8) red[threadIdx.x >> 1][threadIdx.x & 1] = 0.0;   // a block below the diagonal adds nothing
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     double tr = 0.0, fr = 0.0;
     if (bi0 <= bj0 && 32 * bj0 < a.n_real) {
-        fm_store_block<T16>(a, cf, bi0, bj0, acc[0][0], s4, ps, (T16*)(ring + wave * kFmTranspose), &tr, &fr);
+        fm_store_block<T16, false>(a, cf, bi0, bj0, acc[0][0], s4, ps, (T16*)(ring + wave * kFmTranspose), &tr, &fr);
         const double s0 = wave_sum0(tr), s1 = wave_sum0(fr);
         if (lane == 0) {
             red[wave][0] = s0;
@@ -428,9 +466,22 @@ __global__ __launch_bounds__(256) void k_square_fm(FmArgs a) {
 
 }  // namespace
 
-// variant: ORD + 2 x (0: 4-wave workgroups, 1: one wave) (see fm_variant in sp2_api.hip)
+// variant: ORD + 2 x (0: 4-wave workgroups, 1: one wave) (see fm_variant in sp2_api.hip); a.coef: a
+// layer of the network
 template <typename T16>
 hipError_t launch_fm_t(int variant, const FmArgs& a, hipStream_t s) {
+    if (a.coef) {
+#define SP2_L(K, NT) hipLaunchKernelGGL((K), dim3(8 * a.per), dim3(NT), 0, s, a)
+        switch (variant) {
+            case 0: SP2_L((k_square_fm<T16, 4, 2, 0, true>), 256); break;
+            case 1: SP2_L((k_square_fm<T16, 4, 2, 1, true>), 256); break;
+            case 2: SP2_L((k_square_fm1<T16, 4, 4, 0, true>), 64); break;
+            case 3: SP2_L((k_square_fm1<T16, 4, 4, 1, true>), 64); break;
+            default: return hipErrorInvalidValue;
+        }
+#undef SP2_L
+        return hipGetLastError();
+    }
 #define SP2_L(K, NT, LDS) hipLaunchKernelGGL((K), dim3(8 * a.per), dim3(NT), LDS, s, a)
     switch (variant) {
         case 0: SP2_L((k_square_fm<T16, 4, 2, 0>), 256, lead_bytes(a.lead)); break;

@@ -57,7 +57,9 @@ struct FmArgs {
     void* p0_out;           // planes of Y
     void* p1_out;
     const float* s_in;      // X, 32 x 32 blocks of the upper triangle in accumulator order
-    float* s_out;           // Y
+    float* s_out;           // Y                               (coef: row-major, ld floats per row)
+    const float* coef;      // layers without control (network): (alpha, beta, gamma); else null
+    int ld;
     double* parts_out;      // a pair per 64-tile; those of padding tiles stay zero
     int pstride;            // 1 KB blocks per 32-row panel of a plane
     int sb;                 // 32-blocks per row of blocks of S

@@ -274,6 +274,8 @@ hipError_t launch_init_fm(const double* h, int ldh, DevState* st, int np, int pr
 hipError_t launch_select_fm(const DevState* st, const float* s0, const float* s1, double* out, int ld_out, int n,
                             int n_valid, int np, hipStream_t s);
 hipError_t launch_lead_finish(const LeadArgs& a, hipStream_t s);
+bool fm_wanted(bool split, int tile, int kernel, int np);
+int fm_variant(int tile, int ntiles64);
 hipError_t launch_fm(int precision, int variant, const FmArgs& a, hipStream_t s);
 hipError_t launch_control_stride(DevState* st, const double* parts, int nparts, int stride, int layer,
                                  int* host_flag, hipStream_t s);
@@ -291,6 +293,8 @@ hipError_t launch_tiny(const double* h, int ldh, double* d, int ldd, DevState* s
 hipError_t launch_fill(double* d, int ldd, int n, double diag, hipStream_t s);
 hipError_t launch_split(const float* x, void* p0, void* p1, int np, int precision, int scale_log2,
                         hipStream_t s);
+// the same in fragment order (k_square_fm.h); np a multiple of 32
+hipError_t launch_split_fm(const float* x, void* p0, void* p1, int np, int precision, int scale_log2, hipStream_t s);
 hipError_t launch_sum_parts(const double* parts, int nparts, double* out2, hipStream_t s);
 hipError_t launch_set3(float* dst, float a, float b, float c, hipStream_t s);
 // finite-temperature read-out: D (n x n, FP64) = a_0 X_0 + diag I (first) or D + a_0 X_0, then

@@ -21,7 +21,7 @@ constexpr size_t kKeepAllBytes = size_t(8) << 30;
 
 struct NetPlan {
     int n, np, K, c, nck, precision, tile_main, scale_log2;
-    bool split;
+    bool split, fm;   // fm: split layers on fragment-major planes (k_square_fm.h)
     int T_main, nt_main, per_main, T_adj, nt_adj;
     size_t off_coef, off_adj_parts, off_ckpt, off_seg, off_ping, off_planes, off_g,
         off_xout, total;
@@ -37,8 +37,11 @@ bool net_plan(int n, int K, int precision, int ckpt_every, NetPlan* p) {
     p->scale_log2 = precision == SP2_FP16X2 ? 12 : 0;
     p->tile_main = n <= 256 ? 64 : 128;
     p->np = round_up(n, p->tile_main);
+    p->fm = fm_wanted(p->split, p->tile_main, 0, p->np);
     int nmain = 0;
-    if (p->split)
+    if (p->fm)
+        square_split_grid(64, round_up(n, 64), &p->T_main, &p->nt_main, &p->per_main);
+    else if (p->split)
         square_split_grid(p->tile_main, p->np, &p->T_main, &p->nt_main, &p->per_main);
     else   // over the padding too: the adjoint reads it as zeros
         square_mix_grid(p->np, &p->T_main, &nmain, &p->nt_main);
@@ -106,10 +109,36 @@ NetBuffers carve(const NetPlan& p, void* dWork) {
     return b;
 }
 
+hipError_t split_planes(const NetPlan& p, const NetBuffers& b, const float* x, hipStream_t s) {
+    return p.fm ? launch_split_fm(x, b.planes[0][0], b.planes[0][1], p.np, p.precision, p.scale_log2, s)
+                : launch_split(x, b.planes[0][0], b.planes[0][1], p.np, p.precision, p.scale_log2, s);
+}
+
 // One forward layer X_out = W_k X_in^2 + B_k X_in + c_k I.  Planes of X_in are in
 // planes[pin]; the layer writes the planes of X_out into planes[pin ^ 1].
 hipError_t layer(const NetPlan& p, const NetBuffers& b, int k, const float* x_in, float* x_out, int pin,
                  hipStream_t s) {
+    if (p.fm) {
+        FmArgs f;
+        memset(&f, 0, sizeof(f));
+        f.x0 = b.planes[pin][0];
+        f.x1 = b.planes[pin][1];
+        f.p0_out = b.planes[pin ^ 1][0];
+        f.p1_out = b.planes[pin ^ 1][1];
+        f.s_in = x_in;
+        f.s_out = x_out;
+        f.coef = b.coef + 3 * k;
+        f.ld = p.np;
+        f.pstride = fm_pstride(p.np);
+        f.ku = (p.n + 15) / 16;
+        f.n_real = p.n;
+        f.T = p.T_main;
+        f.ntiles = p.nt_main;
+        f.per = p.per_main;
+        f.out_scale = ldexpf(1.f, -2 * p.scale_log2);
+        f.in_scale = ldexpf(1.f, p.scale_log2);
+        return launch_fm(p.precision, fm_variant(p.tile_main, p.nt_main), f, s);
+    }
     SquareArgs a;
     memset(&a, 0, sizeof(a));
     a.x0 = p.split ? b.planes[pin][0] : (const void*)x_in;
@@ -157,7 +186,7 @@ int sp2_net_forward(const float* dX0, int ld0, int n, int K, const float* dW, co
     NetBuffers b = carve(p, dWork);
     SP2_TRY(launch_pack_coef(dW, dB, dC, K, b.coef, s));
     SP2_TRY(launch_copy_pad(dX0, b.ckpt, n, ld0, p.np, 1, s));   // X_0 is checkpoint 0
-    if (p.split) SP2_TRY(launch_split(b.ckpt, b.planes[0][0], b.planes[0][1], p.np, p.precision, p.scale_log2, s));
+    if (p.split) SP2_TRY(split_planes(p, b, b.ckpt, s));
     const float* x_in = b.ckpt;
     for (int k = 0; k < K; ++k) {
         float* x_out;
@@ -201,7 +230,7 @@ int sp2_net_backward(const float* dGK, int ldg, int n, int K, const float* dW, c
         const float* xs = b.ckpt + (size_t)seg * b.m;
         // recompute X_{s0+1} .. X_{e-1} into seg slots 1 .. e-1-s0 (bit-identical to the forward)
         if (e - 1 > s0) {
-            if (p.split) SP2_TRY(launch_split(xs, b.planes[0][0], b.planes[0][1], p.np, p.precision, p.scale_log2, s));
+            if (p.split) SP2_TRY(split_planes(p, b, xs, s));
             const float* x_in = xs;
             for (int k = s0; k < e - 1; ++k) {
                 float* x_out = b.seg + (size_t)(k + 1 - s0) * b.m;

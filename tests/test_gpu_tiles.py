@@ -245,3 +245,26 @@ def test_adjoint_tiles_match_fp64(n, layers):
         g = wd[k] * (g @ x + x @ g) + bd[k] * g
     g0 = g0.double().cpu().numpy()
     assert np.array_equal(g0, g0.T) and nrm(g0 - g) <= eg
+
+
+# network layers on fragment-major planes: 4-wave workgroups, one wave per tile (2050), blocks of a
+# 64-tile beyond the data (65, 200), 64- and 128-tile product order (from 257)
+@pytest.mark.parametrize("prec", ["fp16x2", "bf16x2"])
+@pytest.mark.parametrize("n", [1, 16, 33, 65, 200, 256, 257, 700, 2050])
+def test_fragment_major_network_layers_equal_per_tile_layers(prec, n):
+    x0 = _sym(n, 1900 + n, torch.float32)
+    w, b, c = (torch.tensor(v, device=DEV) for v in ([1.0, -0.5, 0.7], [0.0, 1.5, -0.25], [0.0, 0.25, -0.5]))
+    for ckpt in (0, 2):
+        need = sp2.net_workspace_size(n, 3, prec, ckpt)
+        ws = sp2.alloc_workspace(need, DEV).fill_(255)   # NaN wherever a kernel reads what none has written
+        xk, ws = sp2.net_forward(x0, w, b, c, precision=prec, ckpt_every=ckpt, workspace=ws)
+        x, tile = x0, 64 if n <= 256 else 128
+        for k in range(3):
+            x, _ = sp2.square(x, float(w[k]), float(b[k]), float(c[k]), precision=prec, tile=tile, kernel=1)
+        assert torch.equal(xk, x)
+        dw, db, dc, g0 = sp2.net_backward(x0, w, b, c, ws, precision=prec, ckpt_every=ckpt)
+        assert all(bool(torch.isfinite(t).all()) for t in (dw, db, dc, g0))
+        if ckpt == 0:
+            first = (dw, db, dc, g0)
+        else:   # recomputed layers have the forward's bits
+            assert all(torch.equal(p, q) for p, q in zip(first, (dw, db, dc, g0)))
