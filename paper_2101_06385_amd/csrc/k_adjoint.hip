@@ -67,6 +67,10 @@ __device__ __forceinline__ void wait_vm(int n) {
 }
 #undef SP2_VMCNT
 
+// Every LDS read of this wave has returned, so behind the barrier other waves' direct loads may
+// take its place (__syncthreads alone leaves reads in flight across the barrier).
+__device__ __forceinline__ void stage_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 __device__ inline double wsum(double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
@@ -180,7 +184,7 @@ __device__ __forceinline__ void adjoint_body(const AdjointArgs& a, int I, int J,
         if (st + 1 < nsl) {
             const int last = (st + ST - 1 < nsl - 1) ? st + ST - 1 : nsl - 1;
             wait_vm((last - st - 1) * LPW);
-            __syncthreads();
+            stage_barrier();
             frags((st + 1) % ST, 0, f[(first + UNITS) & 1]);
             mma(f[(first + UNITS - 1) & 1], buf, st + ST, st + ST < nsl);
         } else {

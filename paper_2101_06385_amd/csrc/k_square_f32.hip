@@ -4,18 +4,16 @@
 //  * Bound: the matrix pipes (157.3 TFLOP/s).  As for the FP64 layers (k_square_f64.hip),
 //    several independent workgroups of 4 waves per CU keep them busy: 64 x 64 tiles, two 16 KB
 //    stages of 32 floats per row (one 128-byte line) filled by global_load_lds_dwordx4, the
-//    tiles beyond the last whole round of one per CU cut into 32 x 32 ones.  The launch keeps
-//    every CU at four workgroups to the end; the clock (1.8 - 2.1 GHz under this load) and the
-//    stages' LDS traffic take the rest.  One layer with its control, against the register-staged
-//    128 x 128 (64 x 64 up to n = 512) workgroups and control launch used before: n = 256 15 ->
-//    8.1 us, 777 65 -> 18 us, 1300 113 -> 37 us, 2112 167 -> 100 us, 4096 773 -> 610 us
-//    (113 TFLOP/s), 5000 1190 -> 1116 us.
+//    tiles beyond the last whole round of one per CU cut into 32 x 32 ones.  One layer with its
+//    control, against the register-staged 128 x 128 (64 x 64 up to n = 512) workgroups and control
+//    launch used before: n = 256 15 -> 7.5 us, 777 65 -> 18 us, 1300 113 -> 35 us, 2112 167 ->
+//    81 us, 4096 773 -> 510 us (135 TFLOP/s; the clock holds about 2.1 GHz), 5000 1190 -> 950 us.
 //  * Each element is the chain of fused multiply-adds over ascending K, whichever instruction
-//    computes it, so the tiling changes no bit: a 64-tile's waves hold one 32 x 32 block each
-//    (v_mfma_f32_32x32x2f32), a 32-tile's one 16 x 16 block (v_mfma_f32_16x16x4f32).
-//  * Lanes read the K they take, 2 t + lane / 32 or 4 t + lane / 16, two per ds_read2_b32.  (One
-//    16-byte read per lane and v_permlane32_swap to sort it took 660 us at n = 4096; four stages
-//    for the 32-tiles 56 us at n = 1300, where fewer workgroups then fit a CU.)
+//    computes it, so the tiling changes no bit.  A wave of a 64-tile holds 2 x 2 blocks of
+//    v_mfma_f32_16x16x4f32, four chains (one chain of v_mfma_f32_32x32x2f32 took 610 us at
+//    n = 4096), a wave of a 32-tile one block.
+//  * Lanes read the K they take, 4 t + lane / 16.  The loop over stages is unrolled until buffers
+//    and fragment sets are back, so that LDS addresses are constants (550 -> 510 us).
 #include "sp2_control.h"
 #include "sp2_internal.h"
 
@@ -25,26 +23,26 @@ namespace {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kBK = 32;            // floats per row per stage
-constexpr int kRow = kBK * 4;      // 128 bytes
-constexpr int kRPB = 1024 / kRow;  // rows per 1 KB direct-load block (8)
-
 // BT x BT output tile, four waves with one B x B block each (B = BT / 2), ST LDS stages of
-// 2 BT rows (panels I and J).
-template <int BT, int ST>
+// 2 BT rows (panels I and J) of ROW bytes.
+template <int BT, int ST, int ROW = 128>
 struct F32Cfg {
     static constexpr int B = BT / 2, NT = 256;
-    static constexpr int ARR = BT * kRow;                // bytes of one panel stage
+    static constexpr int BK = ROW / 4;                   // floats per row per stage
+    static constexpr int CH = ROW / 16;                  // 16-byte chunks per row
+    static constexpr int RPB = 1024 / ROW;               // rows per 1 KB direct-load block
+    static constexpr int ARR = BT * ROW;                 // bytes of one panel stage
     static constexpr int STAGE = 2 * ARR;
-    static constexpr int BPR = BT / kRPB;                // 1 KB blocks per panel stage
+    static constexpr int BPR = BT / RPB;                 // 1 KB blocks per panel stage
     static constexpr int LPW = 2 * BPR / 4;              // direct loads per wave per stage
     static constexpr int LDS = ST * STAGE;
     static constexpr int STRIP = 1024 / BT;              // tile_of strip: 1024 columns
-    static_assert(B == 32 || B == 16, "one MFMA block per wave");
+    static_assert(B == 32 || B == 16, "one or four 16 x 16 blocks per wave");
+    static_assert(ROW == 128 || ROW == 256, "a line of the cache, or two");
     static_assert(LPW * (ST - 1) <= 24, "vmcnt range of wait_vm");
+    // chunk c of row r is stored at c ^ swz(r)
+    static __device__ __forceinline__ int swz(int r) { return (ROW == 128 ? r >> 1 : r) & (CH - 1); }
 };
-
-__device__ inline int swz8(int r) { return (r >> 1) & 7; }
 
 typedef __attribute__((address_space(3))) unsigned char lds_byte;
 __device__ __forceinline__ unsigned lds_addr(const unsigned char* p) {
@@ -76,62 +74,22 @@ __device__ __forceinline__ void wait_vm(int n) {
 }
 #undef SP2_VMCNT
 
+// Every LDS read of this wave has returned, so behind the barrier other waves' direct loads may
+// take its place (__syncthreads alone leaves reads in flight across the barrier).
+__device__ __forceinline__ void stage_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 __device__ inline double wsum(double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
 
-// One wave's B x B block.  A unit is 8 K indices; p(s), s < STEPS, is what a lane gives to the
-// unit's product s.
-template <int B>
-struct Block;
-template <>
-struct Block<32> {
-    static constexpr int REGS = 16, STEPS = 4;
-    typedef f32x16 Acc;
-    struct Frag {
-        float v[4];
-        __device__ __forceinline__ void load(const unsigned char* base, int row, int g, int lane) {
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-                v[s] = *(const float*)(base + row * kRow + (((2 * g + (s >> 1)) ^ swz8(row)) << 4) + ((s & 1) << 3) +
-                                       ((lane >> 5) << 2));
-        }
-        __device__ __forceinline__ float p(int s) const { return v[s]; }
-    };
-    static __device__ __forceinline__ Acc mma(float a, float b, const Acc& c) {
-        return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-    }
-    static __device__ __forceinline__ int row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
-};
-template <>
-struct Block<16> {
-    static constexpr int REGS = 4, STEPS = 2;
-    typedef f32x4 Acc;
-    struct Frag {
-        float v[2];
-        __device__ __forceinline__ void load(const unsigned char* base, int row, int g, int lane) {
-#pragma unroll
-            for (int s = 0; s < 2; ++s)
-                v[s] = *(const float*)(base + row * kRow + (((2 * g + s) ^ swz8(row)) << 4) + ((lane >> 4) << 2));
-        }
-        __device__ __forceinline__ float p(int s) const { return v[s]; }
-    };
-    static __device__ __forceinline__ Acc mma(float a, float b, const Acc& c) {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-    static __device__ __forceinline__ int row(int r, int lane) { return 4 * (lane >> 4) + r; }
-};
-
 // Output tile (I, J) of edge BT over all of K; t is the tile's slot in a.parts.  LEAD: the
 // layer's control at its head (`lead`, lead_bytes of LDS at `dyn`).
-template <int BT, int ST, bool LEAD = false>
+template <int BT, int ST, int ROW = 128, bool LEAD = false>
 __device__ __forceinline__ void f32_body(const SquareArgs& a, int I, int J, int t, unsigned char* __restrict__ lds,
                                          const LeadArgs* lead = nullptr, unsigned char* __restrict__ dyn = nullptr) {
-    typedef F32Cfg<BT, ST> C;
-    typedef Block<C::B> M;
-    typedef typename M::Frag Frag;
-    constexpr int LPW = C::LPW, B = C::B;
+    typedef F32Cfg<BT, ST, ROW> C;
+    constexpr int LPW = C::LPW, B = C::B, MB = B / 16, kRow = ROW, kBK = C::BK;
     const int np = a.np;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -141,12 +99,12 @@ __device__ __forceinline__ void f32_body(const SquareArgs& a, int I, int J, int 
     const unsigned char* src_b = (const unsigned char*)(x + (size_t)J * BT * np);
     const int nsl = ((a.k_all ? np : a.n_real) + kBK - 1) / kBK;
     // direct load l of this wave: lane L fills bytes [16 L, 16 L + 16) of a 1 KB block:
-    // panel row q * 8 + L / 8, physical chunk L % 8 = logical chunk (L % 8) ^ swz8(row)
+    // panel row q * RPB + L / CH, physical chunk L % CH = logical chunk (L % CH) ^ swz(row)
     unsigned voff[LPW];
 #pragma unroll
     for (int l = 0; l < LPW; ++l) {
-        const int row = ((wave * LPW + l) % C::BPR) * kRPB + (lane >> 3);
-        voff[l] = (unsigned)row * (unsigned)np * 4u + (unsigned)(((lane & 7) ^ swz8(row)) << 4);
+        const int row = ((wave * LPW + l) % C::BPR) * C::RPB + lane / C::CH;
+        voff[l] = (unsigned)row * (unsigned)np * 4u + (unsigned)(((lane & (C::CH - 1)) ^ C::swz(row)) << 4);
     }
     auto load_one = [&](int l, int buf, int ks) {
         const int j = wave * LPW + l;
@@ -154,23 +112,42 @@ __device__ __forceinline__ void f32_body(const SquareArgs& a, int I, int J, int 
         dma16s(voff[l], (arr ? src_b : src_a) + (size_t)ks * kRow,
                lds_addr(lds + buf * C::STAGE + arr * C::ARR + qd * 1024));
     };
-    auto frags = [&](int buf, int g, Frag& fa, Frag& fb) {
-        const unsigned char* base = lds + buf * C::STAGE;
-        fa.load(base, wm * B + (lane & (B - 1)), g, lane);
-        fb.load(base + C::ARR, wn * B + (lane & (B - 1)), g, lane);
+    // A unit is UK indices of K: product s takes K UK g + 4 s + lane / 16.  A wave's next unit is
+    // read from LDS behind the products of this one; with one block per wave (32-tiles) it takes
+    // eight products to cover those reads.
+    constexpr int UK = MB == 1 ? kBK / 2 : 8, UNITS = kBK / UK, SU = UK / 4, NM = SU * MB * MB;
+    struct Frag {
+        float a[SU][MB], b[SU][MB];
     };
-    typename M::Acc acc;
+    const int r16 = lane & 15, kq = (lane >> 4) << 2;
+    auto frags = [&](int buf, int g, Frag& f) {
+        const unsigned char* base = lds + buf * C::STAGE;
 #pragma unroll
-    for (int r = 0; r < M::REGS; ++r) acc[r] = 0.f;
+        for (int s = 0; s < SU; ++s)
+#pragma unroll
+            for (int m = 0; m < MB; ++m) {
+                const int ra = wm * B + 16 * m + r16, rb = wn * B + 16 * m + r16, c = SU * g + s;
+                f.a[s][m] = *(const float*)(base + ra * kRow + ((c ^ C::swz(ra)) << 4) + kq);
+                f.b[s][m] = *(const float*)(base + C::ARR + rb * kRow + ((c ^ C::swz(rb)) << 4) + kq);
+            }
+    };
+    f32x4 acc[MB][MB];
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+        for (int n = 0; n < MB; ++n)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[m][n][r] = 0.f;
     // the products of one unit, with (doit) the direct loads of stage ks into buffer buf behind them
-    auto mma = [&](Frag fa, Frag fb, int buf, int ks, bool doit) {
+    auto mma = [&](const Frag& f, int buf, int ks, bool doit) {
 #pragma unroll
-        for (int s = 0; s < M::STEPS; ++s) {
-            acc = M::mma(fa.p(s), fb.p(s), acc);
+        for (int i = 0; i < NM; ++i) {
+            const int s = i / (MB * MB), m = (i / MB) % MB, n = i % MB;
+            acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.a[s][m], f.b[s][n], acc[m][n], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
             if (doit)
 #pragma unroll
-                for (int l = s; l < LPW; l += M::STEPS) load_one(l, buf, ks);
+                for (int l = i; l < LPW; l += NM) load_one(l, buf, ks);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -192,29 +169,35 @@ __device__ __forceinline__ void f32_body(const SquareArgs& a, int I, int J, int 
         wait_vm(0);
         return;
     }
-    Frag pa, pb, qa, qb;
-    frags(0, 0, pa, pb);
-    // units alternate between fragment sets P and Q, four per stage.  Stage st + ST refills the
-    // buffer of stage st among the last unit's products, once every wave has read it.
-    for (int st = 0; st < nsl; ++st) {
-        const int buf = st % ST;
-        frags(buf, 1, qa, qb);
-        mma(pa, pb, 0, 0, false);
-        frags(buf, 2, pa, pb);
-        mma(qa, qb, 0, 0, false);
-        frags(buf, 3, qa, qb);
-        mma(pa, pb, 0, 0, false);
+    Frag f[2];
+    frags(0, 0, f[0]);
+    // Stage st + ST refills the buffer of stage st among the last unit's products, once every wave
+    // has read it.
+    auto stage = [&](int st, int buf, int first) {   // buf = st % ST
+#pragma unroll
+        for (int u = 0; u + 1 < UNITS; ++u) {
+            frags(buf, u + 1, f[(first + u + 1) & 1]);
+            mma(f[(first + u) & 1], 0, 0, false);
+        }
         if (st + 1 < nsl) {
             const int last = (st + ST - 1 < nsl - 1) ? st + ST - 1 : nsl - 1;
             __builtin_amdgcn_sched_barrier(0);
             wait_vm((last - st - 1) * LPW);
-            __syncthreads();
-            frags((st + 1) % ST, 0, pa, pb);
-            mma(qa, qb, buf, st + ST, st + ST < nsl);
+            stage_barrier();
+            frags((buf + 1) % ST, 0, f[(first + UNITS) & 1]);
+            mma(f[(first + UNITS - 1) & 1], buf, st + ST, st + ST < nsl);
         } else {
-            mma(qa, qb, 0, 0, false);
+            mma(f[(first + UNITS - 1) & 1], 0, 0, false);
         }
-    }
+    };
+    constexpr int R = ST % 2 ? 2 * ST : ST;   // stages after which buffers and fragment sets are back
+    int st = 0;
+    for (; st + R <= nsl; st += R)
+#pragma unroll
+        for (int k = 0; k < R; ++k) stage(st + k, k % ST, (k * UNITS) & 1);
+#pragma unroll
+    for (int k = 0; k < R; ++k)
+        if (st + k < nsl) stage(st + k, k % ST, (k * UNITS) & 1);
 
     // ------------------------------------------------------------------- epilogue
     if (!LEAD)
@@ -223,26 +206,32 @@ __device__ __forceinline__ void f32_body(const SquareArgs& a, int I, int J, int 
     float* so = (float*)a.s_out;
     const float* si = (const float*)a.s_in;
     const int ldo = a.ld_out, nv = a.n_valid;
-    const int col = J * BT + wn * B + (lane & (B - 1));
     double tr = 0.0, fr = 0.0;
-    if (I * BT + wm * B <= J * BT + wn * B) {   // not wholly below the diagonal
 #pragma unroll
-        for (int r = 0; r < M::REGS; ++r) {
-            const int row = I * BT + wm * B + M::row(r, lane);
-            if (row > col) continue;
-            const float xv = acc[r];
-            float y = (beta != 0.f) ? alpha * xv + beta * si[(size_t)row * np + col] : alpha * xv;
-            if (row == col && col < a.n_real) y += gamma;
-            if (row < nv && col < nv) {
-                so[(size_t)row * ldo + col] = y;
-                if (row != col) so[(size_t)col * ldo + row] = y;
-            }
-            const double yd = (double)y;
-            if (row == col) {
-                tr += yd;
-                fr += yd * yd;
-            } else {
-                fr += 2.0 * yd * yd;
+    for (int m = 0; m < MB; ++m) {
+#pragma unroll
+        for (int n = 0; n < MB; ++n) {
+            const int bi = I * BT + wm * B + 16 * m, bj = J * BT + wn * B + 16 * n;
+            if (bi > bj) continue;   // below the diagonal
+            const int col = bj + r16;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = bi + kq + r;
+                if (row > col) continue;
+                const float xv = acc[m][n][r];
+                float y = (beta != 0.f) ? alpha * xv + beta * si[(size_t)row * np + col] : alpha * xv;
+                if (row == col && col < a.n_real) y += gamma;
+                if (row < nv && col < nv) {
+                    so[(size_t)row * ldo + col] = y;
+                    if (row != col) so[(size_t)col * ldo + row] = y;
+                }
+                const double yd = (double)y;
+                if (row == col) {
+                    tr += yd;
+                    fr += yd * yd;
+                } else {
+                    fr += 2.0 * yd * yd;
+                }
             }
         }
     }
@@ -273,7 +262,6 @@ __device__ __forceinline__ void f32_body(const SquareArgs& a, int I, int J, int 
 
 // 64-tiles [0, nmain) whole (nmain a multiple of 8), the others as four 32-tiles each.
 typedef F32Cfg<64, 2> F32Main;
-typedef F32Cfg<32, 2> F32Sub;
 __global__ __launch_bounds__(256) void k_square_f32_mix(SquareArgs a, int nmain) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[F32Main::LDS];
     int I, J;
@@ -301,11 +289,12 @@ __global__ __launch_bounds__(256) void k_square_f32_mix(SquareArgs a, int nmain)
     f32_body<32, 2>(a, i, j, slot, lds);
 }
 
-// All of a small problem's 64-tiles as four 32-tiles each, with leading control (see
-// k_square_f64_lead).
+// All of a small problem's 64-tiles as four 32-tiles each, with leading control, in rows of 128
+// or 256 bytes (see k_square_f64_lead).
+template <int ROW>
 __global__ __launch_bounds__(256) void k_square_f32_lead(SquareArgs a, LeadArgs lead) {
     extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];   // lead_bytes
-    __shared__ __attribute__((aligned(16))) unsigned char lds[F32Sub::LDS];
+    __shared__ __attribute__((aligned(16))) unsigned char lds[F32Cfg<32, 2, ROW>::LDS];
     const int u = xcd_tile_index(blockIdx.x, (a.ntiles + 7) >> 3, a.ntiles);
     if (u < 0) return;
     int I, J;
@@ -315,7 +304,7 @@ __global__ __launch_bounds__(256) void k_square_f32_lead(SquareArgs a, LeadArgs 
         if (threadIdx.x < 2) a.parts[2 * u + threadIdx.x] = 0.0;
         return;
     }
-    f32_body<32, 2, true>(a, i, j, u, lds, &lead, dyn);
+    f32_body<32, 2, ROW, true>(a, i, j, u, lds, &lead, dyn);
 }
 
 // grouped: block b computes the 64-tile that the tile map names for it (see TileRef)
@@ -343,7 +332,9 @@ hipError_t launch_square_f32_mix(const SquareArgs& a, hipStream_t s) {
 
 hipError_t launch_square_f32_lead(const SquareArgs& a, const LeadArgs& lead, hipStream_t s) {
     if (!square_leads(64 * a.T) || a.ntiles != 4 * ntiles_upper(a.T) || !a.parts) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_square_f32_lead, dim3((a.ntiles + 7) / 8 * 8), dim3(256), lead_bytes(lead), s, a, lead);
+    const dim3 grid((a.ntiles + 7) / 8 * 8);
+    if (lead_wide(a.T)) hipLaunchKernelGGL(k_square_f32_lead<256>, grid, dim3(256), lead_bytes(lead), s, a, lead);
+    else hipLaunchKernelGGL(k_square_f32_lead<128>, grid, dim3(256), lead_bytes(lead), s, a, lead);
     return hipGetLastError();
 }
 

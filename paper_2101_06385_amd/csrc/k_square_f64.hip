@@ -32,27 +32,28 @@ namespace {
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kBK = 16;            // doubles per row per stage
-constexpr int kRow = kBK * 8;      // 128 bytes
-constexpr int kRPB = 1024 / kRow;  // rows per 1 KB direct-load block (8)
-
-// BT x BT output tile, WM x WN waves, ST LDS stages of 2 BT rows (panels I and J).
-template <int BT, int WM, int WN, int ST>
+// BT x BT output tile, WM x WN waves, ST LDS stages of 2 BT rows (panels I and J)
+// of ROW bytes.
+template <int BT, int WM, int WN, int ST, int ROW = 128>
 struct F64Cfg {
+    static constexpr int BK = ROW / 8;                   // doubles per row per stage
+    static constexpr int CH = ROW / 16;                  // 16-byte chunks per row
+    static constexpr int RPB = 1024 / ROW;               // rows per 1 KB direct-load block
     static constexpr int NW = WM * WN, NT = 64 * NW;
     static constexpr int WTM = BT / WM, WTN = BT / WN;
     static constexpr int MB = WTM / 16, NB = WTN / 16;   // 16 x 16 blocks per wave
-    static constexpr int ARR = BT * kRow;                // bytes of one panel stage
+    static constexpr int ARR = BT * ROW;                 // bytes of one panel stage
     static constexpr int STAGE = 2 * ARR;
-    static constexpr int BPR = BT / kRPB;                // 1 KB blocks per panel stage
+    static constexpr int BPR = BT / RPB;                 // 1 KB blocks per panel stage
     static constexpr int LPW = 2 * BPR / NW;             // direct loads per wave per stage
     static constexpr int LDS = ST * STAGE;
     static constexpr int STRIP = 1024 / BT;              // tile_of strip: 1024 columns
     static_assert(MB >= 1 && NB >= 1 && (2 * BPR) % NW == 0, "tile / wave mismatch");
+    static_assert(ROW == 128 || ROW == 256, "a line of the cache, or two");
     static_assert(LPW * (ST - 1) <= 24, "vmcnt range of wait_vm");
+    // chunk c of row r is stored at c ^ swz(r)
+    static __device__ __forceinline__ int swz(int r) { return (ROW == 128 ? r >> 1 : r) & (CH - 1); }
 };
-
-__device__ inline int swz8(int r) { return (r >> 1) & 7; }
 
 typedef __attribute__((address_space(3))) unsigned char lds_byte;
 __device__ __forceinline__ unsigned lds_addr(const unsigned char* p) {
@@ -84,6 +85,10 @@ __device__ __forceinline__ void wait_vm(int n) {
 }
 #undef SP2_VMCNT
 
+// Every LDS read of this wave has returned, so behind the barrier other waves' direct loads may
+// take its place (__syncthreads alone leaves reads in flight across the barrier).
+__device__ __forceinline__ void stage_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 __device__ inline double wsum(double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
@@ -92,10 +97,11 @@ __device__ inline double wsum(double v) {
 // Output tile (I, J) of edge BT over all of K; t is the tile's slot in a.parts.
 // LEAD: the layer's control at its head (`lead`, lead_bytes of LDS at `dyn`) instead of the next
 // layer's control by the last tile.
-template <int BT, int WM, int WN, int ST, bool LEAD = false>
+template <int BT, int WM, int WN, int ST, int ROW = 128, bool LEAD = false>
 __device__ __forceinline__ void f64_body(const SquareArgs& a, int I, int J, int t, unsigned char* __restrict__ lds,
                                          const LeadArgs* lead = nullptr, unsigned char* __restrict__ dyn = nullptr) {
-    typedef F64Cfg<BT, WM, WN, ST> C;
+    typedef F64Cfg<BT, WM, WN, ST, ROW> C;
+    constexpr int kRow = ROW, kBK = C::BK;
     constexpr int MB = C::MB, NB = C::NB, LPW = C::LPW;
     static_assert(ST >= 2 && ST <= 4, "stages");
     const int np = a.np;
@@ -108,12 +114,12 @@ __device__ __forceinline__ void f64_body(const SquareArgs& a, int I, int J, int 
     const int nsl = ((a.k_all ? np : a.n_real) + kBK - 1) / kBK;
 
     // direct load l of this wave: lane L fills bytes [16 L, 16 L + 16) of a 1 KB block:
-    // panel row q * 8 + L / 8, physical chunk L % 8 = logical chunk (L % 8) ^ swz8(row)
+    // panel row q * RPB + L / CH, physical chunk L % CH = logical chunk (L % CH) ^ swz(row)
     unsigned voff[LPW];
 #pragma unroll
     for (int l = 0; l < LPW; ++l) {
-        const int row = ((wave * LPW + l) % C::BPR) * kRPB + (lane >> 3);
-        voff[l] = (unsigned)row * (unsigned)np * 8u + (unsigned)(((lane & 7) ^ swz8(row)) << 4);
+        const int row = ((wave * LPW + l) % C::BPR) * C::RPB + lane / C::CH;
+        voff[l] = (unsigned)row * (unsigned)np * 8u + (unsigned)(((lane & (C::CH - 1)) ^ C::swz(row)) << 4);
     }
     auto load_one = [&](int l, int buf, int ks) {
         const int j = wave * LPW + l;
@@ -124,20 +130,30 @@ __device__ __forceinline__ void f64_body(const SquareArgs& a, int I, int J, int 
 #pragma unroll
         for (int l = 0; l < LPW; ++l) load_one(l, buf, ks);
     };
-    // fragments of unit h (K 8h .. 8h+7) of the stage in buffer buf: lane reads the 16-byte
-    // logical chunk 4h + lane / 16 of row (block base + lane % 16)
-    auto frags = [&](int buf, int h, f64x2 (&fa)[MB], f64x2 (&fb)[NB]) {
+    // A unit is HU runs of 8 K; a run is one 16-byte read per row and lane, the logical chunk
+    // 4 run + lane / 16 of row (block base + lane % 16).  A wave's next unit is read from LDS behind
+    // the products of this one; with one block per wave (32-tiles) it takes four products to cover
+    // those reads.
+    constexpr int HU = ROW / 128, UNITS = kBK / 8 / HU;
+    struct Frag {
+        f64x2 a[HU][MB], b[HU][NB];
+    };
+    auto frags = [&](int buf, int u, Frag& f) {
         const int r16 = lane & 15;
         const unsigned char* base = lds + buf * C::STAGE;
 #pragma unroll
-        for (int m = 0; m < MB; ++m) {
-            const int row = wm * C::WTM + m * 16 + r16;
-            fa[m] = *(const f64x2*)(base + row * kRow + ((((h << 2) + (lane >> 4)) ^ swz8(row)) << 4));
-        }
+        for (int k = 0; k < HU; ++k) {
+            const int ch = 4 * (HU * u + k) + (lane >> 4);
 #pragma unroll
-        for (int n = 0; n < NB; ++n) {
-            const int row = wn * C::WTN + n * 16 + r16;
-            fb[n] = *(const f64x2*)(base + C::ARR + row * kRow + ((((h << 2) + (lane >> 4)) ^ swz8(row)) << 4));
+            for (int m = 0; m < MB; ++m) {
+                const int row = wm * C::WTM + m * 16 + r16;
+                f.a[k][m] = *(const f64x2*)(base + row * kRow + ((ch ^ C::swz(row)) << 4));
+            }
+#pragma unroll
+            for (int n = 0; n < NB; ++n) {
+                const int row = wn * C::WTN + n * 16 + r16;
+                f.b[k][n] = *(const f64x2*)(base + C::ARR + row * kRow + ((ch ^ C::swz(row)) << 4));
+            }
         }
     };
 
@@ -149,14 +165,14 @@ __device__ __forceinline__ void f64_body(const SquareArgs& a, int I, int J, int 
     // the MFMAs of one unit; with doit the direct loads of stage ks (into buffer buf) are
     // spread between them, so that their issue overlaps the matrix cores (scheduling barriers
     // keep the compiler from regrouping them)
-    auto mma = [&](const f64x2 (&fa)[MB], const f64x2 (&fb)[NB], bool doit, int buf, int ks) {
-        constexpr int NM = 2 * MB * NB;
+    auto mma = [&](const Frag& f, bool doit, int buf, int ks) {
+        constexpr int NM = 2 * HU * MB * NB;
         constexpr int EVERY = NM / LPW;
         static_assert(EVERY >= 1 && NM % LPW == 0, "interleave");
 #pragma unroll
         for (int i = 0; i < NM; ++i) {
-            const int s = i / (MB * NB), m = (i / NB) % MB, n = i % NB;
-            acc[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[m][s], fb[n][s], acc[m][n], 0, 0, 0);
+            const int k = i / (2 * MB * NB), s = (i / (MB * NB)) & 1, m = (i / NB) % MB, n = i % NB;
+            acc[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.a[k][m][s], f.b[k][n][s], acc[m][n], 0, 0, 0);
             if (i % EVERY == EVERY - 1) {
                 __builtin_amdgcn_sched_barrier(0);
                 if (doit) load_one(i / EVERY, buf, ks);
@@ -182,27 +198,28 @@ __device__ __forceinline__ void f64_body(const SquareArgs& a, int I, int J, int 
         wait_vm(0);
         return;
     }
-    f64x2 pa[MB], pb[NB], qa[MB], qb[NB];
-    frags(0, 0, pa, pb);
+    Frag p, q;
+    frags(0, 0, p);
     // stage `next` readable: its loads landed (this wave's), every wave past the barrier
     auto arrive = [&](int next) {
         const int last = (next + ST - 2 < nsl - 1) ? next + ST - 2 : nsl - 1;
         wait_vm((last - next) * LPW);
-        __syncthreads();
+        stage_barrier();
     };
-    // units: two per stage (h = 0, 1); P holds h = 0 of a stage, Q h = 1.  Stage st + ST
-    // refills the buffer of stage st once every wave has read it (after arrive(st + 1)).
+    // units: two per stage; p holds a stage's first, q its second.  Stage st + ST refills the
+    // buffer of stage st once every wave has read it (after arrive(st + 1)).
+    static_assert(UNITS == 2, "two units per stage");
     int st = 0;
     for (; st + 1 < nsl; ++st) {
-        frags(st % ST, 1, qa, qb);
-        mma(pa, pb, false, 0, 0);
+        frags(st % ST, 1, q);
+        mma(p, false, 0, 0);
         arrive(st + 1);
-        frags((st + 1) % ST, 0, pa, pb);
-        mma(qa, qb, st + ST < nsl, st % ST, st + ST);
+        frags((st + 1) % ST, 0, p);
+        mma(q, st + ST < nsl, st % ST, st + ST);
     }
-    frags(st % ST, 1, qa, qb);
-    mma(pa, pb, false, 0, 0);
-    mma(qa, qb, false, 0, 0);
+    frags(st % ST, 1, q);
+    mma(p, false, 0, 0);
+    mma(q, false, 0, 0);
 
     // ------------------------------------------------------------------- epilogue
     if (!LEAD)
@@ -277,7 +294,6 @@ __global__ __launch_bounds__(64 * WM * WN) void k_square_f64(SquareArgs a) {
 
 // 64-tiles [0, nmain) whole (nmain a multiple of 8), the others as four 32-tiles each.
 typedef F64Cfg<64, 2, 2, 2> F64Main;
-typedef F64Cfg<32, 2, 2, 2> F64Sub;
 __global__ __launch_bounds__(256) void k_square_f64_mix(SquareArgs a, int nmain) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[F64Main::LDS];
     int I, J;
@@ -307,11 +323,16 @@ __global__ __launch_bounds__(256) void k_square_f64_mix(SquareArgs a, int nmain)
 
 // All of a small problem's 64-tiles as four 32-tiles each, with leading control: at these sizes
 // the chain of memory trips at a launch's end (sums stored, counted, read back, state written)
-// costs more (n = 256: 12.1 us per layer with the control in the last tile, 10.9 us
-// here).
+// costs more (n = 256: 12.1 us per layer with the control in the last tile, 10.9 us here).  With
+// few workgroups per CU a stage lasts as long as its direct loads are under way (about 1000
+// cycles, for 256 of products), so while there are at most two (lead_wide) the rows of a stage
+// are 256 bytes in place of 128: n = 256 9.0 us, 513 15.2 (18.6), 777 22.6 (25.7); at
+// n = 1024 both take 34 us, and at 1300 the larger stages' LDS leaves fewer workgroups on a CU
+// (65 against 55 us).  FP32: n = 256 7.5 (8.1), 513 11.3 (12.5), 777 17.7 (17.7), 1024 24.3 (23.4).
+template <int ROW>
 __global__ __launch_bounds__(256) void k_square_f64_lead(SquareArgs a, LeadArgs lead) {
     extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];   // lead_bytes
-    __shared__ __attribute__((aligned(16))) unsigned char lds[F64Sub::LDS];
+    __shared__ __attribute__((aligned(16))) unsigned char lds[F64Cfg<32, 2, 2, 2, ROW>::LDS];
     const int u = xcd_tile_index(blockIdx.x, (a.ntiles + 7) >> 3, a.ntiles);
     if (u < 0) return;
     int I, J;
@@ -321,7 +342,7 @@ __global__ __launch_bounds__(256) void k_square_f64_lead(SquareArgs a, LeadArgs 
         if (threadIdx.x < 2) a.parts[2 * u + threadIdx.x] = 0.0;
         return;
     }
-    f64_body<32, 2, 2, 2, true>(a, i, j, u, lds, &lead, dyn);
+    f64_body<32, 2, 2, 2, ROW, true>(a, i, j, u, lds, &lead, dyn);
 }
 
 // grouped: block b computes the 64-tile that the tile map names for it (see TileRef)
@@ -364,9 +385,12 @@ bool square_leads(int edge) {
     square_mix_grid(edge, &T, &nmain, &ntiles);
     return nmain == 0;
 }
+bool lead_wide(int T) { return 4 * ntiles_upper(T) <= 2 * kMixCus; }
 hipError_t launch_square_f64_lead(const SquareArgs& a, const LeadArgs& lead, hipStream_t s) {
     if (!square_leads(64 * a.T) || a.ntiles != 4 * ntiles_upper(a.T) || !a.parts) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_square_f64_lead, dim3((a.ntiles + 7) / 8 * 8), dim3(256), lead_bytes(lead), s, a, lead);
+    const dim3 grid((a.ntiles + 7) / 8 * 8);
+    if (lead_wide(a.T)) hipLaunchKernelGGL(k_square_f64_lead<256>, grid, dim3(256), lead_bytes(lead), s, a, lead);
+    else hipLaunchKernelGGL(k_square_f64_lead<128>, grid, dim3(256), lead_bytes(lead), s, a, lead);
     return hipGetLastError();
 }
 

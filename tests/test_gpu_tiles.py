@@ -138,8 +138,9 @@ def test_one_workgroup_solve_reports_bad_input():
         assert i["status_name"] == i1["status_name"] == name
 
 
-# FP64 layers with the control at their head (every 64-tile cut: n <= 1408) and in their last tile
-@pytest.mark.parametrize("n", [65, 100, 257, 1408, 1409])
+# FP64 layers with the control at their head (every 64-tile cut: n <= 1408, stages in rows of 256 bytes
+# up to 960) and in their last tile
+@pytest.mark.parametrize("n", [65, 100, 257, 960, 961, 1408, 1409])
 def test_fp64_layers_equal_128_tile_layers(n):
     w = wl.gapped(1200 + n, n, n // 2, device=DEV if n > 1000 else None)
     h = torch.from_numpy(w.h).to(DEV)
@@ -151,9 +152,10 @@ def test_fp64_layers_equal_128_tile_layers(n):
             assert abs(a - b) <= 2 * (n * n + 1) * 2.0**-53 * n   # sums of n^2 terms of a matrix with norm <= sqrt(n)
 
 
-# FP32 layers: with the control at their head (n <= 1408) or in their last tile (1409, 1472: whole
-# 64-tiles and cut ones) against the register-staged kernel with control launches
-@pytest.mark.parametrize("n", [65, 100, 257, 1408, 1409, 1472])
+# FP32 layers: with the control at their head (n <= 1408; stages in rows of 256 bytes up to 960) or in
+# their last tile (1409, 1472: whole 64-tiles and cut ones) against the register-staged kernel with
+# control launches
+@pytest.mark.parametrize("n", [65, 100, 257, 960, 961, 1408, 1409, 1472])
 def test_fp32_layers_equal_register_staged_layers(n):
     w = wl.gapped(1300 + n, n, n // 2, device=DEV if n > 1000 else None)
     h = torch.from_numpy(w.h).to(DEV)
