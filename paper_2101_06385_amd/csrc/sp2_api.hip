@@ -881,8 +881,6 @@ int sp2_fermi_apply(const double* dH, int ldh, double* dD, int ldd, int n, int l
     double* dcoef64 = (double*)(ws + off_coef + align_up(sizeof(float) * 3 * SP2_MAX_LAYERS));
     DevState init = initial_state(n, 0, 0.0, o, p);
     SP2_TRY(launch_state_init(st, init, s));
-    SP2_TRY(launch_store_coefs(dcoef, coef, 3 * layers, s));
-    SP2_TRY(launch_store_coefs64(dcoef64, coef, 3 * layers, s));
     // The layers' outputs go round in every buffer of state matrices that the workspace has (the
     // FP64 refinement buffers hold two FP32 matrices each) and are read out when all are full.
     const bool wide = o.precision == SP2_FP64;
@@ -909,7 +907,16 @@ int sp2_fermi_apply(const double* dH, int ldh, double* dD, int ldd, int n, int l
     void* P[2][2] = {{p.split ? ws + p.off_p[0][0] : nullptr, p.split ? ws + p.off_p[0][1] : nullptr},
                      {p.split ? ws + p.off_p[1][0] : nullptr, p.split ? ws + p.off_p[1][1] : nullptr}};
     double* init_parts = (double*)(ws + p.off_init_parts);
-    SP2_TRY(launch_init_np(dH, ldh, st, p.np, o.precision, S[0], P[0][0], P[0][1], p.scale_log2, init_parts, s));
+    // layers on fragment-major planes with row-major states, as the network's
+    const bool fm = fm_wanted(p.split, p.tile_main, p.kernel, p.np) && !p.sk_capable;
+    if (fm) {
+        SP2_TRY(launch_init_np(dH, ldh, st, p.np, SP2_FP32, S[0], nullptr, nullptr, 0, init_parts, s));
+        SP2_TRY(launch_split_fm((const float*)S[0], P[0][0], P[0][1], p.np, o.precision, p.scale_log2, s));
+    } else {
+        SP2_TRY(launch_init_np(dH, ldh, st, p.np, o.precision, S[0], P[0][0], P[0][1], p.scale_log2, init_parts, s));
+    }
+    SP2_TRY(launch_store_coefs(dcoef, coef, 3 * layers, s));
+    if (o.precision == SP2_FP64) SP2_TRY(launch_store_coefs64(dcoef64, coef, 3 * layers, s));
     if (const int rc = read_out(S[0], c[0], false)) return rc;
     StreamK sk;
     memset(&sk, 0, sizeof(sk));
@@ -933,8 +940,29 @@ int sp2_fermi_apply(const double* dH, int ldh, double* dD, int ldd, int n, int l
     a.per = p.main_per;
     a.out_scale = ldexpf(1.f, -2 * p.scale_log2);
     a.in_scale = ldexpf(1.f, p.scale_log2);
+    FmArgs f;
+    memset(&f, 0, sizeof(f));
+    f.ld = p.np;
+    f.pstride = fm_pstride(p.np);
+    f.ku = (n + 15) / 16;
+    f.n_real = n;
+    square_split_grid(64, round_up(n, 64), &f.T, &f.ntiles, &f.per);
+    f.out_scale = a.out_scale;
+    f.in_scale = a.in_scale;
     for (int k = 0; k < layers; ++k) {
         const int in = k & 1, out = in ^ 1;
+        if (fm) {
+            f.x0 = P[in][0];
+            f.x1 = P[in][1];
+            f.p0_out = P[out][0];
+            f.p1_out = P[out][1];
+            f.s_in = (const float*)S[k % slots];
+            f.s_out = (float*)S[(k + 1) % slots];
+            f.coef = dcoef + 3 * k;
+            SP2_TRY(launch_fm(o.precision, fm_variant(p.tile_main, f.ntiles), f, s));
+            if (const int rc = read_out(S[(k + 1) % slots], -c[k + 1], k + 1 == layers)) return rc;
+            continue;
+        }
         a.coef = dcoef + 3 * k;
         a.coef64 = o.precision == SP2_FP64 ? dcoef64 + 3 * k : nullptr;
         a.x0 = p.split ? P[in][0] : S[k % slots];

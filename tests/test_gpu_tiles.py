@@ -270,3 +270,16 @@ def test_fragment_major_network_layers_equal_per_tile_layers(prec, n):
             first = (dw, db, dc, g0)
         else:   # recomputed layers have the forward's bits
             assert all(torch.equal(p, q) for p, q in zip(first, (dw, db, dc, g0)))
+
+
+@pytest.mark.parametrize("prec", ["fp16x2", "bf16x2"])
+@pytest.mark.parametrize("n", [1, 33, 65, 131, 700, 2050])
+def test_fragment_major_fermi_layers_equal_register_staged_layers(prec, n):
+    h = _sym(n, 2000 + n, torch.float64)
+    theta = np.array([(0.9, 0.0, 0.1), (-1.0, 2.0, 0.0), (1.0, -0.5, 0.25)])
+    c = [0.5, -0.25, 0.125, 0.75]
+    need = sp2.fermi_workspace_size(n, (-3.0, 3.0), prec, tile=64)
+    ws = sp2.alloc_workspace(need, DEV).fill_(255)   # NaN wherever a kernel reads what none has written
+    d, obs = sp2.fermi_apply(h, theta, c, (-3.0, 3.0), precision=prec, tile=64, workspace=ws)
+    d8, obs8 = sp2.fermi_apply(h, theta, c, (-3.0, 3.0), precision=prec, tile=64, kernel=8)
+    assert torch.equal(d, d8) and obs == obs8
