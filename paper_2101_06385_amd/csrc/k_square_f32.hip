@@ -260,20 +260,15 @@ __device__ __forceinline__ void f32_body(const SquareArgs& a, int I, int J, int 
     }
 }
 
-// 64-tiles [0, nmain) whole (nmain a multiple of 8), the others as four 32-tiles each.
 typedef F32Cfg<64, 2> F32Main;
-__global__ __launch_bounds__(256) void k_square_f32_mix(SquareArgs a, int nmain) {
-    __shared__ __attribute__((aligned(16))) unsigned char lds[F32Main::LDS];
-    int I, J;
-    if ((int)blockIdx.x < nmain) {
-        const int t = (blockIdx.x & 7) * (nmain >> 3) + (blockIdx.x >> 3);
-        tile_of(t, a.T, F32Main::STRIP, &I, &J);
-        f32_body<64, 2>(a, I, J, t, lds);
-        return;
-    }
+
+// Cut tile u of those behind `nmain` whole 64-tiles (blocks from nmain on).
+template <int ROW>
+__device__ __forceinline__ void f32_cut(const SquareArgs& a, int nmain, unsigned char* lds) {
     const int nsub = a.ntiles - nmain;
     const int u = xcd_tile_index(blockIdx.x - nmain, (nsub + 7) >> 3, nsub);
     if (u < 0) return;
+    int I, J;
     tile_of(nmain + (u >> 2), a.T, F32Main::STRIP, &I, &J);
     const int i = 2 * I + ((u >> 1) & 1), j = 2 * J + (u & 1), slot = nmain + u;
     if (i > j) {   // below the diagonal: its mirror computes it
@@ -286,7 +281,26 @@ __global__ __launch_bounds__(256) void k_square_f32_mix(SquareArgs a, int nmain)
         tile_done<256>(a, slot, (double*)lds, (int*)(lds + 4096));
         return;
     }
-    f32_body<32, 2>(a, i, j, slot, lds);
+    f32_body<32, 2, ROW>(a, i, j, slot, lds);
+}
+
+// 64-tiles [0, nmain) whole (nmain a multiple of 8), the others as four 32-tiles each.
+__global__ __launch_bounds__(256) void k_square_f32_mix(SquareArgs a, int nmain) {
+    __shared__ __attribute__((aligned(16))) unsigned char lds[F32Main::LDS];
+    int I, J;
+    if ((int)blockIdx.x < nmain) {
+        const int t = (blockIdx.x & 7) * (nmain >> 3) + (blockIdx.x >> 3);
+        tile_of(t, a.T, F32Main::STRIP, &I, &J);
+        f32_body<64, 2>(a, I, J, t, lds);
+        return;
+    }
+    f32_cut<128>(a, nmain, lds);
+}
+// Every 64-tile cut, stages in rows of ROW bytes.
+template <int ROW>
+__global__ __launch_bounds__(256) void k_square_f32_cut(SquareArgs a) {
+    __shared__ __attribute__((aligned(16))) unsigned char lds[F32Cfg<32, 2, ROW>::LDS];
+    f32_cut<ROW>(a, 0, lds);
 }
 
 // All of a small problem's 64-tiles as four 32-tiles each, with leading control, in rows of 128
@@ -326,14 +340,17 @@ hipError_t launch_square_f32_mix(const SquareArgs& a, hipStream_t s) {
     square_mix_grid(64 * a.T, &T, &nmain, &ntiles);
     if (ntiles != a.ntiles || a.np % 64 || 64 * T > a.np) return hipErrorInvalidValue;
     const int nsub = ntiles - nmain;
-    hipLaunchKernelGGL(k_square_f32_mix, dim3(nmain + (nsub + 7) / 8 * 8), dim3(256), 0, s, a, nmain);
+    const dim3 grid(nmain + (nsub + 7) / 8 * 8);
+    if (nmain > 0) hipLaunchKernelGGL(k_square_f32_mix, grid, dim3(256), 0, s, a, nmain);
+    else if (few_cut_tiles(a.T)) hipLaunchKernelGGL(k_square_f32_cut<256>, grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(k_square_f32_cut<128>, grid, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_square_f32_lead(const SquareArgs& a, const LeadArgs& lead, hipStream_t s) {
     if (!square_leads(64 * a.T) || a.ntiles != 4 * ntiles_upper(a.T) || !a.parts) return hipErrorInvalidValue;
     const dim3 grid((a.ntiles + 7) / 8 * 8);
-    if (lead_wide(a.T)) hipLaunchKernelGGL(k_square_f32_lead<256>, grid, dim3(256), lead_bytes(lead), s, a, lead);
+    if (few_cut_tiles(a.T)) hipLaunchKernelGGL(k_square_f32_lead<256>, grid, dim3(256), lead_bytes(lead), s, a, lead);
     else hipLaunchKernelGGL(k_square_f32_lead<128>, grid, dim3(256), lead_bytes(lead), s, a, lead);
     return hipGetLastError();
 }

@@ -292,20 +292,15 @@ __global__ __launch_bounds__(64 * WM * WN) void k_square_f64(SquareArgs a) {
     f64_body<BT, WM, WN, ST>(a, I, J, t, lds);
 }
 
-// 64-tiles [0, nmain) whole (nmain a multiple of 8), the others as four 32-tiles each.
 typedef F64Cfg<64, 2, 2, 2> F64Main;
-__global__ __launch_bounds__(256) void k_square_f64_mix(SquareArgs a, int nmain) {
-    __shared__ __attribute__((aligned(16))) unsigned char lds[F64Main::LDS];
-    int I, J;
-    if ((int)blockIdx.x < nmain) {
-        const int t = (blockIdx.x & 7) * (nmain >> 3) + (blockIdx.x >> 3);
-        tile_of(t, a.T, F64Main::STRIP, &I, &J);
-        f64_body<64, 2, 2, 2>(a, I, J, t, lds);
-        return;
-    }
+
+// Cut tile u of those behind `nmain` whole 64-tiles (blocks from nmain on).
+template <int ROW>
+__device__ __forceinline__ void f64_cut(const SquareArgs& a, int nmain, unsigned char* lds) {
     const int nsub = a.ntiles - nmain;
     const int u = xcd_tile_index(blockIdx.x - nmain, (nsub + 7) >> 3, nsub);
     if (u < 0) return;
+    int I, J;
     tile_of(nmain + (u >> 2), a.T, F64Main::STRIP, &I, &J);
     const int i = 2 * I + ((u >> 1) & 1), j = 2 * J + (u & 1), slot = nmain + u;
     if (i > j) {   // below the diagonal: its mirror computes it
@@ -318,14 +313,34 @@ __global__ __launch_bounds__(256) void k_square_f64_mix(SquareArgs a, int nmain)
         tile_done<256>(a, slot, (double*)lds, (int*)(lds + 4096));
         return;
     }
-    f64_body<32, 2, 2, 2>(a, i, j, slot, lds);
+    f64_body<32, 2, 2, 2, ROW>(a, i, j, slot, lds);
+}
+
+// 64-tiles [0, nmain) whole (nmain a multiple of 8), the others as four 32-tiles each.
+__global__ __launch_bounds__(256) void k_square_f64_mix(SquareArgs a, int nmain) {
+    __shared__ __attribute__((aligned(16))) unsigned char lds[F64Main::LDS];
+    int I, J;
+    if ((int)blockIdx.x < nmain) {
+        const int t = (blockIdx.x & 7) * (nmain >> 3) + (blockIdx.x >> 3);
+        tile_of(t, a.T, F64Main::STRIP, &I, &J);
+        f64_body<64, 2, 2, 2>(a, I, J, t, lds);
+        return;
+    }
+    f64_cut<128>(a, nmain, lds);
+}
+// Every 64-tile cut, stages in rows of ROW bytes (see k_square_f64_lead).  As the refinement
+// of a solve, two layers, against cut tiles in the LDS of whole ones: n = 256 5 us less, 513 8, 777 6.
+template <int ROW>
+__global__ __launch_bounds__(256) void k_square_f64_cut(SquareArgs a) {
+    __shared__ __attribute__((aligned(16))) unsigned char lds[F64Cfg<32, 2, 2, 2, ROW>::LDS];
+    f64_cut<ROW>(a, 0, lds);
 }
 
 // All of a small problem's 64-tiles as four 32-tiles each, with leading control: at these sizes
 // the chain of memory trips at a launch's end (sums stored, counted, read back, state written)
 // costs more (n = 256: 12.1 us per layer with the control in the last tile, 10.9 us here).  With
 // few workgroups per CU a stage lasts as long as its direct loads are under way (about 1000
-// cycles, for 256 of products), so while there are at most two (lead_wide) the rows of a stage
+// cycles, for 256 of products), so while there are at most two (few_cut_tiles) the rows of a stage
 // are 256 bytes in place of 128: n = 256 9.0 us, 513 15.2 (18.6), 777 22.6 (25.7); at
 // n = 1024 both take 34 us, and at 1300 the larger stages' LDS leaves fewer workgroups on a CU
 // (65 against 55 us).  FP32: n = 256 7.5 (8.1), 513 11.3 (12.5), 777 17.7 (17.7), 1024 24.3 (23.4).
@@ -376,7 +391,10 @@ hipError_t launch_square_f64_mix(const SquareArgs& a, hipStream_t s) {
     square_mix_grid(64 * a.T, &T, &nmain, &ntiles);
     if (ntiles != a.ntiles || a.np % 64 || 64 * T > a.np) return hipErrorInvalidValue;
     const int nsub = ntiles - nmain;
-    hipLaunchKernelGGL(k_square_f64_mix, dim3(nmain + (nsub + 7) / 8 * 8), dim3(256), 0, s, a, nmain);
+    const dim3 grid(nmain + (nsub + 7) / 8 * 8);
+    if (nmain > 0) hipLaunchKernelGGL(k_square_f64_mix, grid, dim3(256), 0, s, a, nmain);
+    else if (few_cut_tiles(a.T)) hipLaunchKernelGGL(k_square_f64_cut<256>, grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(k_square_f64_cut<128>, grid, dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -385,11 +403,11 @@ bool square_leads(int edge) {
     square_mix_grid(edge, &T, &nmain, &ntiles);
     return nmain == 0;
 }
-bool lead_wide(int T) { return 4 * ntiles_upper(T) <= 2 * kMixCus; }
+bool few_cut_tiles(int T) { return 4 * ntiles_upper(T) <= 2 * kMixCus; }
 hipError_t launch_square_f64_lead(const SquareArgs& a, const LeadArgs& lead, hipStream_t s) {
     if (!square_leads(64 * a.T) || a.ntiles != 4 * ntiles_upper(a.T) || !a.parts) return hipErrorInvalidValue;
     const dim3 grid((a.ntiles + 7) / 8 * 8);
-    if (lead_wide(a.T)) hipLaunchKernelGGL(k_square_f64_lead<256>, grid, dim3(256), lead_bytes(lead), s, a, lead);
+    if (few_cut_tiles(a.T)) hipLaunchKernelGGL(k_square_f64_lead<256>, grid, dim3(256), lead_bytes(lead), s, a, lead);
     else hipLaunchKernelGGL(k_square_f64_lead<128>, grid, dim3(256), lead_bytes(lead), s, a, lead);
     return hipGetLastError();
 }

@@ -240,7 +240,7 @@ void square_mix_grid(int edge, int* T, int* nmain, int* ntiles);
 hipError_t launch_square_f64_mix(const SquareArgs& a, hipStream_t s);
 // the same with leading control, where every 64-tile is cut (a.parts: not the buffer that `lead` reads)
 bool square_leads(int edge);
-bool lead_wide(int T);   // its stages in rows of 256 bytes
+bool few_cut_tiles(int T);   // at most two workgroups per CU: stages in rows of 256 bytes
 hipError_t launch_square_f64_lead(const SquareArgs& a, const LeadArgs& lead, hipStream_t s);
 // grouped FP64 layer over a map of 64-tiles (see TileRef), grid 8 per
 hipError_t launch_square_f64_g(const SquareArgs* descs, const TileRef* map, int per, hipStream_t s);
