@@ -9,8 +9,8 @@
 //    ones so that the end of the launch is spread over the chip (k_square_f64_mix).
 //    One layer, against the 8-wave 128 x 128 workgroups with one per CU (and their
 //    persistent form with a split-K tail) used before: n = 256 17 -> 7.3 us, 832 128 -> 25 us,
-//    2112 290 -> 167 us, 4096 1265 -> 1036 us (66 TFLOP/s), 5120 2233 -> 2015 us, 8192
-//    8.90 -> 8.74 ms (there the panels' L2 misses count too).
+//    2112 290 -> 167 us, 4096 1265 -> 1030 us (67 TFLOP/s), 5120 2233 -> 2015 us, 8192
+//    8.90 -> 8.12 ms (68 TFLOP/s).
 //  * K-stages of 16 doubles: each row of a stage is one 128-byte line.  The two row
 //    panels (I and J: X is symmetric, so both operands are K-contiguous rows) go straight
 //    from global memory into LDS with global_load_lds_dwordx4 (16 bytes per lane, a
@@ -47,7 +47,10 @@ struct F64Cfg {
     static constexpr int BPR = BT / RPB;                 // 1 KB blocks per panel stage
     static constexpr int LPW = 2 * BPR / NW;             // direct loads per wave per stage
     static constexpr int LDS = ST * STAGE;
-    static constexpr int STRIP = 1024 / BT;              // tile_of strip: 1024 columns
+    // tile_of strip of 384 columns: the tiles that an XCD runs at a time drift apart in K, and narrow
+    // blocks of rows keep more of their panels in its L2 (n = 8192: 8.12 ms per layer, 8.44 with
+    // strips of 1024 columns, 8.18 with 512, 8.21 with 192; equal within 1 % up to n = 7000)
+    static constexpr int STRIP = BT == 128 ? 8 : 384 / BT;
     static_assert(MB >= 1 && NB >= 1 && (2 * BPR) % NW == 0, "tile / wave mismatch");
     static_assert(ROW == 128 || ROW == 256, "a line of the cache, or two");
     static_assert(LPW * (ST - 1) <= 24, "vmcnt range of wait_vm");
