@@ -60,8 +60,10 @@ SK_VARIANTS = {256: [(4, 16, 4, 0), (8, 16, 4, 0), (4, 32, 2, 0), (8, 32, 2, 0),
                128: [(4, 32, 4, 0), (4, 64, 2, 0), (4, 16, 4, 0), (4, 32, 2, 0), (4, 64, 2, 1), (4, 32, 2, 1)]}
 
 
-def kernel_name(precision, tile, kernel):
-    """Name of the squaring kernel a call used (as reported in sp2_info.kernel)."""
+def kernel_name(precision, tile, kernel, n, n_padded):
+    """Name of the squaring kernel a call used (from sp2_info and the library's size rules)."""
+    t64 = -(-n // 64)
+    ntiles64 = t64 * (t64 + 1) // 2
     if precision in ("fp16x2", "bf16x2"):
         t16 = "_Float16" if precision == "fp16x2" else "__bf16"
         if kernel >= 2:
@@ -70,10 +72,12 @@ def kernel_name(precision, tile, kernel):
             mb = tile // 64
             nb = tile // (32 * wn)
             return "k_square_sk<%s, 2, %d, %d, %d, %d, %d, %d>" % (t16, wn, mb, nb, sk, st, rp)
+        if kernel == 1 and tile <= 128 and n_padded < 3072:
+            return ("k_square_fm1<%s, 4, 4, %d>" if ntiles64 > 512 else "k_square_fm<%s, 4, 2, %d>") % (t16, tile == 128)
         if kernel == 1 and tile in (128, 256):
             return "k_square_dp<%s, 2, %d, %d, 2, 32, 2>" % (t16, 4 if tile == 256 else 2, tile // 64)
         return "k_square_split<%s, %d>" % (t16, tile)
-    return "k_square_plain<%s, %d>" % ("double" if precision == "fp64" else "float", tile)
+    return "k_square_%s_%s" % ("f64" if precision == "fp64" else "f32", "lead" if ntiles64 < 256 else "mix")
 
 
 def kernel_sources_digest():
@@ -194,7 +198,7 @@ def main():
     sq_mean = float(np.mean(sq)) if sq else float("nan")
     achieved = f_layer / (sq_mean * 1e-3) / 1e12
     peak = PEAK_FP16_TFLOPS if split else (PEAK_FP64_TFLOPS if args.precision == "fp64" else 157.3)
-    kname = kernel_name(args.precision, info["tile"], info["kernel"])
+    kname = kernel_name(args.precision, info["tile"], info["kernel"], n, info["n_padded"])
     traffic = recorded_traffic(kname, n)
     log("layers m=%d squarings=%d loop %.2f ms (%.1f TFLOP/s) square kernel %.3f ms (%.1f TFLOP/s, %s) "
         "refine %.2f ms status %s; whole call %.1f TFLOP/s" % (info["layers"], k, loop_ms, loop_tflops, sq_mean,

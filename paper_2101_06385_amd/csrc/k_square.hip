@@ -21,8 +21,10 @@
 //   coefficients, writes Y in FP32 and re-splits it into the planes of the next layer,
 //   and reduces Tr Y and ||Y||_F^2 in FP64 (the traces that drive the next sigma).
 // k_square_plain: the same layer with X in FP64 (v_mfma_f64_16x16x4_f64) or FP32
-//   (v_mfma_f32_32x32x2_f32); used for the FP64/FP32 recursions and for the FP64
-//   refinement layers.
+//   (v_mfma_f32_32x32x2_f32).
+//
+// Both are the register-staged forms: kernel option 8 of the split modes, option 1 of the
+// FP64 and FP32 modes, and single FP64 / FP32 layers on buffers that are not 16-byte aligned.
 //
 // Staging: the K loop streams BK-deep slices of the row panels through LDS, double
 // buffered; global loads of slice k+1 are in flight while slice k feeds the matrix

@@ -1,8 +1,8 @@
 // Host side of libsp2: argument checks, workspace layout and the launch sequence of
-// Alg. 1.  Control stays on the device: every layer is a control kernel (IdErr_n,
-// sigma_n, stopping tests) followed by a squaring kernel that reads its coefficients
-// and a skip flag from the device state, so the host enqueues the whole recursion
-// without reading anything back.
+// Alg. 1.  Control stays on the device: IdErr_n, sigma_n and the stopping tests of a layer
+// run in the last tile of the squaring launch before it, at the head of its own launch, or
+// (register-staged kernels) in a control kernel between the two, so the host enqueues the
+// whole recursion without reading anything back.
 #include "sp2_internal.h"
 
 #include <math.h>
