@@ -4,13 +4,17 @@
 //  * sp2_autotune(n, precision): one split-precision layer Y = X^2 of an n x n symmetric
 //    synthetic matrix (entries from a counter hash, zero padding), timed with HIP events for
 //    every schedule that can run at this size: tiles 64 (small n), 128, 256 with one
-//    workgroup per tile, and the persistent variants that have at least one tile per
+//    workgroup per tile (on fragment-major planes where a solve uses them), and the persistent
+//    variants that have at least one tile per
 //    workgroup.  Key: (device, precision, n rounded up to 256).
 //  * sp2_autotune_batched: the batched solve itself on the caller's problems, once per
 //    grouped-kernel tile (64, 128).  Key: (device, precision, the multiset of sizes).
 //
 // The table is guarded by a mutex; entries are only ever replaced by a later measurement.
 #include "sp2_internal.h"
+
+#include <math.h>
+#include <string.h>
 
 #include <algorithm>
 #include <chrono>
@@ -87,6 +91,34 @@ std::vector<Candidate> candidates(int n) {
 
 inline size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
+// A per-tile candidate that a solve of this size runs on fragment-major planes is timed so.
+bool on_fm(const Candidate& c, int np) { return fm_wanted(true, c.tile, c.kernel, np); }
+size_t fm_plane_bytes(int np) { return align256((size_t)2 * np * plane_ld(np)); }
+hipError_t fm_layer(const Candidate& c, int n, int np, int precision, const float* x, float* y, char* ws, hipStream_t s) {
+    const int scale_log2 = precision == SP2_FP16X2 ? 12 : 0;
+    char* planes = ws + 256;
+    const size_t pb = fm_plane_bytes(np);
+    FmArgs f;
+    memset(&f, 0, sizeof(f));
+    f.x0 = planes;
+    f.x1 = planes + pb;
+    f.p0_out = planes + 2 * pb;
+    f.p1_out = planes + 3 * pb;
+    f.s_in = x;
+    f.s_out = y;
+    f.coef = (const float*)ws;
+    f.ld = np;
+    f.pstride = fm_pstride(np);
+    f.ku = (n + 15) / 16;
+    f.n_real = n;
+    square_split_grid(64, (n + 63) / 64 * 64, &f.T, &f.ntiles, &f.per);
+    f.out_scale = ldexpf(1.f, -2 * scale_log2);
+    f.in_scale = ldexpf(1.f, scale_log2);
+    hipError_t e = launch_set3((float*)ws, 1.f, 0.f, 0.f, s);
+    if (e == hipSuccess) e = launch_split_fm(x, planes, planes + pb, np, precision, scale_log2, s);
+    return e == hipSuccess ? launch_fm(precision, fm_variant(c.tile, f.ntiles), f, s) : e;
+}
+
 }  // namespace
 
 unsigned long long tune_key_single(int n) { return (unsigned long long)((n + 255) / 256 * 256); }
@@ -130,7 +162,11 @@ size_t sp2_autotune_workspace_size(int n, int precision) {
     if (n <= 0 || n > 65536 || (precision != SP2_FP16X2 && precision != SP2_BF16X2)) return 0;
     const size_t np = (size_t)(n + 255) / 256 * 256;
     size_t ws = 0;
-    for (const Candidate& c : candidates(n)) ws = std::max(ws, sp2_square_workspace_size(n, precision, c.tile, c.kernel));
+    for (const Candidate& c : candidates(n)) {
+        const int cnp = sp2_square_padded(n, precision, c.tile);
+        ws = std::max(ws, on_fm(c, cnp) ? 256 + 4 * fm_plane_bytes(cnp)
+                                        : sp2_square_workspace_size(n, precision, c.tile, c.kernel));
+    }
     return 2 * align256(4 * np * np) + ws;
 }
 
@@ -167,14 +203,17 @@ int sp2_autotune(int n, int precision, int reps, int* tile, int* kernel, float* 
             st = SP2_EDEVICE;
             break;
         }
-        st = sp2_square(x, y, n, precision, c.tile, c.kernel, -1, 1.f, 0.f, 0.f, nullptr, sq_ws, sq_bytes, stream);
+        auto layer = [&]() -> int {
+            if (on_fm(c, np)) return fm_layer(c, n, np, precision, x, y, sq_ws, s) == hipSuccess ? SP2_OK : SP2_EDEVICE;
+            return sp2_square(x, y, n, precision, c.tile, c.kernel, -1, 1.f, 0.f, 0.f, nullptr, sq_ws, sq_bytes, stream);
+        };
+        st = layer();
         if (st != SP2_OK) break;
         if (hipEventRecord(e0, s) != hipSuccess) {
             st = SP2_EDEVICE;
             break;
         }
-        for (int r = 0; r < reps && st == SP2_OK; ++r)
-            st = sp2_square(x, y, n, precision, c.tile, c.kernel, -1, 1.f, 0.f, 0.f, nullptr, sq_ws, sq_bytes, stream);
+        for (int r = 0; r < reps && st == SP2_OK; ++r) st = layer();
         if (st != SP2_OK) break;
         float t = 0.f;
         if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
