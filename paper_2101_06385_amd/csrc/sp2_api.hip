@@ -364,6 +364,8 @@ struct ChunkEvents {
 };
 
 // HIP events recorded between the kernels of one call (timed entry point only).
+// Those of the layers only take times: without the system-scope fences a layer that returns at
+// once reads 4.4 us in place of 6 (a working one of n = 2100 44.6 in place of 46.0).
 struct Events {
     bool on = false, ok = true;
     int layers = 0, launched = 0;
@@ -375,7 +377,8 @@ struct Events {
         hipEvent_t* all[] = {&start, &prep, &loop_end, &end, &ref[0], &ref[1], &ref[2]};
         for (hipEvent_t* e : all) ok = ok && hipEventCreate(e) == hipSuccess;
         for (int k = 1; k <= layers; ++k)
-            ok = ok && hipEventCreate(&sq_b[k]) == hipSuccess && hipEventCreate(&sq_e[k]) == hipSuccess;
+            ok = ok && hipEventCreateWithFlags(&sq_b[k], hipEventDisableSystemFence) == hipSuccess &&
+                 hipEventCreateWithFlags(&sq_e[k], hipEventDisableSystemFence) == hipSuccess;
     }
     ~Events() {
         if (!on) return;
