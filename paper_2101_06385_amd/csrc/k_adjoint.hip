@@ -21,6 +21,7 @@
 //    B alike.  Rows are XOR-swizzled in 16-byte chunks, so that 16 lanes hit distinct banks.
 //  * The sums of the layer's partials ride in the next launch (its last workgroup), so a layer is
 //    one launch.
+#include "lds_stage.h"
 #include "sp2_internal.h"
 
 namespace sp2 {
@@ -66,10 +67,6 @@ __device__ __forceinline__ void wait_vm(int n) {
     else SP2_VMCNT(0);
 }
 #undef SP2_VMCNT
-
-// Every LDS read of this wave has returned, so behind the barrier other waves' direct loads may
-// take its place (__syncthreads alone leaves reads in flight across the barrier).
-__device__ __forceinline__ void stage_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 __device__ inline double wsum(double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

@@ -14,6 +14,7 @@
 //    n = 4096), a wave of a 32-tile one block.
 //  * Lanes read the K they take, 4 t + lane / 16.  The loop over stages is unrolled until buffers
 //    and fragment sets are back, so that LDS addresses are constants (550 -> 510 us).
+#include "lds_stage.h"
 #include "sp2_control.h"
 #include "sp2_internal.h"
 
@@ -73,10 +74,6 @@ __device__ __forceinline__ void wait_vm(int n) {
     else SP2_VMCNT(0);
 }
 #undef SP2_VMCNT
-
-// Every LDS read of this wave has returned, so behind the barrier other waves' direct loads may
-// take its place (__syncthreads alone leaves reads in flight across the barrier).
-__device__ __forceinline__ void stage_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 __device__ inline double wsum(double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

@@ -23,6 +23,7 @@
 //    in its K lane j = lane / 16, the K index 8 h + 2 j + s.  A and B use the same map, so
 //    every product term appears once; one 16-byte read then feeds two MFMAs.  Every tile
 //    edge runs the same chain of products per element, so the tiling changes no bit.
+#include "lds_stage.h"
 #include "sp2_control.h"
 #include "sp2_internal.h"
 
@@ -87,10 +88,6 @@ __device__ __forceinline__ void wait_vm(int n) {
     else SP2_VMCNT(0);
 }
 #undef SP2_VMCNT
-
-// Every LDS read of this wave has returned, so behind the barrier other waves' direct loads may
-// take its place (__syncthreads alone leaves reads in flight across the barrier).
-__device__ __forceinline__ void stage_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 __device__ inline double wsum(double v) {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

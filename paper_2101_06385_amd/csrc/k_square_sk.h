@@ -23,6 +23,7 @@
 //    16-wide K unit, the LDS reads of the next unit are in flight.
 #pragma once
 
+#include "lds_stage.h"
 #include "sp2_control.h"
 #include "sp2_internal.h"
 
@@ -403,7 +404,7 @@ __device__ __forceinline__ void sk_body(const SquareArgs& a, const StreamK& sk, 
                 });
                 if constexpr (SE && NX) {
                     wait_vm(0);   // this wave's loads of the next slice (the only ones in flight)
-                    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                    stage_barrier();
                     __builtin_amdgcn_sched_barrier(0);
                     static_for<0, NB>([&](auto n) { B1[n] = rd(nbuf, nu, 3, rb + 32 * n); });
                     __builtin_amdgcn_sched_barrier(0);
@@ -448,7 +449,7 @@ __device__ __forceinline__ void sk_body(const SquareArgs& a, const StreamK& sk, 
             auto arrive = [&](int next) {
                 const int last = (next + ST - 2 < nsl - 1) ? next + ST - 2 : nsl - 1;   // last slice issued
                 wait_vm((last - next) * LPW);
-                __syncthreads();
+                stage_barrier();   // the reads of slice next - 1 too: mma_issue refills its buffer
             };
             vec8 pa0[MB], pa1[MB], pb0[NB], pb1[NB];   // fragments of even units
             vec8 qa0[MB], qa1[MB], qb0[NB], qb1[NB];   // fragments of odd units
@@ -764,7 +765,9 @@ __device__ __forceinline__ void sk_body(const SquareArgs& a, const StreamK& sk, 
                 tile_done<C::NT>(a, t, scr + 2 * C::NW, &s_flag);
             }
         }
-        __syncthreads();   // LDS is reused by the next item's prologue
+        // the next item's prologue refills the LDS: what this item read from it has gone into its
+        // stores or its control, so no read is still in flight
+        __syncthreads();
     }
 }
 

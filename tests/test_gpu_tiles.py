@@ -283,3 +283,17 @@ def test_fragment_major_fermi_layers_equal_register_staged_layers(prec, n):
     d, obs = sp2.fermi_apply(h, theta, c, (-3.0, 3.0), precision=prec, tile=64, workspace=ws)
     d8, obs8 = sp2.fermi_apply(h, theta, c, (-3.0, 3.0), precision=prec, tile=64, kernel=8)
     assert torch.equal(d, d8) and obs == obs8
+
+
+# batches whose largest problem has n < 1024 run the 64-tile pipeline with four stages: one to
+# four units of K behind the prologue, whole and ragged tiles, problems that stop at different layers
+@pytest.mark.parametrize("prec", ["fp16x2", "bf16x2"])
+def test_split_batch_on_64_tiles_equals_register_staged_single_calls(prec):
+    ns = (2, 33, 64, 65, 128, 200, 257, 640, 1000)
+    ws = [wl.gapped(2100 + n, n, max(1, n // 2)) for n in ns]
+    hs = [torch.from_numpy(w.h).to(DEV) for w in ws]
+    ds, infos = sp2.density_batched(hs, [w.n_occ for w in ws], precision=prec)
+    for h, w, d, i in zip(hs, ws, ds, infos):
+        d1, i1 = sp2.density(h, w.n_occ, precision=prec, tile=64, kernel=8)
+        assert torch.equal(d, d1)
+        assert i["sigma"] == i1["sigma"] and i["layers"] == i1["layers"] and i["status"] == i1["status"] == sp2.SP2_OK
