@@ -119,7 +119,8 @@ typedef struct {
     int n_padded;          /* internal matrix edge (n rounded up to the tile) */
     int tile;              /* output tile edge used */
     int kernel;            /* squaring schedule used: 1 = one workgroup per tile (also every
-                              FP32/FP64 run), 8 = the register-staged per-tile kernel,
+                              FP32/FP64 run, and the one-workgroup solves of n <= 64, see
+                              sp2_timing), 8 = the register-staged per-tile kernel,
                               2 + v = persistent schedule, variant v */
     int accelerated;       /* number of accelerated layers (they are layers 1..accelerated) */
     int gap_violation;     /* accelerated runs: first layer n where |Tr S_{n-1} - n_occ| exceeded
@@ -196,11 +197,16 @@ int sp2_density(const double* dH, int ldh, double* dD, int ldd, int n, int n_occ
 int sp2_density_static(const double* dH, int ldh, double* dD, int ldd, int n, int n_occ, double tol,
                        const sp2_options* opt, sp2_info* info, void* stream);
 
-/* Phase and per-layer durations of one sp2_density call, from HIP events on `stream`. */
+/*
+ * Phase and per-layer durations of one sp2_density call, from HIP events on `stream`.  A solve
+ * that is one launch (n <= 64 in FP16X2, BF16X2 and FP64 with tile = kernel = 0) takes total_ms
+ * from the events and the phases inside the launch from the device's wall clock (100 MHz), so
+ * they leave out what total_ms spends on the launch itself.
+ */
 typedef struct {
     double total_ms;       /* first kernel of the call .. last kernel */
     double prep_ms;        /* state init, spectral bounds, input layer */
-    double loop_ms;        /* every layer launched (max_layers control + squaring pairs) */
+    double loop_ms;        /* every layer launched, with its control */
     double loop_active_ms; /* start of the loop .. end of the last squaring that ran (S_{m-1}) */
     double refine_ms;      /* widening to FP64 and the two refinement layers */
     double final_ms;       /* final reductions and acceptance test */

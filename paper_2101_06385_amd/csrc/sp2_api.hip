@@ -412,6 +412,28 @@ struct Events {
         t->refine_square_ms[1] = (float)ms(ref[1], ref[2]);
         return hipSuccess;
     }
+    // A solve of one launch: the whole from the events, its phases from the kernel's clock.
+    hipError_t fill_tiny(sp2_timing* t, int ran, const TinyTicks* device_ticks) {
+        hipError_t e = hipEventSynchronize(end);
+        TinyTicks k;
+        int device = 0, khz = 0;
+        if (e == hipSuccess) e = hipMemcpy(&k, device_ticks, sizeof(k), hipMemcpyDeviceToHost);
+        if (e == hipSuccess) e = hipGetDevice(&device);
+        if (e == hipSuccess) e = hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device);
+        if (e != hipSuccess) return e;
+        auto span = [&](long long a, long long b) { return khz > 0 ? (double)(b - a) / khz : 0.0; };
+        memset(t, 0, sizeof(*t));
+        t->total_ms = ms(start, end);
+        t->squarings = ran;
+        t->prep_ms = span(k.start, k.prep);
+        t->loop_ms = span(k.prep, k.loop_end);
+        t->loop_active_ms = ran > 0 ? span(k.prep, k.layer[ran - 1][1]) : 0.0;
+        t->refine_ms = span(k.loop_end, k.ref[2]);
+        t->final_ms = span(k.ref[2], k.end);
+        for (int i = 0; i < ran; ++i) t->square_ms[i] = (float)span(k.layer[i][0], k.layer[i][1]);
+        for (int i = 0; i < 2; ++i) t->refine_square_ms[i] = (float)span(k.ref[i], k.ref[i + 1]);
+        return hipSuccess;
+    }
 };
 
 }  // namespace
@@ -515,7 +537,11 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
     hipStream_t s = (hipStream_t)stream;
     char* ws = (char*)dWork;
     DevState* st = (DevState*)ws;
-    Events ev(timing != nullptr, o.max_layers);
+    // The smallest problems run in one launch (k_tiny.hip) when the schedule is left open
+    // (n = 10: 325 us per call in launches per layer).
+    const bool tiny = n <= kTinyMax && n_occ > 0 && n_occ < n && o.tile == 0 && o.kernel == 0 &&
+                      o.precision != SP2_FP32;
+    Events ev(timing != nullptr, tiny ? 0 : o.max_layers);
     if (!ev.ok) return SP2_EDEVICE;
     SP2_TRY(ev.rec(ev.start, s));
 
@@ -524,17 +550,15 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
     if (!flag.ok) return SP2_EDEVICE;
 
     const DevState init = initial_state(n, n_occ, tol, o, p);
-    // The smallest problems run in one launch (k_tiny.hip) when the schedule is left open; a
-    // timed call keeps the launches that it times.  n = 10: 325 us per call in launches per layer.
-    const bool tiny = n <= kTinyMax && n_occ > 0 && n_occ < n && o.tile == 0 && o.kernel == 0 &&
-                      o.precision != SP2_FP32 && !timing;
     if (!tiny) SP2_TRY(launch_state_init(st, init, s));
 
     double* init_parts = (double*)(ws + p.off_init_parts);
     double* main_parts = (double*)(ws + p.off_main_parts);
 
+    TinyTicks* ticks = timing ? (TinyTicks*)(ws + p.off_s[0]) : nullptr;   // one launch: the states are unused
+    static_assert(sizeof(TinyTicks) <= sizeof(float) * 64 * 64, "fits the smallest state");
     if (tiny) {
-        SP2_TRY(launch_tiny(dH, ldh, dD, ldd, st, init, p.scale_log2, o.refine, flag.dev_state, s));
+        SP2_TRY(launch_tiny(dH, ldh, dD, ldd, st, init, p.scale_log2, o.refine, flag.dev_state, ticks, s));
     } else if (n_occ == 0 || n_occ == n) {
         SP2_TRY(run_trivial(dH, ldh, dD, ldd, n, n_occ, o, p, ws, flag.dev_state, s));
     } else {
@@ -743,7 +767,7 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
     if (info) fill_info(host, &p, info);
     if (timing) {
         const bool trivial = (n_occ == 0 || n_occ == n);
-        SP2_TRY(ev.fill(timing, trivial ? 0 : host.ran, trivial));
+        SP2_TRY(tiny ? ev.fill_tiny(timing, host.ran, ticks) : ev.fill(timing, trivial ? 0 : host.ran, trivial));
     }
     const int status = host.status;
     flag.release();

@@ -289,8 +289,14 @@ hipError_t launch_finalize(DevState* st, const double* dparts, int ndparts, cons
                            int ninit, DevState* host_state, hipStream_t s);
 // the whole solve of n <= kTinyMax in one workgroup (k_tiny.hip): split modes and FP64
 constexpr int kTinyMax = 64;
+// The phases of such a solve in ticks of the device's wall clock (timed calls).
+struct TinyTicks {
+    long long start, prep, loop_end, end;
+    long long ref[3];                      // before, between and after the refinement layers
+    long long layer[SP2_MAX_LAYERS][2];    // layer n at n - 1: begin, end
+};
 hipError_t launch_tiny(const double* h, int ldh, double* d, int ldd, DevState* st, const DevState& init, int scale_log2,
-                       int refine, DevState* host_state, hipStream_t s);
+                       int refine, DevState* host_state, TinyTicks* ticks, hipStream_t s);
 hipError_t launch_fill(double* d, int ldd, int n, double diag, hipStream_t s);
 hipError_t launch_split(const float* x, void* p0, void* p1, int np, int precision, int scale_log2,
                         hipStream_t s);

@@ -297,3 +297,25 @@ def test_split_batch_on_64_tiles_equals_register_staged_single_calls(prec):
         d1, i1 = sp2.density(h, w.n_occ, precision=prec, tile=64, kernel=8)
         assert torch.equal(d, d1)
         assert i["sigma"] == i1["sigma"] and i["layers"] == i1["layers"] and i["status"] == i1["status"] == sp2.SP2_OK
+
+
+# n <= 64: a timed call runs the one-workgroup solve that an untimed one runs
+@pytest.mark.parametrize("prec", ["fp16x2", "bf16x2", "fp64"])
+@pytest.mark.parametrize("n", [2, 10, 33, 64])
+def test_timed_call_of_one_workgroup_solve_is_the_untimed_one(prec, n):
+    w = wl.gapped(2200 + n, n, max(1, n // 2))
+    h = torch.from_numpy(w.h).to(DEV)
+    for kw in (dict(), dict(refine=False), dict(gap=(-0.9, 0.8)), dict(max_layers=4)):
+        d, i = sp2.density(h, w.n_occ, precision=prec, want_energy=True, **kw)
+        for _ in range(2):
+            dt, it, tm = sp2.density(h, w.n_occ, precision=prec, want_energy=True, timed=True, **kw)
+            assert torch.equal(d, dt) and it == i
+            ran = tm["squarings"]
+            assert ran == i["layers"] - (1 if i["converged"] else 0)
+            assert all(x > 0 for x in tm["square_ms"][:ran]) and not any(tm["square_ms"][ran:])
+            phases = tm["prep_ms"], tm["loop_ms"], tm["refine_ms"], tm["final_ms"]
+            assert min(phases[0], phases[1], phases[3]) > 0 and phases[2] >= 0
+            # ticks of 1e-5 ms; the event in front of the launch and the one behind it enclose it
+            assert sum(phases) <= tm["total_ms"]
+            assert sum(tm["square_ms"]) <= tm["loop_active_ms"] + 1e-5 * (ran + 1) <= tm["loop_ms"] + 2e-5 * (ran + 1)
+            assert (min(tm["refine_square_ms"]) > 0) == (kw.get("refine") is not False)
