@@ -38,41 +38,6 @@ constexpr int kCh = kRow / 16;     // 16-byte chunks per row
 // chunk c of row r is stored at c ^ swz8(r)
 __device__ inline int swz8(int r) { return (r >> 1) & 7; }
 
-typedef __attribute__((address_space(3))) unsigned char lds_byte;
-__device__ __forceinline__ unsigned lds_addr(const unsigned char* p) {
-    return (unsigned)(uintptr_t)(const lds_byte*)p;
-}
-// wave-uniform base in SGPRs and a 32-bit per-lane byte offset
-__device__ __forceinline__ void dma16s(unsigned voff, const void* sbase, unsigned lds_base) {
-    asm volatile(
-        "s_mov_b32 m0, %2\n\t"
-        "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %0, %1"
-        :
-        : "v"(voff), "s"(sbase), "s"(lds_base)
-        : "memory", "m0");
-}
-
-#define SP2_VMCNT(n) asm volatile("s_waitcnt vmcnt(" #n ")" ::: "memory")
-// waits until at most n (rounded down to an available immediate) vector-memory
-// instructions of this wave are outstanding
-__device__ __forceinline__ void wait_vm(int n) {
-    if (n >= 24) SP2_VMCNT(24);
-    else if (n >= 16) SP2_VMCNT(16);
-    else if (n >= 12) SP2_VMCNT(12);
-    else if (n >= 8) SP2_VMCNT(8);
-    else if (n >= 6) SP2_VMCNT(6);
-    else if (n >= 4) SP2_VMCNT(4);
-    else if (n >= 2) SP2_VMCNT(2);
-    else SP2_VMCNT(0);
-}
-#undef SP2_VMCNT
-
-__device__ inline double wsum(double v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
 // BT x BT output tile, four waves with one B x B block each (B = BT / 2), two stages
 template <int BT>
 struct AdjCfg {
@@ -109,7 +74,7 @@ struct Mfma<16> {
 template <int BT>
 __device__ __forceinline__ void adjoint_body(const AdjointArgs& a, int I, int J, int t, unsigned char* __restrict__ lds) {
     typedef AdjCfg<BT> C;
-    constexpr int B = C::B, ST = C::ST, LPW = C::LPW;
+    constexpr int B = C::B, ST = C::ST, LPW = C::LPW, VM = LPW * (ST - 1);
     typedef Mfma<B> M;
     constexpr int UK = 4 * (64 / B);        // K per unit: one 16-byte read per lane and fragment
     constexpr int UNITS = kBK / UK;         // units per stage
@@ -164,7 +129,7 @@ __device__ __forceinline__ void adjoint_body(const AdjointArgs& a, int I, int J,
     for (int q = 0; q < pro; ++q)
 #pragma unroll
         for (int l = 0; l < LPW; ++l) load_one(l, q, q);
-    wait_vm((pro - 1) * LPW);
+    wait_vm<VM>((pro - 1) * LPW);
     __syncthreads();
     Frags f[2];
     frags(0, 0, f[0]);
@@ -180,7 +145,7 @@ __device__ __forceinline__ void adjoint_body(const AdjointArgs& a, int I, int J,
         __builtin_amdgcn_sched_barrier(0);
         if (st + 1 < nsl) {
             const int last = (st + ST - 1 < nsl - 1) ? st + ST - 1 : nsl - 1;
-            wait_vm((last - st - 1) * LPW);
+            wait_vm<VM>((last - st - 1) * LPW);
             stage_barrier();
             frags((st + 1) % ST, 0, f[(first + UNITS) & 1]);
             mma(f[(first + UNITS - 1) & 1], buf, st + ST, st + ST < nsl);
@@ -225,9 +190,9 @@ __device__ __forceinline__ void adjoint_body(const AdjointArgs& a, int I, int J,
             if (!diag) *(f32x4*)(a.g_out + (size_t)col * np + row0) = gn;
         }
     }
-    p_tr = wsum(p_tr);
-    p_gx = wsum(p_gx);
-    p_mx = wsum(p_mx);
+    p_tr = wave_sum(p_tr);
+    p_gx = wave_sum(p_gx);
+    p_mx = wave_sum(p_mx);
     double* red = (double*)lds;   // the stages' LDS, once every wave has left them
     __syncthreads();
     if (lane == 0) {

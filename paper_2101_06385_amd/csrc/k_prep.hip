@@ -12,6 +12,7 @@
 //
 // All reductions use a fixed order (strided per-thread sums, then a fixed tree), so a
 // given input reproduces bit-identical traces, histories and statuses.
+#include "lds_stage.h"
 #include "sp2_internal.h"
 #include "sp2_control.h"
 
@@ -23,10 +24,6 @@ namespace {
 
 constexpr int kThreads = 256;
 
-__device__ inline double wave_sum(double v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 __device__ inline double wave_min(double v) {
     for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
     return v;
@@ -583,7 +580,7 @@ __global__ __launch_bounds__(kThreads) void k_select_fm(const DevState* __restri
 // the control after the last layer launched: leaves the state in its first hot block
 __global__ __launch_bounds__(64) void k_lead_finish(LeadArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lead[];
-    lead_load(a, (unsigned)(uintptr_t)(const __attribute__((address_space(3))) unsigned char*)lead);
+    lead_load(a, lds_addr(lead));
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     Coefs cf;
     (void)lead_finish(a, lead, true, &cf);

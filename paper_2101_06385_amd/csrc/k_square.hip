@@ -62,10 +62,6 @@ struct HalfOps<__bf16> {
     }
 };
 
-__device__ inline double wave_sum(double v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 
 // Block reduction of (tr, fr) in a fixed order; `scratch` holds >= 2 * waves doubles.
 template <int NWAVES>

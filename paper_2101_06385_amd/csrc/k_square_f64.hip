@@ -54,45 +54,9 @@ struct F64Cfg {
     static constexpr int STRIP = BT == 128 ? 8 : 384 / BT;
     static_assert(MB >= 1 && NB >= 1 && (2 * BPR) % NW == 0, "tile / wave mismatch");
     static_assert(ROW == 128 || ROW == 256, "a line of the cache, or two");
-    static_assert(LPW * (ST - 1) <= 24, "vmcnt range of wait_vm");
     // chunk c of row r is stored at c ^ swz(r)
     static __device__ __forceinline__ int swz(int r) { return (ROW == 128 ? r >> 1 : r) & (CH - 1); }
 };
-
-typedef __attribute__((address_space(3))) unsigned char lds_byte;
-__device__ __forceinline__ unsigned lds_addr(const unsigned char* p) {
-    return (unsigned)(uintptr_t)(const lds_byte*)p;
-}
-// wave-uniform base in SGPRs and a 32-bit per-lane byte offset
-__device__ __forceinline__ void dma16s(unsigned voff, const void* sbase, unsigned lds_base) {
-    asm volatile(
-        "s_mov_b32 m0, %2\n\t"
-        "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %0, %1"
-        :
-        : "v"(voff), "s"(sbase), "s"(lds_base)
-        : "memory", "m0");
-}
-
-#define SP2_VMCNT(n) asm volatile("s_waitcnt vmcnt(" #n ")" ::: "memory")
-// waits until at most n (rounded down to an available immediate) vector-memory
-// instructions of this wave are outstanding
-__device__ __forceinline__ void wait_vm(int n) {
-    if (n >= 24) SP2_VMCNT(24);
-    else if (n >= 16) SP2_VMCNT(16);
-    else if (n >= 12) SP2_VMCNT(12);
-    else if (n >= 8) SP2_VMCNT(8);
-    else if (n >= 6) SP2_VMCNT(6);
-    else if (n >= 4) SP2_VMCNT(4);
-    else if (n >= 2) SP2_VMCNT(2);
-    else SP2_VMCNT(0);
-}
-#undef SP2_VMCNT
-
-__device__ inline double wsum(double v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 
 // Output tile (I, J) of edge BT over all of K; t is the tile's slot in a.parts.
 // LEAD: the layer's control at its head (`lead`, lead_bytes of LDS at `dyn`) instead of the next
@@ -102,7 +66,7 @@ __device__ __forceinline__ void f64_body(const SquareArgs& a, int I, int J, int 
                                          const LeadArgs* lead = nullptr, unsigned char* __restrict__ dyn = nullptr) {
     typedef F64Cfg<BT, WM, WN, ST, ROW> C;
     constexpr int kRow = ROW, kBK = C::BK;
-    constexpr int MB = C::MB, NB = C::NB, LPW = C::LPW;
+    constexpr int MB = C::MB, NB = C::NB, LPW = C::LPW, VM = LPW * (ST - 1);
     static_assert(ST >= 2 && ST <= 4, "stages");
     const int np = a.np;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -188,14 +152,14 @@ __device__ __forceinline__ void f64_body(const SquareArgs& a, int I, int J, int 
     // read while the first loads are in flight
     const bool stop = LEAD ? ((const StateHot*)lead->hot_in)->stopped && blockIdx.x != 0 : a.skip && *a.skip;
     if (stop) {
-        wait_vm(0);
+        wait_vm<VM>(0);
         return;
     }
-    wait_vm((pro - 1) * LPW);
+    wait_vm<VM>((pro - 1) * LPW);
     __syncthreads();
     Coefs cf;
     if (LEAD && !lead_finish(*lead, dyn, blockIdx.x == 0 && wave == 0, &cf)) {   // Alg. 1 has stopped
-        wait_vm(0);
+        wait_vm<VM>(0);
         return;
     }
     Frag p, q;
@@ -203,7 +167,7 @@ __device__ __forceinline__ void f64_body(const SquareArgs& a, int I, int J, int 
     // stage `next` readable: its loads landed (this wave's), every wave past the barrier
     auto arrive = [&](int next) {
         const int last = (next + ST - 2 < nsl - 1) ? next + ST - 2 : nsl - 1;
-        wait_vm((last - next) * LPW);
+        wait_vm<VM>((last - next) * LPW);
         stage_barrier();
     };
     // units: two per stage; p holds a stage's first, q its second.  Stage st + ST refills the
@@ -259,8 +223,8 @@ __device__ __forceinline__ void f64_body(const SquareArgs& a, int I, int J, int 
         // in the stages, which every wave has left: the LDS of a workgroup stays a fifth of a CU's
         double* red = (double*)(lds + C::LDS - 256);
         int* s_done = (int*)(lds + C::LDS - 64);
-        tr = wsum(tr);
-        fr = wsum(fr);
+        tr = wave_sum(tr);
+        fr = wave_sum(fr);
         __syncthreads();
         if (lane == 0) {
             red[2 * wave] = tr;

@@ -31,6 +31,7 @@
 // 16 bytes per clock and wave: 512 cycles per unit for 384 of products).
 #pragma once
 
+#include "lds_stage.h"
 #include "sp2_control.h"
 #include "sp2_internal.h"
 
@@ -61,7 +62,6 @@ struct FmOps<__bf16> {
     }
 };
 
-typedef __attribute__((address_space(3))) unsigned char fm_lds_byte;
 // 16 bytes per lane from sbase + voff straight to LDS bytes [lds_base + off + 16 lane, + 16)
 __device__ __forceinline__ void fm_dma16(unsigned voff, const void* sbase, unsigned lds_base, unsigned off) {
     asm volatile(
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(64) void k_square_fm1(FmArgs a) {
         abase[k] = (const char*)(pl + (size_t)(2 * I + (k & 1)) * ps);
         bbase[k] = (const char*)(pl + (size_t)(2 * J + (k & 1)) * ps);
     });
-    const unsigned lo = lane * 16, ring0 = (unsigned)(uintptr_t)(const fm_lds_byte*)ring;
+    const unsigned lo = lane * 16, ring0 = lds_addr(ring);
     auto off = [&](int u) { return lo + (unsigned)(u < KU ? u : KU - 1) * 1024u; };   // past the end: the last unit
     vec8 fa[DA][4], fb[2][4];
     auto load_a = [&](auto d, auto k, unsigned o) { fa[d][k] = *(const vec8*)(abase[k] + o); };
@@ -330,7 +330,7 @@ __global__ __launch_bounds__(256) void k_square_fm(FmArgs a) {
 
     f32x4 s4[4];
     fm_load_block<NET>(a, bi0, bj0, s4);
-    if (!NET && wave == 0) lead_load(a.lead, (unsigned)(uintptr_t)(const fm_lds_byte*)dyn);
+    if (!NET && wave == 0) lead_load(a.lead, lds_addr(dyn));
 
     const int KU = a.ku;
     const size_t ps = (size_t)a.pstride * 512;   // halves per 32-row panel
@@ -348,7 +348,7 @@ __global__ __launch_bounds__(256) void k_square_fm(FmArgs a) {
         slot_off[l] = j * 1024;
         unit_of[l] = j / FPU;
     });
-    const unsigned lo = lane * 16, ring0 = (unsigned)(uintptr_t)(const fm_lds_byte*)ring;
+    const unsigned lo = lane * 16, ring0 = lds_addr(ring);
     const int KS = (KU + US - 1) / US;   // slots' worth of K
     // direct load l of this wave's share of slot w (units US w ..; past the end: the last unit
     // again) into slot w mod R
@@ -448,7 +448,7 @@ __global__ __launch_bounds__(256) void k_square_fm(FmArgs a) {
         return fm_store_block<T16, true>(a, cf, bi0, bj0, acc[0][0], s4, ps, (T16*)(ring + wave * kFmTranspose), &tr, &fr);
     }
     if (threadIdx.x < 8) red[threadIdx.x >> 1][threadIdx.x & 1] = 0.0;   // a block below the diagonal adds nothing
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    stage_barrier();
     double tr = 0.0, fr = 0.0;
     if (bi0 <= bj0 && 32 * bj0 < a.n_real) {
         fm_store_block<T16, false>(a, cf, bi0, bj0, acc[0][0], s4, ps, (T16*)(ring + wave * kFmTranspose), &tr, &fr);
@@ -458,7 +458,7 @@ __global__ __launch_bounds__(256) void k_square_fm(FmArgs a) {
             red[wave][1] = s1;
         }
     }
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    stage_barrier();
     if (threadIdx.x < 2)   // the tile's sums, blocks in row-major order
         a.parts_out[2 * (size_t)t + threadIdx.x] =
             ((red[0][threadIdx.x] + red[1][threadIdx.x]) + red[2][threadIdx.x]) + red[3][threadIdx.x];

@@ -78,69 +78,11 @@ __device__ __forceinline__ void static_for(F&& f) {
     }
 }
 
-__device__ inline double wsum(double v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-// s_waitcnt needs an immediate: wait until at most n vector-memory instructions of this
-// wavefront are outstanding, for the counts the pipeline below can ask for.
-#define SP2_VMCNT(n) asm volatile("s_waitcnt vmcnt(" #n ")" ::: "memory")
-// Rounds n down to an immediate it has (waiting for more than asked is always safe).
-__device__ __forceinline__ void wait_vm(int n) {
-    if (n >= 48) SP2_VMCNT(48);
-    else if (n >= 40) SP2_VMCNT(40);
-    else if (n >= 32) SP2_VMCNT(32);
-    else if (n >= 28) SP2_VMCNT(28);
-    else if (n >= 24) SP2_VMCNT(24);
-    else if (n >= 20) SP2_VMCNT(20);
-    else if (n >= 18) SP2_VMCNT(18);
-    else if (n >= 16) SP2_VMCNT(16);
-    else if (n >= 14) SP2_VMCNT(14);
-    else if (n >= 12) SP2_VMCNT(12);
-    else if (n >= 10) SP2_VMCNT(10);
-    else if (n >= 8) SP2_VMCNT(8);
-    else if (n >= 6) SP2_VMCNT(6);
-    else if (n >= 4) SP2_VMCNT(4);
-    else if (n >= 2) SP2_VMCNT(2);
-    else SP2_VMCNT(0);
-}
-#undef SP2_VMCNT
-
-// One 16-byte-per-lane direct load from global memory into LDS (global_load_lds_dwordx4:
-// M0 holds the wave-uniform LDS base, lane L's 16 bytes land at base + 16 L).  Issued from
-// inline asm so that the compiler does not treat it as an LDS store it must wait for
-// before every later LDS read: completion is tracked explicitly with wait_vm() and a
-// barrier before a slice is read.
-typedef __attribute__((address_space(3))) unsigned char lds_byte;
-__device__ __forceinline__ unsigned lds_addr(const unsigned char* p) {
-    return (unsigned)(uintptr_t)(const lds_byte*)p;
-}
-// The same with a wave-uniform base address in SGPRs and a 32-bit per-lane byte offset:
-// half the address data of the 64-bit form, and no per-load vector address arithmetic.
-__device__ __forceinline__ void dma16s(unsigned voff, const void* sbase, unsigned lds_base) {
-    asm volatile(
-        "s_mov_b32 m0, %2\n\t"
-        "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %0, %1"
-        :
-        : "v"(voff), "s"(sbase), "s"(lds_base)
-        : "memory", "m0");
-}
-__device__ __forceinline__ void dma16(const void* g, unsigned lds_base) {
-    asm volatile(
-        "s_mov_b32 m0, %1\n\t"
-        "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %0, off"
-        :
-        : "v"(g), "s"(lds_base)
-        : "memory", "m0");
-}
-
 // agent-coherent 16-byte store / load of FP32 partials (see st16_agent)
 __device__ __forceinline__ void store_agent(f32x4* p, f32x4 v) { st16_agent(p, __builtin_bit_cast(u32x4_t, v)); }
 __device__ __forceinline__ f32x4 load_agent(const f32x4* p) { return __builtin_bit_cast(f32x4, ld16_agent(p)); }
 
+constexpr int kMaxVm = 48;
 template <typename T16, int WM, int WN, int MB, int NB, int SK, int ST, int RP>
 struct Cfg {
     static constexpr int NW = WM * WN;
@@ -161,7 +103,7 @@ struct Cfg {
     static_assert((4 * BPR) % NW == 0, "slice blocks must split evenly over waves");
     static constexpr int LDS_ALL = LDS;
     static_assert(LDS_ALL <= 160 * 1024, "LDS budget");
-    static_assert(LPW * (ST - 1) <= 48, "vmcnt range of wait_vm");
+    static_assert(LPW * (ST - 1) <= kMaxVm, "vmcnt range");
 };
 
 // The work of one workgroup.  ONE_TILE: exactly tile t0 over all of K (one workgroup per
@@ -334,10 +276,10 @@ __device__ __forceinline__ void sk_body(const SquareArgs& a, const StreamK& sk, 
         // flight and the first one landed.  Slice q >= ST is issued right after the barrier
         // that frees buffer q % ST.  To wait for slice t, a wave allows the direct loads it
         // issued after slice t to stay outstanding (they complete in order).
-        wait_vm(0);   // nothing of the previous item may still count against vmcnt
+        wait_vm<kMaxVm>(0);   // nothing of the previous item may still count against vmcnt
         const int pro = nsl < ST ? nsl : ST;
         for (int q = 0; q < pro; ++q) issue(q, kb + q);
-        wait_vm((pro - 1) * LPW);   // the first slice has landed
+        wait_vm<kMaxVm>((pro - 1) * LPW);   // the first slice has landed
         __syncthreads();
         if constexpr (RP) {
             // Rolling fragment pipeline.  One set of fragment registers: each register takes
@@ -403,7 +345,7 @@ __device__ __forceinline__ void sk_body(const SquareArgs& a, const StreamK& sk, 
                     }
                 });
                 if constexpr (SE && NX) {
-                    wait_vm(0);   // this wave's loads of the next slice (the only ones in flight)
+                    wait_vm<kMaxVm>(0);   // this wave's loads of the next slice (the only ones in flight)
                     stage_barrier();
                     __builtin_amdgcn_sched_barrier(0);
                     static_for<0, NB>([&](auto n) { B1[n] = rd(nbuf, nu, 3, rb + 32 * n); });
@@ -448,7 +390,7 @@ __device__ __forceinline__ void sk_body(const SquareArgs& a, const StreamK& sk, 
             // Two fragment sets (P, Q), double buffered per unit.
             auto arrive = [&](int next) {
                 const int last = (next + ST - 2 < nsl - 1) ? next + ST - 2 : nsl - 1;   // last slice issued
-                wait_vm((last - next) * LPW);
+                wait_vm<kMaxVm>((last - next) * LPW);
                 stage_barrier();   // the reads of slice next - 1 too: mma_issue refills its buffer
             };
             vec8 pa0[MB], pa1[MB], pb0[NB], pb1[NB];   // fragments of even units
@@ -744,8 +686,8 @@ __device__ __forceinline__ void sk_body(const SquareArgs& a, const StreamK& sk, 
                 });
             });
             if (a.parts) {
-                tr = wsum(tr);
-                fr = wsum(fr);
+                tr = wave_sum(tr);
+                fr = wave_sum(fr);
                 double* scr = (double*)lds;   // the stages are free: every wave passed the last barrier
                 __syncthreads();
                 if (olane == 0) {

@@ -75,10 +75,6 @@ __device__ __forceinline__ double block_max(double v, double* sh) {
     __syncthreads();
     return r;
 }
-__device__ __forceinline__ double wave_sum(double v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 
 // One FP64 layer Y = alpha X^2 + beta X + gamma I on LDS matrices, upper triangle and mirror;
 // returns this wave's sums of Tr Y and ||Y||_F^2 in lane 0 (unless tr_out is null).  `out` takes Y too (n x n, ldo).

@@ -153,6 +153,12 @@ __device__ inline int xcd_tile_index(int b, int per, int ntiles) {
 
 inline int ntiles_upper(int T) { return T * (T + 1) / 2; }
 
+// Sum over the wave, in every lane.
+__device__ inline double wave_sum(double v) {
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
 // Group of a block in a launch that covers several problems: offs[0..n] are the first
 // block of each problem (offs[0] = 0, offs[n] = total); returns p with offs[p] <= b < offs[p+1].
 __device__ inline int find_group(const int* offs, int n, int b) {
@@ -164,8 +170,6 @@ __device__ inline int find_group(const int* offs, int n, int b) {
     }
     return lo;
 }
-
-
 
 // Autotuner table (sp2_tune.hip): the fastest measured schedule per (device, kind,
 // precision, key); kind single: key = n rounded up to 256; kind batched: key = hash of the
