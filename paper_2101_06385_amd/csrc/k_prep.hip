@@ -24,15 +24,6 @@ namespace {
 
 constexpr int kThreads = 256;
 
-__device__ inline double wave_min(double v) {
-    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
-    return v;
-}
-__device__ inline double wave_max(double v) {
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
 // Fixed-order block sum of `count` doubles per thread (count <= 3), result in out[] of thread 0.
 template <int C>
 __device__ inline void block_sum(double (&v)[C], double* sh /* C * kThreads */) {
@@ -619,11 +610,11 @@ __global__ __launch_bounds__(kThreads) void k_init_g(const BatchProblem* __restr
     init_body<float, T16, kSplit>(q.h, q.ldh, q.st, (float*)q.s[0], (T16*)q.pl[0][0], (T16*)q.pl[0][1],
                                   q.in_scale, q.init_parts, blockIdx.x - offs[p]);
 }
-__global__ __launch_bounds__(kThreads) void k_control_g(const BatchProblem* __restrict__ pr, int layer) {
+// the first layer's control (those behind it run in the squaring launches)
+__global__ __launch_bounds__(kThreads) void k_control_g(const BatchProblem* __restrict__ pr) {
     __shared__ double sh[kControlLds];
     const BatchProblem& q = pr[blockIdx.x];
-    if (layer == 1) control_body<kThreads>(q.st, q.init_parts, q.init_tiles, 3, layer, nullptr, sh);
-    else control_body<kThreads>(q.st, q.main_parts, q.main_tiles, 2, layer, nullptr, sh);
+    control_body<kThreads>(q.st, q.init_parts, q.init_tiles, 3, 1, nullptr, sh);
 }
 __global__ __launch_bounds__(kThreads) void k_select_g(const BatchProblem* __restrict__ pr, int per_problem) {
     const int p = blockIdx.x / per_problem;
@@ -908,8 +899,8 @@ hipError_t launch_batch_init(int precision, const BatchProblem* pr, const int* o
         return hipErrorInvalidValue;
     return hipGetLastError();
 }
-hipError_t launch_batch_control(const BatchProblem* pr, int nprob, int layer, hipStream_t s) {
-    hipLaunchKernelGGL(k_control_g, dim3(nprob), dim3(kThreads), 0, s, pr, layer);
+hipError_t launch_batch_control(const BatchProblem* pr, int nprob, hipStream_t s) {
+    hipLaunchKernelGGL(k_control_g, dim3(nprob), dim3(kThreads), 0, s, pr);
     return hipGetLastError();
 }
 hipError_t launch_batch_select(const BatchProblem* pr, int nprob, int per_problem, hipStream_t s) {

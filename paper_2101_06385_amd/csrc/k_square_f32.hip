@@ -21,7 +21,6 @@
 namespace sp2 {
 namespace {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // BT x BT output tile, four waves with one B x B block each (B = BT / 2), ST LDS stages of

@@ -308,7 +308,6 @@ __global__ __launch_bounds__(256) void k_square_fm(FmArgs a) {
     typedef FmOps<T16> Ops;
     typedef typename Ops::vec8 vec8;
     static_assert((R & (R - 1)) == 0 && R >= 2, "slot index by mask");
-    constexpr int MB = 1, NB = 1;                  // blocks per wave
     constexpr int NW = 4;                          // waves
     constexpr int FPU = 8;                         // fragments (1 KB direct loads) per unit
     constexpr int LPW = FPU * US / NW;             // direct loads per wave and slot
@@ -357,7 +356,7 @@ __global__ __launch_bounds__(256) void k_square_fm(FmArgs a) {
         fm_dma16(lo + (unsigned)(u < KU ? u : KU - 1) * 1024u, base[l], sl, slot_off[l]);
     };
     auto slot_addr = [&](int w) { return ring0 + (w & (R - 1)) * SLOT; };
-    constexpr int FPW = 2 * (MB + NB);   // fragments of a wave per unit: X0, X1 of A, X0, X1 of B
+    constexpr int FPW = 4;   // fragments of a wave per unit: X0, X1 of A, X0, X1 of B
     struct Frags {
         vec8 f[US * FPW];
     };
@@ -366,19 +365,14 @@ __global__ __launch_bounds__(256) void k_square_fm(FmArgs a) {
         const int at = k * FPU + 2 * j + (j >= 2 ? wj : wi);
         f.f[i] = *(const vec8*)(ring + (w & (R - 1)) * SLOT + at * 1024 + lo);
     };
-    f32x16 acc[MB][NB];
-    fm_for<0, MB>([&](auto m) {
-        fm_for<0, NB>([&](auto n) {
+    f32x16 acc;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[m][n][r] = 0.f;
-        });
-    });
-    constexpr int MPU = 3 * MB * NB;   // products per unit
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    constexpr int MPU = 3;   // products per unit
     auto mma_one = [&](auto i, const Frags& f) {
-        constexpr int k = i / MPU, p = (i % MPU) / (MB * NB), m = (i / NB) % MB, n = i % NB;
+        constexpr int k = i / MPU, p = i % MPU;
         constexpr int kind = ORD == 0 ? p : (p == 0 ? 1 : p == 1 ? 0 : 2);
-        acc[m][n] = Ops::mfma(f.f[k * FPW + (kind == 2 ? MB : 0) + m], f.f[k * FPW + 2 * MB + (kind == 1 ? NB : 0) + n],
-                              acc[m][n]);
+        acc = Ops::mfma(f.f[k * FPW + (kind == 2)], f.f[k * FPW + 2 + (kind == 1)], acc);
     };
     auto mma_last = [&](const Frags& f) {   // the last slot: only the units that exist
         fm_for<0, US>([&](auto k) {
@@ -445,13 +439,13 @@ __global__ __launch_bounds__(256) void k_square_fm(FmArgs a) {
         if (bi0 > bj0) return;
         if (32 * bj0 >= a.n_real) return fm_zero_block(a, bi0, bj0);
         double tr = 0.0, fr = 0.0;
-        return fm_store_block<T16, true>(a, cf, bi0, bj0, acc[0][0], s4, ps, (T16*)(ring + wave * kFmTranspose), &tr, &fr);
+        return fm_store_block<T16, true>(a, cf, bi0, bj0, acc, s4, ps, (T16*)(ring + wave * kFmTranspose), &tr, &fr);
     }
     if (threadIdx.x < 8) red[threadIdx.x >> 1][threadIdx.x & 1] = 0.0;   // a block below the diagonal adds nothing
     stage_barrier();
     double tr = 0.0, fr = 0.0;
     if (bi0 <= bj0 && 32 * bj0 < a.n_real) {
-        fm_store_block<T16, false>(a, cf, bi0, bj0, acc[0][0], s4, ps, (T16*)(ring + wave * kFmTranspose), &tr, &fr);
+        fm_store_block<T16, false>(a, cf, bi0, bj0, acc, s4, ps, (T16*)(ring + wave * kFmTranspose), &tr, &fr);
         const double s0 = wave_sum0(tr), s1 = wave_sum0(fr);
         if (lane == 0) {
             red[wave][0] = s0;

@@ -649,14 +649,12 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
             fm.out_scale = a.out_scale;
             fm.in_scale = a.in_scale;
         }
-        int waited = 0;   // chunks whose completion the host has observed
         for (int layer = 1; layer <= o.max_layers + 1; ++layer) {
             if (flag.on && layer > 1 && (layer - 1) % chunk == 0) {
                 const int c = (layer - 1) / chunk;          // chunk about to start
                 SP2_TRY(cev.record(c - 1, s));              // end of chunk c - 1
                 if (c >= 2) {
                     SP2_TRY(hipEventSynchronize(cev.ev[c - 2]));
-                    waited = c - 1;
                     if (*flag.host) break;
                 }
             }
@@ -707,7 +705,6 @@ int sp2::density_call(const double* dH, int ldh, double* dD, int ldd, int n, int
                 SP2_TRY(launch_plain_layer(o.precision, p.tile_main, p.kernel, a, s));
             SP2_TRY(ev.rec(ev.sq_e[layer], s));
         }
-        (void)waited;
         if (p.lead) {
             LeadArgs lead = lead_of(lead_done + 1);
             lead.hot_out = hot_block(st, 0);
@@ -1267,7 +1264,7 @@ bool batch_layout(int batch, const int* n, const int* n_occ, const Opts& o, Batc
     L->off_sq = off;
     off = align_up(off + sizeof(SquareArgs) * 4 * batch);   // even layer, odd layer, refine 1, refine 2
     L->off_offs = off;
-    off = align_up(off + sizeof(int) * 4 * L->n_offs);      // gersh, init, main, dstats
+    off = align_up(off + sizeof(int) * 3 * L->n_offs);      // gersh, init, dstats
     L->map_size = L->ref_map_size = 0;
     for (int i = 0; i < batch; ++i) {
         L->map_size += 8 * (size_t)L->plans[i].main_tiles;
@@ -1397,12 +1394,11 @@ static int run_batched(int batch, const double* const* dH, const int* ldh, doubl
         // ---------------------------------------------------------------- descriptors
         std::vector<BatchProblem> probs(nt);
         std::vector<SquareArgs> sq(4 * nt);
-        std::vector<int> offs(4 * L.n_offs, 0);
+        std::vector<int> offs(3 * L.n_offs, 0);
         std::vector<DevState> states(nt);
         int* o_g = offs.data();
         int* o_i = o_g + L.n_offs;
-        int* o_m = o_i + L.n_offs;
-        int* o_d = o_m + L.n_offs;
+        int* o_d = o_i + L.n_offs;
         BatchProblem* d_probs = (BatchProblem*)(ws + L.off_probs);
         for (int k = 0; k < nt; ++k) {
             const int i = L.nontrivial[k];
@@ -1420,7 +1416,6 @@ static int run_batched(int batch, const double* const* dH, const int* ldh, doubl
             q.s64 = (double*)(r + p.off_s64);
             q.y = (double*)(r + p.off_y);
             q.init_parts = (double*)(r + p.off_init_parts);
-            q.main_parts = (double*)(r + p.off_main_parts);
             q.gersh = (double*)(r + p.off_gersh);
             q.dstats = (double*)(r + p.off_dstats);
             q.ldh = ldh[i];
@@ -1430,13 +1425,11 @@ static int run_batched(int batch, const double* const* dH, const int* ldh, doubl
             q.n_occ = n_occ[i];
             q.want_energy = o.want_energy;
             q.init_tiles = p.init_tiles;
-            q.main_tiles = p.main_tiles;
             q.gersh_blocks = p.gersh_blocks;
             q.dstats_blocks = p.dstats_blocks;
             q.in_scale = ldexpf(1.f, p.scale_log2);
             o_g[k + 1] = o_g[k] + p.gersh_blocks;
             o_i[k + 1] = o_i[k] + p.init_tiles;
-            o_m[k + 1] = o_m[k] + p.main_tiles;
             o_d[k + 1] = o_d[k] + p.dstats_blocks;
             // squaring layers (even: S[0] -> S[1], odd: S[1] -> S[0]) and the two refinement layers
             for (int par = 0; par < 2; ++par) {
@@ -1449,10 +1442,10 @@ static int run_batched(int batch, const double* const* dH, const int* ldh, doubl
                 a.s_out = q.s[out];
                 a.p0_out = q.pl[out][0];
                 a.p1_out = q.pl[out][1];
-                a.parts = q.main_parts;
+                a.parts = (double*)(r + p.off_main_parts);
                 a.ctl = r;
                 a.arrivals = p.main_tiles;
-                    a.coef = ((DevState*)r)->coef;
+                a.coef = ((DevState*)r)->coef;
                 a.skip = &((DevState*)r)->skip;
                 a.np = p.np;
                 a.ld_out = p.np;
@@ -1504,8 +1497,7 @@ static int run_batched(int batch, const double* const* dH, const int* ldh, doubl
         const int* d_offs = (const int*)(ws + L.off_offs);
         const int* d_og = d_offs;
         const int* d_oi = d_og + L.n_offs;
-        const int* d_om = d_oi + L.n_offs;
-        const int* d_od = d_om + L.n_offs;
+        const int* d_od = d_oi + L.n_offs;
 
         // ---------------------------------------------------------------- the sequence
         hipStream_t cs = batch_stream();
@@ -1518,7 +1510,7 @@ static int run_batched(int batch, const double* const* dH, const int* ldh, doubl
         const int la = o.max_layers < kBatchLayersA ? o.max_layers : kBatchLayersA;
         auto layers = [&](hipStream_t s, int l0, int l1) -> int {
             for (int layer = l0; layer <= l1; ++layer) {
-                if (layer == 1) SP2_TRY(launch_batch_control(d_probs, nt, layer, s));
+                if (layer == 1) SP2_TRY(launch_batch_control(d_probs, nt, s));
                 if (layer > o.max_layers) break;
                 const SquareArgs* a = d_sq + ((layer - 1) & 1) * nt;
                 if (o.precision == SP2_FP32)
@@ -1557,7 +1549,7 @@ static int run_batched(int batch, const double* const* dH, const int* ldh, doubl
             if (!use_graph) return part(cs, which);
             const std::vector<long long> key = {which, dev, (long long)(uintptr_t)ws, (long long)L.total, L.batch,
                                                 nt, L.tile, o.precision, o.max_layers, la, map_per, ref_per, o_g[nt],
-                                                o_i[nt], o_m[nt], o_d[nt], (long long)L.off_probs,
+                                                o_i[nt], o_d[nt], (long long)L.off_probs,
                                                 (long long)L.off_sq, (long long)L.off_offs, (long long)L.off_map,
                                                 (long long)L.off_ref_map, (long long)L.off_stage};
             hipGraphExec_t exec = graph_cache_find(key);

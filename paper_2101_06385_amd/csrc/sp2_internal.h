@@ -215,19 +215,18 @@ struct BatchProblem {
     double* s64;          // refinement input (FP64)
     double* y;            // refinement intermediate (FP64)
     double* init_parts;   // 3 per input-layer tile
-    double* main_parts;   // 2 per squaring tile
     double* gersh;        // 3 per Gershgorin block
     double* dstats;       // 3 per final-check block
     int ldh, ldd, n, np, n_occ, want_energy;
-    int init_tiles, main_tiles, gersh_blocks, dstats_blocks;
-    float in_scale, pad;
+    int init_tiles, gersh_blocks, dstats_blocks;
+    float in_scale;
 };
 
 hipError_t launch_batch_gershgorin(const BatchProblem* pr, const int* offs, int nprob, int blocks, hipStream_t s);
 hipError_t launch_batch_bounds(const BatchProblem* pr, int nprob, hipStream_t s);
 hipError_t launch_batch_init(int precision, const BatchProblem* pr, const int* offs, int nprob, int blocks,
                              hipStream_t s);
-hipError_t launch_batch_control(const BatchProblem* pr, int nprob, int layer, hipStream_t s);
+hipError_t launch_batch_control(const BatchProblem* pr, int nprob, hipStream_t s);   // of layer 1
 hipError_t launch_batch_select(const BatchProblem* pr, int nprob, int per_problem, hipStream_t s);
 hipError_t launch_batch_dstats(const BatchProblem* pr, const int* offs, int nprob, int blocks, hipStream_t s);
 hipError_t launch_batch_finalize(const BatchProblem* pr, int nprob, hipStream_t s);

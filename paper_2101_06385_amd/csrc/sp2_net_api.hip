@@ -159,9 +159,10 @@ hipError_t layer(const NetPlan& p, const NetBuffers& b, int k, const float* x_in
     a.per = p.per_main;
     a.out_scale = ldexpf(1.f, -2 * p.scale_log2);
     a.in_scale = ldexpf(1.f, p.scale_log2);
-    // one workgroup per 128 tile with 64-half K-slices (the single-problem choice)
-    if (p.split && p.tile_main == 128) return launch_square_dp(p.precision, 128, 3, a, s);
-    return p.split ? launch_square_split(p.precision, p.tile_main, a, s) : launch_square_f32_mix(a, s);
+    if (!p.split) return launch_square_f32_mix(a, s);
+    // one workgroup per 128 tile with 64-half K-slices (the single-problem choice); 64 tiles are
+    // fragment-major at every size
+    return p.tile_main == 128 ? launch_square_dp(p.precision, 128, 3, a, s) : hipErrorInvalidValue;
 }
 
 }  // namespace
