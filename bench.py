@@ -62,10 +62,12 @@ SK_VARIANTS = {256: [(4, 16, 4, 0), (8, 16, 4, 0), (4, 32, 2, 0), (8, 32, 2, 0),
 
 def kernel_name(precision, tile, kernel, n, n_padded):
     """Name of the squaring kernel a call used (from sp2_info and the library's size rules)."""
+    t16 = {"fp16x2": "_Float16", "bf16x2": "__bf16"}.get(precision)
+    if n <= 64 and precision != "fp32":   # with the schedule left open: the whole solve in one launch
+        return "k_tiny<%s, %s, true>" % (t16 or "_Float16", "true" if t16 else "false")
     t64 = -(-n // 64)
     ntiles64 = t64 * (t64 + 1) // 2
-    if precision in ("fp16x2", "bf16x2"):
-        t16 = "_Float16" if precision == "fp16x2" else "__bf16"
+    if t16:
         if kernel >= 2:
             waves, sk, st, rp = SK_VARIANTS[tile][kernel - 2]
             wn = waves // 2

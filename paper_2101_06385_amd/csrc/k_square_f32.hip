@@ -23,8 +23,8 @@ namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// BT x BT output tile, four waves with one B x B block each (B = BT / 2), ST LDS stages of
-// 2 BT rows (panels I and J) of ROW bytes.
+// BT x BT output tile, four waves with a B x B part each (B = BT / 2: 2 x 2 blocks of 16, or one), ST
+// LDS stages of 2 BT rows (panels I and J) of ROW bytes.
 template <int BT, int ST, int ROW = 128>
 struct F32Cfg {
     static constexpr int B = BT / 2, NT = 256;

@@ -5,12 +5,13 @@
 //  * Bound: the matrix pipes (64 cycles per v_mfma_f64_16x16x4f64, 78.6 TFLOP/s).  Several
 //    independent workgroups of 4 waves per CU keep them busy: one's prologue, barriers and
 //    epilogue hide behind the others' products.  64 x 64 tiles with two 16 KB stages fit
-//    five to a CU; the tiles beyond the last whole round of one per CU are cut into 32 x 32
+//    five to a CU (by LDS and by registers); the tiles beyond the last whole round of one per CU are cut into 32 x 32
 //    ones so that the end of the launch is spread over the chip (k_square_f64_mix).
 //    One layer, against the 8-wave 128 x 128 workgroups with one per CU (and their
 //    persistent form with a split-K tail) used before: n = 256 17 -> 7.3 us, 832 128 -> 25 us,
-//    2112 290 -> 167 us, 4096 1265 -> 1030 us (67 TFLOP/s), 5120 2233 -> 2015 us, 8192
-//    8.90 -> 8.12 ms (68 TFLOP/s).
+//    2112 290 -> 167 us, 4096 1265 -> 1030 us (67 TFLOP/s), 5120 2233 -> 2015 us; 8192
+//    8.58 -> 8.28 ms per layer of an FP64 solve (66 TFLOP/s), 17.3 -> 16.5 ms for the two
+//    refinement layers of a mixed one.
 //  * K-stages of 16 doubles: each row of a stage is one 128-byte line.  The two row
 //    panels (I and J: X is symmetric, so both operands are K-contiguous rows) go straight
 //    from global memory into LDS with global_load_lds_dwordx4 (16 bytes per lane, a
@@ -49,8 +50,9 @@ struct F64Cfg {
     static constexpr int LPW = 2 * BPR / NW;             // direct loads per wave per stage
     static constexpr int LDS = ST * STAGE;
     // tile_of strip of 384 columns: the tiles that an XCD runs at a time drift apart in K, and narrow
-    // blocks of rows keep more of their panels in its L2 (n = 8192: 8.12 ms per layer, 8.44 with
-    // strips of 1024 columns, 8.18 with 512, 8.21 with 192; equal within 1 % up to n = 7000)
+    // blocks of rows keep more of their panels in its L2 (n = 8192: 8.29 ms per layer of an FP64
+    // solve, 8.61 with strips of 1024 columns; 512 and 192 are 1 % slower than 384; equal within 1 % up
+    // to n = 7000)
     static constexpr int STRIP = BT == 128 ? 8 : 384 / BT;
     static_assert(MB >= 1 && NB >= 1 && (2 * BPR) % NW == 0, "tile / wave mismatch");
     static_assert(ROW == 128 || ROW == 256, "a line of the cache, or two");

@@ -3,7 +3,9 @@
 // Computes the same layer as k_square_dp (Y = alpha X^2 + beta X + gamma I from the planes
 // X0, X1, X0 X0 + X0 X1 + X1 X0 of Eq. Square over the upper triangle), with the same chain of
 // products per element, hence the same bits.  Such a layer is bound by latency (dependent
-// trips to memory, launches) and by LDS bandwidth on the few busy CUs, not by the matrix pipes:
+// trips to memory, launches), not by the matrix pipes or the LDS (counters at n = 777: 91 busy CUs,
+// matrix pipes busy 0.20 and LDS reads under way 0.18 of their cycles, waves waiting for memory
+// counters or barriers 0.49):
 //
 //  * Fragment-major planes: a plane is stored as 32-row x 16-column blocks of 1 KB in the
 //    order in which v_mfma_f32_32x32x16 takes them (lane l = row + 32 (k / 8), 8 halves each),
@@ -23,12 +25,12 @@
 // per-tile kernel with control launches: n = 65 6.9 against 11.2 us, 400 8.8 against 16.1, 777
 // 11.8 against 24, 1000 13.4 against 24.8, 1400 18 against 30, 2000 38 against 66, 2100 41
 // against 55 us.  A layer of the network, against k_square_dp on 128-tiles: n = 512 8 against 27,
-// 1400 16 against 39, 2048 38 against 50, 2900 102 against 122 us.  A 64 x 64 tile takes 192 LDS cycles per 16-wide unit of K (8 KB in, 16 KB
-// out) for 96 cycles of products per wave; the clock holds about 1.65 GHz here.  Tried and not
-// kept: one wave per 32 x 32 block (equal up to n = 550, half as fast at 1700), two waves of
-// 64 x 32 (10-20 % slower below n = 2000), the tiles beyond a whole round of one per CU cut into
-// 32 x 32 blocks (40 against 28 us at n = 1700), all fragments in registers (their loads return
-// 16 bytes per clock and wave: 512 cycles per unit for 384 of products).
+// 1400 16 against 39, 2048 38 against 50, 2900 102 against 122 us.  The clock holds about 1.65 GHz.
+// Tried and not kept: one wave per 32 x 32 block (equal up to n = 550, half as fast at 1700), two
+// waves of 64 x 32 (10-20 % slower below n = 2000; not timed above, where the one-wave kernel
+// serves), the tiles beyond a whole round of one per CU cut into 32 x 32 blocks (40 against 28 us at
+// n = 1700), all fragments in registers (their loads return 16 bytes per clock and wave: 512 cycles
+// per unit for 384 of products).
 #pragma once
 
 #include "lds_stage.h"
@@ -188,6 +190,9 @@ __device__ __forceinline__ void fm_zero_block(const FmArgs& a, int bi, int bj) {
 // unit, whatever its depth, against 384 of the unit's 12 products), so the A fragments come
 // straight into registers, DA units ahead, and the B fragments through a ring of R units in
 // LDS; reads and loads go between the products.
+// Bound: the chain of products of a wave.  n = 2100 (counters): 561 waves, four to a CU, so 140 CUs work;
+// their matrix pipes are busy 0.69 and their LDS reads under way 0.14 of the cycles, without bank
+// conflicts.
 template <typename T16, int R, int DA, int ORD, bool NET = false>
 __global__ __launch_bounds__(64) void k_square_fm1(FmArgs a) {
     typedef FmOps<T16> Ops;
@@ -460,7 +465,7 @@ __global__ __launch_bounds__(256) void k_square_fm(FmArgs a) {
 
 }  // namespace
 
-// variant: ORD + 2 x (0: 4-wave workgroups, 1: one wave) (see fm_variant in sp2_api.hip); a.coef: a
+// variant: ORD + 2 x (0: 4-wave workgroups, 1: one wave) (see fm_variant in k_square2.hip); a.coef: a
 // layer of the network
 template <typename T16>
 hipError_t launch_fm_t(int variant, const FmArgs& a, hipStream_t s) {

@@ -107,7 +107,7 @@ constexpr int kSkVariants = 6;
 // range) and 2v + 1 (last tile); `counter` then counts arrivals per tile.
 struct StreamK {
     int grid = 0, rounds = 0, tail_tiles = 0, chunks = 0;
-    float* partial = nullptr;     // FP32 partial tiles (split squaring, adjoint)
+    float* partial = nullptr;     // FP32 partial tiles
     int* counter = nullptr;       // arrivals per tail tile, counted modulo chunks
     int stream_k = 0;             // slices per stream-K unit; 0: whole rounds + split tail
     int pad = 0;
