@@ -116,9 +116,16 @@ bool sk_resolve(const Plan& p, StreamK* sk, int* variant) {
 // On 64 tiles the pipeline has 4 stages of 32 halves (n = 777: 15.4 us per layer with the next
 // layer's control, against 18.2 us + 4.0 us control + 2 us gap register-staged; 2 stages of
 // 64 halves are 4 % slower at n = 777 and 4 % faster at 1500, 4 stages of 64 slower at both).
+// Its 64 KB hold two workgroups per CU: a layer without control with more than two and at most
+// three 64-tiles per CU goes to the register-staged kernel, which has room for all of them at once
+// (n = 2048 108.6 us per call against 115.1, 2432 134.2 against 137.1; 1984 97.3 against 96.7,
+// 2496 161.3 against 148.5; the bits are the same).
 constexpr int kKernelLegacyTile = 8;
 constexpr int kDpSingle128 = 3;
+constexpr int kCus = 256;
 hipError_t launch_split_tile_layer(int precision, int tile, int kernel, const SquareArgs& a, hipStream_t s) {
+    const bool third = tile == 64 && kernel == 0 && !a.ctl && a.ntiles > 2 * kCus && a.ntiles <= 3 * kCus;
+    if (third) return launch_square_split(precision, tile, a, s);
     if (kernel != kKernelLegacyTile)
         return launch_square_dp(precision, tile, tile == 128 ? kDpSingle128 : 0, a, s);
     return launch_square_split(precision, tile, a, s);

@@ -319,3 +319,14 @@ def test_timed_call_of_one_workgroup_solve_is_the_untimed_one(prec, n):
             assert sum(phases) <= tm["total_ms"]
             assert sum(tm["square_ms"]) <= tm["loop_active_ms"] + 1e-5 * (ran + 1) <= tm["loop_ms"] + 2e-5 * (ran + 1)
             assert (min(tm["refine_square_ms"]) > 0) == (kw.get("refine") is not False)
+
+
+# one layer on 64-tiles with the schedule left open: more than two, at most three tiles per CU (513 .. 768)
+# take the register-staged kernel; 496, 528, 741 and 780 tiles
+@pytest.mark.parametrize("prec", ["fp16x2", "bf16x2"])
+@pytest.mark.parametrize("n", [1984, 1985, 2432, 2433])
+def test_split_layer_of_either_schedule_has_the_same_bits(prec, n):
+    x = _sym(n, 2300 + n, torch.float32)
+    y, s = sp2.square(x, -1.0, 2.0, 0.25, precision=prec, tile=64)
+    y1, s1 = sp2.square(x, -1.0, 2.0, 0.25, precision=prec, tile=64, kernel=1)
+    assert torch.equal(y, y1) and s == s1
